@@ -22,7 +22,9 @@ hipError_t launch_stats(char* ws, const Layout& L, hipStream_t st);
 hipError_t set_step_lds_limit(size_t bytes);
 hipError_t step_static_lds(size_t* bytes);
 size_t step_lds_bytes(uint32_t maxL, uint32_t W, uint32_t ucap, uint32_t rcap, uint32_t path_sets);
-size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t ucap, uint32_t rcap);
+size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t nbuf, uint32_t ucap, uint32_t rcap);
+uint32_t step_pipe_evictors();
+uint32_t step_pipe_jobs();
 hipError_t noalloc_scratch(int device, void** ptr, size_t* bytes);
 hipError_t launch_stats_into(char* ws, const Layout& L, uint64_t w0, uint32_t n, uint64_t* fifo, uint64_t fifo_words,
                              kvr_worker_stats* out, hipStream_t st);
@@ -38,9 +40,10 @@ struct kvr_ctx {
   uint32_t seen_bits;  // device status bits already reported to the host
   uint32_t ucap;       // candidate entries the step kernel stages in LDS
   uint32_t rcap;       // draw words the step kernel precomputes in LDS
-  uint32_t pipe;       // 1: the pipelined step kernel (a separate evicting wave)
-  uint32_t ucap_p;     // its staged candidates
-  uint32_t rcap_p;     // its draw words per insertion (two insertions' worth)
+  uint32_t pipe;       // 1: the pipelined step kernel (separate evicting waves)
+  uint32_t ucap_p;     // its staged candidates per evicting wave
+  uint32_t rcap_p;     // its ring of draw words
+  uint32_t nbuf;       // its query buffers
   void* scratch;       // the device's static scratch of kvr_stats_noalloc
   size_t scratch_bytes;
 };
@@ -234,25 +237,30 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
     if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(max dynamic LDS)");
   }
   // the pipelined kernel (RLT, prompts only, no router tree, single-query
-  // processing): the draw words of two insertions take 2/5 of the room
-  const bool pipe = cfg->evict == KVR_EVICT_RLT && !cfg->router_tree && cfg->batch_size == 1 && !cfg->cache_responses;
+  // processing), where its state fits
+  const size_t lds_room = (size_t)lds_max - static_lds;
+  const bool pipe = cfg->evict == KVR_EVICT_RLT && !cfg->router_tree && cfg->batch_size == 1 && !cfg->cache_responses &&
+                    kvr::step_lds_bytes_pipe(L.maxL, L.W, 2, 0, 0) <= lds_room;
   size_t rcap_p = 0, ucap_p = 0;
+  uint32_t nbuf = 2;
   if (pipe) {
-    const size_t qb = kvr::step_lds_bytes_pipe(L.maxL, L.W, 0, 0);
-    if (qb + static_lds > (size_t)lds_max)
-      return fail(KVR_EINVAL, "max_query_tokens does not fit in LDS (" + std::to_string(lds_max) + " bytes)");
-    // (the candidate list is short on these workloads: 512 staged entries
-    // first, then the draw words of two whole insertions, then the rest)
-    size_t room_p = (size_t)lds_max - static_lds - qb;
-    const size_t ufirst = room_p >= 512u * 16u ? 512u * 16u : 0u;
-    rcap_p = (room_p - ufirst) / 8u;
-    if (rcap_p > L.maxL) rcap_p = L.maxL;
-    room_p -= rcap_p * 8u;
-    ucap_p = room_p / 16u;
+    const size_t ne = kvr::step_pipe_evictors();
+    // 512 staged candidates per evicting wave first (the candidate lists are
+    // short on these workloads), then a third query buffer where the draw
+    // words of two whole insertions still fit beside it, then the draw words
+    // of as many insertions as can be under way, then more candidates
+    const size_t ufirst = ne * 512u * 16u;
+    if (kvr::step_lds_bytes_pipe(L.maxL, L.W, 3, 512, 2u * L.maxL) <= lds_room) nbuf = 3;
+    size_t left = lds_room - kvr::step_lds_bytes_pipe(L.maxL, L.W, nbuf, 0, 0);
+    rcap_p = (left > ufirst ? left - ufirst : 0u) / 4u;
+    const size_t most = (size_t)(kvr::step_pipe_jobs() - 1u) * L.maxL;
+    if (rcap_p > most) rcap_p = most;
+    left -= rcap_p * 4u;
+    ucap_p = left / (ne * 16u);
     if (ucap_p > 8192) ucap_p = 8192;
     if (ucap_p < 64) ucap_p = 0;
-    if (kvr::step_lds_bytes_pipe(L.maxL, L.W, (uint32_t)ucap_p, (uint32_t)rcap_p) > 65536) {
-      e = kvr::set_step_lds_limit((size_t)lds_max - static_lds);
+    if (kvr::step_lds_bytes_pipe(L.maxL, L.W, nbuf, (uint32_t)ucap_p, (uint32_t)rcap_p) > 65536) {
+      e = kvr::set_step_lds_limit(lds_room);
       if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(max dynamic LDS)");
     }
   }
@@ -269,6 +277,7 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
   c->pipe = pipe ? 1u : 0u;
   c->ucap_p = (uint32_t)ucap_p;
   c->rcap_p = (uint32_t)rcap_p;
+  c->nbuf = nbuf;
   c->L = L;
   c->C.seed = cfg->seed;
   c->C.alpha_cached = cfg->alpha_cached;
@@ -328,6 +337,8 @@ kvr_status kvr_route_batch(kvr_ctx* ctx, uint32_t n, const int32_t* d_tokens, co
   a.all_hits = d_all_hits;
   a.n = n;
   a.pipe = ctx->pipe;
+  a.nbuf = ctx->nbuf;
+  a.check = 0;
   a.pad2 = 0;
   a.ucap = ctx->pipe ? ctx->ucap_p : ctx->ucap;
   a.rcap = ctx->pipe ? ctx->rcap_p : ctx->rcap;

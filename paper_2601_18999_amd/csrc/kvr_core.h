@@ -318,6 +318,27 @@ __device__ __forceinline__ int32_t mark_top(const St& s, const NodeRec& nd, int3
   return top;
 }
 
+// ---------------------------------------------------------------- uniform reads
+
+__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
+// A node record in scalar registers: one 32-byte load, a word per lane.
+__device__ __forceinline__ NodeRec load_node(const NodeRec* nodes, int32_t id) {
+  if (KVR_WAVE == 1) return nodes[id];
+  const int32_t v = reinterpret_cast<const int32_t*>(nodes + id)[lane_id() & 7];
+  NodeRec r;
+  r.parent = __builtin_amdgcn_readlane(v, 0);
+  r.off = (uint32_t)__builtin_amdgcn_readlane(v, 1);
+  r.len = __builtin_amdgcn_readlane(v, 2);
+  r.nchild = __builtin_amdgcn_readlane(v, 3);
+  r.coff = (uint32_t)__builtin_amdgcn_readlane(v, 4);
+  r.ccap = __builtin_amdgcn_readlane(v, 5);
+  r.mphase = (uint32_t)__builtin_amdgcn_readlane(v, 6);
+  r.ma = __builtin_amdgcn_readlane(v, 7);
+  return r;
+}
+
 // ---------------------------------------------------------------- array tools (wave)
 
 __device__ int32_t arr_find(const int32_t* a, uint32_t n, int32_t v) {
@@ -523,28 +544,38 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 // Copying collector: move every live edge and child array of the active
 // semispace to the other one, compacted, and switch semispaces.  Node slots
 // are taken 64 at a time: one lane reads each node, a prefix sum gives the
-// new offsets (edge padded to an even length, then the child array), and
-// the wave copies the blocks.  False (and nothing switched) when the live
-// data does not fit a semispace.
+// new offsets (the edge, then the child array), and the wave copies the
+// blocks.  While that leaves half of the semispace free, an edge keeps its
+// place within its 16 bytes (new edges are placed in line with the query
+// buffer, so that matches compare 16 bytes per lane); else edges are packed,
+// padded to an even length.  False (and nothing switched) when the live data
+// does not fit a semispace.
 // Out of line (it runs rarely) and with scalar arguments only, so the
 // caller's cache state never has to live in memory.  Returns the new arena
 // top, or ~0 when the live data does not fit.
 __device__ __noinline__ uint64_t collect_arena(NodeRec* nodes, const int32_t* src, int32_t* dst, uint32_t hwm,
                                                uint32_t A, const int32_t* ssrc, int32_t* sdst) {
   wave_mem_sync();  // the caller's stores (e.g. a new edge) before they are copied
-  uint64_t top = 0;
+  const uint32_t sbase = (uint32_t)(reinterpret_cast<uintptr_t>(src) >> 2);
+  const uint32_t dbase = (uint32_t)(reinterpret_cast<uintptr_t>(dst) >> 2);
+  uint64_t top = 0, top4 = 0;
   // sizes first: the live data must fit
   for (uint32_t b = 0; b < hwm; b += KVR_WAVE) {
     const uint32_t x = b + (uint32_t)lane_id();
-    uint32_t sz = 0;
+    uint32_t sz = 0, sz4 = 0;
     if (x < hwm) {
       const NodeRec nd = nodes[x];
-      if (nd.parent != -2) sz = (((uint32_t)nd.len + 1u) & ~1u) + 2u * (uint32_t)nd.ccap;
+      if (nd.parent != -2) {
+        sz = (((uint32_t)nd.len + 1u) & ~1u) + 2u * (uint32_t)nd.ccap;
+        sz4 = ((((sbase + nd.off) & 3u) + (uint32_t)nd.len + 3u) & ~3u) + ((2u * (uint32_t)nd.ccap + 3u) & ~3u);
+      }
     }
     top += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(sz), KVR_WAVE - 1);
+    top4 += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(sz4), KVR_WAVE - 1);
   }
   if (top > A) return ~0ull;
-  top = 0;
+  const bool in_line = top4 + 4u <= A / 2u;
+  top = in_line ? (0u - dbase) & 3u : 0u;
   for (uint32_t b = 0; b < hwm; b += KVR_WAVE) {
     const uint32_t x = b + (uint32_t)lane_id();
     NodeRec nd;
@@ -556,11 +587,13 @@ __device__ __noinline__ uint64_t collect_arena(NodeRec* nodes, const int32_t* sr
     nd.coff = 0;
     if (x < hwm) nd = nodes[x];
     const bool live = x < hwm && nd.parent != -2;
-    const uint32_t elen = live ? (((uint32_t)nd.len + 1u) & ~1u) : 0u;
-    const uint32_t sz = live ? elen + 2u * (uint32_t)nd.ccap : 0u;
+    const uint32_t place = in_line ? (sbase + nd.off) & 3u : 0u;
+    const uint32_t grain = in_line ? 3u : 1u;
+    const uint32_t elen = live ? (place + (uint32_t)nd.len + grain) & ~grain : 0u;
+    const uint32_t sz = live ? elen + ((2u * (uint32_t)nd.ccap + grain) & ~grain) : 0u;
     const uint32_t incl = wave_inclusive_sum(sz);
-    const uint32_t noff = (uint32_t)top + incl - sz;
-    const uint32_t ncoff = noff + elen;
+    const uint32_t noff = (uint32_t)top + incl - sz + place;
+    const uint32_t ncoff = (uint32_t)top + incl - sz + elen;
     uint64_t todo = __ballot(live);
     while (todo) {
       const int j = first_lane(todo);
@@ -615,6 +648,52 @@ __device__ __forceinline__ bool arena_alloc(const Ptrs& P, St& s, uint32_t words
   off = (uint32_t)top;
   s.arena_top = (uint32_t)(top + words);
   return true;
+}
+
+// Arena space for an edge whose first token is at depth d of its path, its
+// 16-byte blocks in line with those of a query buffer.
+__device__ __forceinline__ bool place_edge(const Ptrs& P, St& s, uint32_t words, uint32_t d, uint32_t& off) {
+  const uint32_t base = (uint32_t)(reinterpret_cast<uintptr_t>(arena_of(P, s.arena_sel)) >> 2);
+  const uint32_t pad = (d - base - s.arena_top) & 3u;
+  if ((uint64_t)s.arena_top + pad + words <= P.A) {
+    off = s.arena_top + pad;
+    s.arena_top = off + words;
+    return true;
+  }
+  // a collection, then in line if it still fits, else anywhere
+  uint32_t any;
+  if (!arena_alloc(P, s, words, false, any)) return false;
+  const uint32_t base2 = (uint32_t)(reinterpret_cast<uintptr_t>(arena_of(P, s.arena_sel)) >> 2);
+  const uint32_t pad2 = (d - base2 - any) & 3u;
+  if ((uint64_t)s.arena_top + pad2 <= P.A) {
+    s.arena_top += pad2;
+    any += pad2;
+  }
+  off = any;
+  return true;
+}
+
+// ar[eo, eo + n) = q[d, d + n) (q in LDS): 16 bytes per lane
+// where the two line up.  Stores only; nothing waits for them.
+__device__ __forceinline__ void copy_words(int32_t* ar, uint32_t eo, const int32_t* q, int32_t d, int32_t n) {
+  const uint32_t ea = (uint32_t)(reinterpret_cast<uintptr_t>(ar + eo) >> 2);
+  int32_t head = n;  // words stored one by one before the blocks
+  int32_t nb = 0;
+  if (((ea - (uint32_t)d) & 3u) == 0u && (reinterpret_cast<uintptr_t>(q) & 15u) == 0u) {
+    head = (4 - (d & 3)) & 3;
+    if (head > n) head = n;
+    nb = (n - head) >> 2;
+    int4* eb = reinterpret_cast<int4*>(ar + eo + head);
+    const int4* qb = reinterpret_cast<const int4*>(q + d + head);
+#pragma unroll 4
+    for (int32_t k = lane_id(); k < nb; k += KVR_WAVE) eb[k] = qb[k];
+  }
+  // the words outside the blocks: [0, head) and [head + 4 nb, n)
+  const int32_t tail = n - head - 4 * nb;
+  for (int32_t k = lane_id(); k < head + tail; k += KVR_WAVE) {
+    const int32_t x = k < head ? k : k + 4 * nb;
+    ar[eo + (uint32_t)x] = q[d + x];
+  }
 }
 
 __device__ __forceinline__ int32_t node_alloc(const Ptrs& P, St& s) {
@@ -694,6 +773,13 @@ __device__ int32_t child_slot(const int32_t* ar, const NodeRec& na, int32_t c) {
   return -1;
 }
 
+// A child entry in one store (a match may read it meanwhile).
+__device__ __forceinline__ void child_put(int32_t* p, const int2& e) {
+  if (lane_id() == 0)
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), ((uint64_t)(uint32_t)e.y << 32) | (uint32_t)e.x, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Remove child c of node a, whose record (as read by the caller) is na; na
 // is updated to the new child count.  The last entry, which moves into the
 // removed one's slot, is taken from the chunk just read when it is there
@@ -721,10 +807,11 @@ __device__ __forceinline__ bool child_remove_rec(const Ptrs& P, const St& s, int
   }
   if (pos < 0) return false;
   if (pos != last && !have_last) lst = *reinterpret_cast<const int2*>(ar + na.coff + 2 * last);
-  if (lane_id() == 0) {
-    if (pos != last) *reinterpret_cast<int2*>(ar + na.coff + 2 * pos) = lst;
-    P.nodes[a].nchild = last;
-  }
+  // the moved entry before the count: a match that reads the node meanwhile
+  // finds every child that stays
+  if (pos != last) child_put(ar + na.coff + 2 * pos, lst);
+  wave_mem_sync();
+  if (lane_id() == 0) P.nodes[a].nchild = last;
   wave_mem_sync();
   na.nchild = last;
   return true;
@@ -736,13 +823,10 @@ __device__ __forceinline__ bool child_remove(const Ptrs& P, const St& s, int32_t
   int32_t pos = child_slot(ar, na, c);
   if (pos < 0) return false;
   int32_t last = na.nchild - 1;
-  if (lane_id() == 0) {
-    if (pos != last) {
-      ar[na.coff + 2 * pos] = ar[na.coff + 2 * last];
-      ar[na.coff + 2 * pos + 1] = ar[na.coff + 2 * last + 1];
-    }
-    P.nodes[a].nchild = last;
-  }
+  // the moved entry, whole, before the count (as above)
+  if (pos != last) child_put(ar + na.coff + 2 * pos, *reinterpret_cast<const int2*>(ar + na.coff + 2 * last));
+  wave_mem_sync();
+  if (lane_id() == 0) P.nodes[a].nchild = last;
   wave_mem_sync();
   return true;
 }
@@ -1158,15 +1242,25 @@ __device__ __forceinline__ void stage_erase(const UStage& u, uint32_t n, uint32_
   }
 }
 
+// What the second half of an insertion does with its new leaf's place in the
+// leaf list and with the worker's state: by default the first half has
+// entered the leaf already, and the state goes back to the header.
+struct HeaderHook {
+  // called before anything edits or reads the leaf list
+  __device__ __forceinline__ void before_list(const Ptrs&, St&) {}
+  __device__ __forceinline__ void keep(const Ptrs& P, const St& s) { store_st(P.hdr, s); }
+};
+
 // evict_block with U staged in LDS (same draws, same result), kDraws draws
 // per lane: draw j of the block is taken by lane j % wave in slot j / wave.
 // Every draw of the block first trims its candidate with an LDS atomic; the
 // values the atomics return show whether some candidate ran out of
 // evictable tokens.  Only then (rarely) is the first exhausting draw in draw
 // order found exactly and the draws after it are undone.
-template <int kDraws>
+template <int kDraws, typename Hook>
 __device__ __forceinline__ bool evict_block_staged(const Ptrs& P, St& s, const InsertArgs& ia, const UStage& u,
-                                                   uint64_t dctr, uint32_t cnt, uint32_t& done, bool& changed) {
+                                                   uint64_t dctr, uint32_t cnt, uint32_t& done, bool& changed,
+                                                   Hook& hook) {
   changed = false;
   const int lane = lane_id();
   bool act[kDraws];
@@ -1303,6 +1397,8 @@ __device__ __forceinline__ bool evict_block_staged(const Ptrs& P, St& s, const I
     }
     // the node is empty: drop it; its parent may take its place.  The
     // parent's record is read together with the leaf list.
+    hook.before_list(P, s);
+    if (s.err) return false;
     NodeRec np = P.nodes[pf];
     const int32_t li = arr_find(P.leaf, s.nleaves, nf);
     if (li < 0) {
@@ -1553,19 +1649,19 @@ __device__ __forceinline__ uint32_t rlt_insert_front(const Ptrs& P, const Insert
     if (!rank_helper) pos = new_leaf_rank(P, s, ar, split ? last : a, 0, split ? 1 : 0, qs[h]);
     // ---- the new leaf node holding q[h, L)
     bool ranked = false;
-    if (rank_helper && (uint64_t)s.arena_top + (uint32_t)nload > P.A) {
+    if (rank_helper && (uint64_t)s.arena_top + (uint32_t)nload + 3u > P.A) {
       // a collection is coming, which moves what the other wave reads
       pos = await_rank(ia);
       if (pos < 0) pos = new_leaf_rank(P, s, ar, a, 0, 0, qs[h]);
       ranked = true;
     }
     uint32_t eoff;
-    if (!arena_alloc(P, s, (uint32_t)nload, false, eoff)) goto fail;
+    if (!place_edge(P, s, (uint32_t)nload, (uint32_t)h, eoff)) goto fail;
     ar = arena_of(P, s.arena_sel);
     // no fence here: nothing in this insertion reads the new edge's tokens
     // except a collection, which fences first; the fence at the end of the
     // insertion orders them before the next match
-    wave_copy(ar + eoff, qs + h, nload);
+    copy_words(ar, eoff, qs, h, nload);
     if (rank_helper && !ranked) {
       // if the other wave could not, or takes too long, rank here (the tree
       // is as the local ranking above would see it)
@@ -1661,10 +1757,9 @@ fail:
 // draw's Philox word), in blocks of draws that commute; the phase reset
 // where |T| reaches B+1 among the loaded tokens; then the marks of the
 // loaded tokens and the cache header.  Returns the KVR_DEV_* error bits.
-template <bool PT = false>
-__device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJob& job, const UStage& ustage,
-                                                    int64_t* dbg, PhaseClock* clk = nullptr,
-                                                    int ph_evict = KVR_PHASE_EVICT, int ph_finish = KVR_PHASE_FINISH) {
+template <bool PT, typename Hook>
+__device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job, const UStage& ustage, int64_t* dbg,
+                                              PhaseClock* clk, int ph_evict, int ph_finish, Hook& hook) {
   St s = job.s;
   const int32_t h = job.h, L = job.L, l = job.l;
   if (h < L) {
@@ -1693,7 +1788,11 @@ __device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJo
         s.U_valid = 0;
         applied = true;
       }
-      if (!s.U_valid) rebuild_U(P, s, l);
+      if (!s.U_valid) {
+        hook.before_list(P, s);
+        if (s.err) goto fail;
+        rebuild_U(P, s, l);
+      }
       if (s.nU == 0) {
         // no unmarked leaf: a new phase starts with the current token
         if (staged) {
@@ -1702,6 +1801,8 @@ __device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJo
         }
         s.phase += 1;
         hdr_count(&P.hdr->forced_resets, 1u);
+        hook.before_list(P, s);
+        if (s.err) goto fail;
         rebuild_U(P, s, l);
         reset_at = p;
         applied = true;
@@ -1735,7 +1836,7 @@ __device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJo
           }
           uint32_t done = 0;
           bool changed = false;
-          ok = evict_block_staged<kEvictDraws>(P, s, iq, ustage, (uint64_t)du, cnt, done, changed);
+          ok = evict_block_staged<kEvictDraws>(P, s, iq, ustage, (uint64_t)du, cnt, done, changed, hook);
           if (!ok) break;
           done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
           du += done;
@@ -1753,7 +1854,8 @@ __device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJo
           if (have == 0u) iq.rn = 0;
         }
         uint32_t done = 0;
-        if (!evict_block(P, s, iq, dctr, cnt, done)) goto fail;
+        hook.before_list(P, s);
+        if (s.err || !evict_block(P, s, iq, dctr, cnt, done)) goto fail;
         dctr += done;
         k += done;
       }
@@ -1791,13 +1893,15 @@ __device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJo
     s.size = s.size + (uint32_t)nload - nev;
     hdr_count(&P.hdr->loads, (uint64_t)nload);
     hdr_count(&P.hdr->evictions, nev);
+    hook.before_list(P, s);
+    if (s.err) goto fail;
   }
-  store_st(P.hdr, s);
+  hook.keep(P, s);
   wave_mem_sync();
   clock_mark<PT>(clk, ph_finish);
   return 0;
 fail:
-  store_st(P.hdr, s);
+  hook.keep(P, s);
   if (dbg) {
     dbg[0] = s.dbg_check;
     dbg[1] = s.dbg_val[0];
@@ -1805,6 +1909,14 @@ fail:
     dbg[3] = s.dbg_val[2];
   }
   return s.err ? s.err : (uint32_t)KVR_DEV_INTERNAL;
+}
+
+template <bool PT = false>
+__device__ __forceinline__ uint32_t rlt_insert_back(const Ptrs& P, const EvictJob& job, const UStage& ustage,
+                                                    int64_t* dbg, PhaseClock* clk = nullptr,
+                                                    int ph_evict = KVR_PHASE_EVICT, int ph_finish = KVR_PHASE_FINISH) {
+  HeaderHook hook;
+  return rlt_evict<PT>(P, job, ustage, dbg, clk, ph_evict, ph_finish, hook);
 }
 
 // RLT insertion of q[0, L) into the worker's cache on one wave: the front
@@ -2138,10 +2250,10 @@ __device__ __forceinline__ uint32_t lru_insert(const Ptrs& P, const InsertArgs& 
       }
     }
     uint32_t eoff;
-    if (!arena_alloc(P, s, (uint32_t)nload, false, eoff)) goto fail;
+    if (!place_edge(P, s, (uint32_t)nload, (uint32_t)h, eoff)) goto fail;
     ar = arena_of(P, s.arena_sel);
     st = P.stamp0 + (size_t)s.arena_sel * P.A;
-    wave_copy(ar + eoff, qs + h, nload);
+    copy_words(ar, eoff, qs, h, nload);
     lru_stamp(st, eoff, nload, jq);
     wave_mem_sync();
     l = node_alloc(P, s);
@@ -2239,44 +2351,63 @@ fail:
   return s.err ? s.err : (uint32_t)KVR_DEV_INTERNAL;
 }
 
-// First index k < n with e[k] != q[k] (e in global memory, q in LDS), or
-// n.  The edge is read in aligned 16-byte blocks of four tokens, one block
-// per lane and KVR_MATCH_UNROLL blocks per lane in flight (up to 2,048
-// tokens per round trip on a 64-lane wave).  The first block may start up
-// to three tokens before e and the last end up to three after e + n, always
-// inside the same aligned 16 bytes; those tokens are not compared.
+// 16-byte compare loads in flight per lane
 #ifndef KVR_MATCH_UNROLL
 #define KVR_MATCH_UNROLL 8
 #endif
-template <int kUnroll = KVR_MATCH_UNROLL>
-__device__ int32_t first_mismatch(const int32_t* e, const int32_t* q, int32_t n) {
-  const uintptr_t ea = reinterpret_cast<uintptr_t>(e);
-  const int32_t lead = (int32_t)((ea & 15u) >> 2);
-  const int4* base = reinterpret_cast<const int4*>(ea - (uintptr_t)lead * 4u);
-  const int32_t nb = (lead + n + 3) >> 2;  // blocks covering e[-lead, n)
-  for (int32_t b = 0; b < nb; b += kUnroll * KVR_WAVE) {
-    int4 v[kUnroll];
+
+// Number of leading words of the edge ar[eo, eo + n) that equal q[d, d + n)
+// (q in LDS).  A new edge is placed so that its 16-byte
+// blocks line up with the query buffer's (`place_edge`), and splits and
+// the collector keep that: the wave then compares a block per lane, kU blocks
+// per lane in flight, with no branch in the round (lanes past the end read the
+// last block again).  Blocks reach up to three words outside the edge, inside
+// the same aligned 16 bytes; those words are masked.  An edge that a collection
+// had to pack closer is compared word by word.
+template <int kU>
+__device__ __forceinline__ int32_t same_words(const int32_t* ar, uint32_t eo, const int32_t* q, int32_t d, int32_t n) {
+  const uint32_t ea = (uint32_t)(reinterpret_cast<uintptr_t>(ar + eo) >> 2);
+  if (((ea - (uint32_t)d) & 3u) == 0u && (reinterpret_cast<uintptr_t>(q) & 15u) == 0u) {
+    const int32_t lead = d & 3;
+    const int4* eb = reinterpret_cast<const int4*>(ar + eo - lead);
+    const int4* qb = reinterpret_cast<const int4*>(q + (d - lead));
+    const int32_t nb = (lead + n + 3) >> 2;
+    for (int32_t b = 0; b < nb; b += kU * KVR_WAVE) {
+      int4 v[kU];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int32_t blk = b + u * KVR_WAVE + lane_id();
-      v[u].x = v[u].y = v[u].z = v[u].w = 0;
-      if (blk < nb) v[u] = base[blk];
+      for (int u = 0; u < kU; ++u) {
+        const int32_t k = b + u * KVR_WAVE + lane_id();
+        if (u == 0 || b + u * KVR_WAVE < nb) v[u] = eb[k < nb ? k : nb - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int32_t k0 = b + u * KVR_WAVE + lane_id();
+        const int32_t k = k0 < nb ? k0 : nb - 1;
+        const int4 w = qb[k];
+        uint32_t ne = (v[u].x != w.x ? 1u : 0u) | (v[u].y != w.y ? 2u : 0u) | (v[u].z != w.z ? 4u : 0u) |
+                      (v[u].w != w.w ? 8u : 0u);
+        if (k == 0) ne &= 0xfu << lead;
+        const int32_t x = k * 4 - lead + (__ffsll((unsigned long long)ne) - 1);
+        const uint64_t m = __ballot(ne != 0u && x < n);
+        if (m) return __builtin_amdgcn_readlane(x, first_lane(m));
+        if (b + (u + 1) * KVR_WAVE >= nb) return n;
+      }
+    }
+    return n;
+  }
+  constexpr int kW = 4;
+  for (int32_t b = 0; b < n; b += kW * KVR_WAVE) {
+    int32_t v[kW];
+#pragma unroll
+    for (int u = 0; u < kW; ++u) {
+      const int32_t k = b + u * KVR_WAVE + lane_id();
+      v[u] = ar[eo + (uint32_t)(k < n ? k : n - 1)];
     }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int32_t blk = b + u * KVR_WAVE + lane_id();
-      const int32_t x0 = blk * 4 - lead;  // index into e of v[u].x
-      int32_t mm = n;
-      if (blk < nb) {
-        const int32_t t4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-        for (int c = 3; c >= 0; --c) {
-          const int32_t x = x0 + c;
-          if (x >= 0 && x < n && t4[c] != q[x]) mm = x;
-        }
-      }
-      const uint64_t m = __ballot(mm < n);
-      if (m) return __builtin_amdgcn_readlane(mm, first_lane(m));
+    for (int u = 0; u < kW; ++u) {
+      const int32_t k = b + u * KVR_WAVE + lane_id();
+      const uint64_t m = __ballot(k < n && v[u] != q[d + (k < n ? k : n - 1)]);
+      if (m) return b + u * KVR_WAVE + first_lane(m);
     }
   }
   return n;
@@ -2289,27 +2420,26 @@ template <int kU = KVR_MATCH_UNROLL>
 __device__ __forceinline__ int32_t match_from(const Ptrs& P, uint32_t sel, const int32_t* qs, int32_t L, int32_t x, int32_t off,
                               int32_t d, const PathRef& pr, int32_t& pc) {
   const int32_t* ar = arena_of(P, sel);
-  if (d >= L) return d;
   // the record of the current node is loaded once and carried down
-  NodeRec nx = P.nodes[x];
-  if (x != 0 && off < nx.len) {  // the rest of this edge first
-    const int32_t rest = nx.len - off;
-    const int32_t n = rest < L - d ? rest : L - d;
-    const int32_t k = first_mismatch<kU>(ar + nx.off + off, qs + d, n);
-    d += k;
-    if (k < rest) return d;
-  }
+  NodeRec nx = load_node(P.nodes, x);
+  if (x == 0) off = nx.len;
   while (d < L) {
-    const int32_t c = child_find(ar, nx, qs[d]);
+    if (off < nx.len) {  // the rest of this edge
+      const int32_t rest = nx.len - off;
+      const int32_t n = rest < L - d ? rest : L - d;
+      const int32_t k = same_words<kU>(ar, nx.off + (uint32_t)off, qs, d, n);
+      d += k;
+      off += k;
+      if (k < rest) break;
+      continue;
+    }
+    const int32_t c = child_find(ar, nx, uni(qs[d]));
     if (c < 0) break;
-    const NodeRec nc = P.nodes[c];
-    if (nc.len <= 0) break;  // never true for a consistent tree
-    path_add(pr, pc, c, d, d + nc.len);
-    const int32_t n = nc.len < L - d ? nc.len : L - d;
-    const int32_t k = 1 + first_mismatch<kU>(ar + nc.off + 1, qs + d + 1, n - 1);
-    d += k;
-    if (k < nc.len) break;
-    nx = nc;
+    nx = load_node(P.nodes, c);
+    if (nx.len <= 0) break;  // never true for a consistent tree
+    path_add(pr, pc, c, d, d + nx.len);
+    d += 1;  // the child entry holds the edge's first token
+    off = 1;
   }
   return d;
 }
@@ -2335,65 +2465,46 @@ __device__ __forceinline__ int32_t match_lcp(const Ptrs& P, uint32_t sel, const 
 template <int kU = KVR_MATCH_UNROLL>
 __device__ __forceinline__ int32_t match_incremental(const Ptrs& P, uint32_t sel, const int32_t* qn, int32_t Ln, int32_t h_old,
                                      int32_t ell, const PathRef& pr) {
-  int32_t pc = *pr.cnt;
-  if (pc > kPathMax || ell == 0) return match_lcp<kU>(P, sel, qn, Ln, pr);
-  if (h_old < ell) return h_old;
-  // the entry holding depth ell: the last one starting above it
-  int32_t e = pc - 1;
-  while (e > 0 && pr.start[e] >= ell) --e;
-  const int32_t x = pr.node[e], st = pr.start[e], en = pr.end[e];
-  if (pc == 0 || st >= ell || en < ell) return match_lcp<kU>(P, sel, qn, Ln, pr);  // inconsistent record
-  pc = e + 1;
-  int32_t h;
-  if (ell == Ln || (ell < en && h_old > ell)) {
-    h = ell;
-  } else {
-    h = match_from<kU>(P, sel, qn, Ln, x, ell - st, ell, pr, pc);
+  const int32_t have = uni(*pr.cnt);
+  int32_t pc = 0, x = 0, off = 0, d = 0;
+  bool walk = true;
+  if (have <= kPathMax && ell > 0) {
+    if (h_old < ell) return h_old;
+    // the entry holding depth ell: the last one starting above it
+    int32_t e = have - 1;
+    while (e > 0 && uni(pr.start[e]) >= ell) --e;
+    const int32_t st = have > 0 ? uni(pr.start[e]) : ell, en = have > 0 ? uni(pr.end[e]) : 0;
+    if (st < ell && en >= ell) {  // (always, for a consistent record)
+      pc = e + 1;
+      d = ell;
+      walk = !(ell == Ln || (ell < en && h_old > ell));
+      x = uni(pr.node[e]);
+      off = ell - st;
+    }
   }
-  if (lane_id() == 0) *pr.cnt = pc;
-  return h;
-}
-
-// match_incremental that reads the worker's active semispace only when it
-// walks the tree (the common outcomes need no global memory at all).
-template <int kU = KVR_MATCH_UNROLL>
-__device__ __forceinline__ int32_t match_incremental_lazy(const Ptrs& P, const int32_t* qn, int32_t Ln, int32_t h_old,
-                                                          int32_t ell, const PathRef& pr) {
-  int32_t pc = *pr.cnt;
-  if (pc > kPathMax || ell == 0) return match_lcp<kU>(P, P.hdr->arena_sel, qn, Ln, pr);
-  if (h_old < ell) return h_old;
-  int32_t e = pc - 1;
-  while (e > 0 && pr.start[e] >= ell) --e;
-  const int32_t x = pr.node[e], st = pr.start[e], en = pr.end[e];
-  if (pc == 0 || st >= ell || en < ell) return match_lcp<kU>(P, P.hdr->arena_sel, qn, Ln, pr);
-  pc = e + 1;
-  int32_t h;
-  if (ell == Ln || (ell < en && h_old > ell)) {
-    h = ell;
-  } else {
-    h = match_from<kU>(P, P.hdr->arena_sel, qn, Ln, x, ell - st, ell, pr, pc);
-  }
+  const int32_t h = walk ? match_from<kU>(P, sel, qn, Ln, x, off, d, pr, pc) : d;
   if (lane_id() == 0) *pr.cnt = pc;
   return h;
 }
 
 // ---------------------------------------------------------------- LBGR (one lane per worker)
 
-__device__ void online_update(const Consts& C, WorkerHdr* w, const double phi[4], double e) {
+__device__ __forceinline__ void online_update(const Consts& C, double* theta, double* Pm, const double phi[4],
+                                              double e) {
   if (C.update == KVR_UPD_NLMS) {
     double ss = phi[0] * phi[0];
     ss = ss + phi[1] * phi[1];
     ss = ss + phi[2] * phi[2];
     ss = ss + phi[3] * phi[3];
     double g = (C.lr * e) / (C.nlms_eps + ss);
-    for (int a = 0; a < 4; ++a) w->theta[a] = w->theta[a] + g * phi[a];
+    for (int a = 0; a < 4; ++a) theta[a] = theta[a] + g * phi[a];
   } else if (C.update == KVR_UPD_RLS) {
     double pi[4];
     for (int a = 0; a < 4; ++a) {
-      double acc = w->Pm[a * 4 + 0] * phi[0];
-      acc = acc + w->Pm[a * 4 + 1] * phi[1];
-      acc = acc + w->Pm[a * 4 + 2] * phi[2];
-      acc = acc + w->Pm[a * 4 + 3] * phi[3];
+      double acc = Pm[a * 4 + 0] * phi[0];
+      acc = acc + Pm[a * 4 + 1] * phi[1];
+      acc = acc + Pm[a * 4 + 2] * phi[2];
+      acc = acc + Pm[a * 4 + 3] * phi[3];
       pi[a] = acc;
     }
     double den = phi[0] * pi[0];
@@ -2403,9 +2514,9 @@ __device__ void online_update(const Consts& C, WorkerHdr* w, const double phi[4]
     den = C.lr + den;
     double k[4];
     for (int a = 0; a < 4; ++a) k[a] = pi[a] / den;
-    for (int a = 0; a < 4; ++a) w->theta[a] = w->theta[a] + k[a] * e;
+    for (int a = 0; a < 4; ++a) theta[a] = theta[a] + k[a] * e;
     for (int a = 0; a < 4; ++a)
-      for (int b = 0; b < 4; ++b) w->Pm[a * 4 + b] = (w->Pm[a * 4 + b] - k[a] * pi[b]) / C.lr;
+      for (int b = 0; b < 4; ++b) Pm[a * 4 + b] = (Pm[a * 4 + b] - k[a] * pi[b]) / C.lr;
   }
 }
 
@@ -2439,7 +2550,7 @@ __device__ __forceinline__ void complete_and_decay(const Consts& C, const Ptrs& 
     res = res + w->theta[3] * phi[3];
     double ehat_now = pr.base + res;
     double e_obs = (double)(pr.t_done - pr.t_route) * 1e-6;
-    online_update(C, w, phi, e_obs - ehat_now);
+    online_update(C, w->theta, w->Pm, phi, e_obs - ehat_now);
     done += 1;
   }
   Pl = Pl * pow_int(C.rho, (uint64_t)(t / dt - tl / dt));

@@ -44,7 +44,7 @@
 
 #include <mutex>
 
-#include "kvr_core.h"
+#include "kvr_trail.h"
 
 namespace kvr {
 
@@ -72,43 +72,47 @@ __device__ __forceinline__ void count_matched(const Ptrs& P, int32_t h, int32_t*
   }
 }
 
+// Words in front of and behind each query buffer: staging writes whole 16-byte
+// blocks of the stream, up to three words outside the query.
+constexpr uint32_t kQueryPad = 4;
+__host__ __device__ constexpr uint32_t query_words(uint32_t maxL) { return ((maxL + 3u) & ~3u) + 2u * kQueryPad; }
+
+// The buffer of query k (nbuf = 2 or 3).
+__device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) { return nbuf == 2u ? k & 1u : k % 3u; }
+
 // Stage q_next[0, Ln) (threads t0, t0 + stride, ...) and fold each thread's
 // first position where it differs from q_cur into *ell (LDS minimum), so
-// that after the next barrier *ell = LCP(q_cur, q_next).  The stream is read
-// in aligned 16-byte blocks of four tokens, eight blocks per thread in flight;
-// the first and last block may reach up to three tokens outside the query,
-// inside the same aligned 16 bytes, and those are not staged.
-template <int kUnroll = 8>  // blocks in flight per thread
-__device__ __forceinline__ void stage_next(const int32_t* tokens, uint64_t n0, int32_t Ln, int32_t* qn,
-                                           const int32_t* qc, int32_t Lc, uint32_t t0, uint32_t stride,
-                                           int32_t* ell) {
-  const uintptr_t sa = reinterpret_cast<uintptr_t>(tokens + n0);
-  const int32_t lead = (int32_t)((sa & 15u) >> 2);
-  const int4* base = reinterpret_cast<const int4*>(sa - (uintptr_t)lead * 4u);
+// that once all have staged, *ell = LCP(q_cur, q_next).  The stream is read in
+// aligned 16-byte blocks, kU per thread in flight; threads past the end read
+// the last block again.
+template <int kU>
+__device__ __forceinline__ void stage_query(const int32_t* tokens, uint64_t n0, int32_t Ln, int32_t* qn,
+                                            const int32_t* qc, int32_t Lc, uint32_t wave0, uint32_t stride,
+                                            int32_t* ell) {
+  const int32_t* p = tokens + n0;
+  const int32_t lead = (int32_t)((reinterpret_cast<uintptr_t>(p) >> 2) & 3u);
+  const int4* base = reinterpret_cast<const int4*>(p - lead);
   const uint32_t nb = (uint32_t)((lead + Ln + 3) >> 2);
   int32_t m = Lc < Ln ? Lc : Ln;
-  for (uint32_t b = t0; b < nb; b += kUnroll * stride) {
-    int4 v[kUnroll];
+  for (uint32_t b = wave0; b < nb; b += kU * stride) {
+    int4 v[kU];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t blk = b + (uint32_t)u * stride;
-      v[u].x = v[u].y = v[u].z = v[u].w = 0;
-      if (blk < nb) v[u] = base[blk];
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t k = b + (uint32_t)u * stride + (uint32_t)lane_id();
+      if (u == 0 || b + (uint32_t)u * stride < nb) v[u] = base[k < nb ? k : nb - 1u];
     }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t blk = b + (uint32_t)u * stride;
-      if (blk < nb) {
-        const int32_t t4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-        const int32_t x0 = (int32_t)blk * 4 - lead;
+    for (int u = 0; u < kU; ++u) {
+      if (u != 0 && b + (uint32_t)u * stride >= nb) break;
+      const uint32_t k = b + (uint32_t)u * stride + (uint32_t)lane_id();
+      const int32_t x0 = (int32_t)(k < nb ? k : nb - 1u) * 4 - lead;
+      const int32_t t4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      const bool end = x0 < 0 || x0 + 4 > Ln;  // the first or last block
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int32_t x = x0 + c;
-          if (x >= 0 && x < Ln) {
-            qn[x] = t4[c];
-            if (x < m && qc[x] != t4[c]) m = x;
-          }
-        }
+      for (int c = 3; c >= 0; --c) {
+        const int32_t x = x0 + c;
+        qn[x] = t4[c];
+        if (qc[x] != t4[c] && x < m && (!end || x >= 0)) m = x;
       }
     }
   }
@@ -263,6 +267,51 @@ __device__ __forceinline__ uint32_t router_admit(const StepArgs& a, uint32_t r, 
   return err;
 }
 
+// Is the batch to be routed at all?  Called by a whole workgroup before it
+// changes anything, with bad, a word of its LDS, at 0; after the next barrier
+// `batch_ok` says.  The run must not have failed and, with a.check, the batch
+// must be valid: lengths (with cached responses, a prompt of at least one token
+// before the response) and arrival order, which every wave looks at for
+// itself, and only then the tokens.  Every workgroup reads the same batch and
+// its replica's own last arrival, so all come to the same verdict.
+constexpr uint32_t kRunFailed = 1u << 31;
+__device__ __forceinline__ void check_batch(const StepArgs& a, GlobalHdr* g, int64_t tprev, uint32_t* bad) {
+  if (threadIdx.x == 0 && __atomic_load_n(&g->status, __ATOMIC_RELAXED)) atomicOr(bad, kRunFailed);
+  if (!a.check) return;
+  uint32_t bits = 0;
+  for (uint32_t j = (uint32_t)lane_id(); j < a.n; j += KVR_WAVE) {
+    const uint64_t o0 = a.offsets[j], o1 = a.offsets[j + 1];
+    if (o1 <= o0 || o1 - o0 > a.L.maxL) bits |= KVR_DEV_BAD_LENGTH;
+    if (a.C.cache_responses && o1 - o0 <= (uint64_t)query_out_len(a.out_len, j)) bits |= KVR_DEV_BAD_LENGTH;
+    if (a.arrival[j] < (j == 0 ? tprev : a.arrival[j - 1])) bits |= KVR_DEV_BAD_ARRIVAL;
+  }
+  if (__ballot(bits != 0u)) {
+    if (bits) atomicOr(bad, bits);
+    return;
+  }
+  const int32_t* p = a.tokens + a.offsets[0];
+  const uint32_t m = (uint32_t)(a.offsets[a.n] - a.offsets[0]);
+  constexpr int kU = 4;  // loads in flight per thread
+  int32_t low = 0;
+  for (uint32_t x = threadIdx.x; x < m; x += kU * blockDim.x) {
+    int32_t v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t k = x + (uint32_t)u * blockDim.x;
+      v[u] = p[k < m ? k : m - 1u];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) low |= v[u];
+  }
+  if (low < 0) atomicOr(bad, (uint32_t)KVR_DEV_BAD_TOKEN);
+}
+
+__device__ __forceinline__ bool batch_ok(GlobalHdr* g, uint32_t bad) {
+  if (!bad) return true;
+  if (threadIdx.x == 0 && !(bad & kRunFailed)) atomicOr(&g->status, bad);
+  return false;
+}
+
 // One workgroup per replica walks the batch in order.  A worker's tree
 // changes only when a query is routed to it, so while wave 0 inserts query k
 // into the routed worker the other waves compute the draw words of that
@@ -281,10 +330,10 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
   // dynamic LDS: two query buffers (max_query_tokens entries each), the high
   // halves of the draw words, the match paths (the caches', then the router
   // trees'), then the staged candidate list
-  extern __shared__ int32_t smem[];
+  extern __shared__ __align__(16) int32_t smem[];
   const uint32_t W = a.L.W;
   constexpr bool rtree = RT;
-  const uint32_t qstride = (a.L.maxL + 3u) & ~3u;
+  const uint32_t qstride = query_words(a.L.maxL);
   uint32_t* rw = reinterpret_cast<uint32_t*>(smem + 2 * qstride);
   PathArea paths, rpaths;
   paths.base = reinterpret_cast<int32_t*>(rw + a.rcap);
@@ -325,11 +374,13 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
   ReplicaHdr* rh = reinterpret_cast<ReplicaHdr*>(a.ws + a.L.off_rhdr) + r;
 
   if (threadIdx.x == 0) {
-    abort_sh = __atomic_load_n(&g->status, __ATOMIC_RELAXED);
+    abort_sh = 0;
     ell_sh[0] = 0x7fffffff;
   }
   __syncthreads();
-  if (abort_sh) return;
+  check_batch(a, g, rh->tprev, &abort_sh);
+  __syncthreads();
+  if (!batch_ok(g, abort_sh)) return;
   // the replica's route digest and query count, kept by the routing wave
   uint64_t chain = 0, routed = 0;
   if (wave == 0) {
@@ -345,17 +396,17 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
     const uint64_t o0 = a.offsets[0];
     const int32_t L0 = (int32_t)(a.offsets[1] - o0);
     const int32_t L0q = resp ? L0 - query_out_len(a.out_len, 0) : L0;
-    for (int32_t x = (int32_t)threadIdx.x; x < L0; x += (int32_t)blockDim.x) smem[x] = a.tokens[o0 + x];
+    for (int32_t x = (int32_t)threadIdx.x; x < L0; x += (int32_t)blockDim.x) smem[kQueryPad + x] = a.tokens[o0 + x];
     if (wave == 0 && (uint32_t)lane < W)
       complete_and_decay(a.C, worker_ptrs(a.ws, a.L, r, (uint32_t)lane), a.arrival[0], rh->tprev);
     __syncthreads();
     for (uint32_t i = wave; i < W; i += nwaves) {
       Ptrs P = worker_ptrs(a.ws, a.L, r, i);
-      const int32_t h = match_lcp(P, P.hdr->arena_sel, smem, L0q, paths.of(i));
+      const int32_t h = match_lcp(P, P.hdr->arena_sel, smem + kQueryPad, L0q, paths.of(i));
       if (rtree) {
         store_h(h, &h_sh[0][i]);
         Ptrs Pr = router_ptrs(a.ws, a.L, r, i);
-        count_matched(P, match_lcp(Pr, Pr.hdr->arena_sel, smem, L0q, rpaths.of(i)), &g_sh[0][i]);
+        count_matched(P, match_lcp(Pr, Pr.hdr->arena_sel, smem + kQueryPad, L0q, rpaths.of(i)), &g_sh[0][i]);
       } else {
         count_matched(P, h, &h_sh[0][i]);
       }
@@ -368,8 +419,8 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
     const int32_t olen = query_out_len(a.out_len, k);
     const int32_t Lq = resp ? Lp - olen : Lp;  // the prompt
     const uint32_t cur = k & 1u;
-    int32_t* qs = smem + cur * qstride;
-    int32_t* qn = smem + (cur ^ 1u) * qstride;
+    int32_t* qs = smem + cur * qstride + kQueryPad;
+    int32_t* qn = smem + (cur ^ 1u) * qstride + kQueryPad;
     const bool has_next = k + 1 < a.n;
     int32_t Ln = 0, Lnq = 0;  // path and prompt of the next query
     uint64_t n0 = 0;
@@ -428,9 +479,9 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
       }
       if (a.all_hits && (uint32_t)lane < W)
         a.all_hits[((uint64_t)r * a.n + k) * W + (uint32_t)lane] = est[cur][lane];
-      if (nh == 0 && has_next) stage_next(a.tokens, n0, Ln, qn, qs, Lp, (uint32_t)lane, KVR_WAVE, &ell_sh[cur]);
+      if (nh == 0 && has_next) stage_query<8>(a.tokens, n0, Ln, qn, qs, Lp, 0u, KVR_WAVE, &ell_sh[cur]);
     } else if (has_next) {
-      stage_next(a.tokens, n0, Ln, qn, qs, Lp, threadIdx.x - KVR_WAVE, blockDim.x - KVR_WAVE, &ell_sh[cur]);
+      stage_query<8>(a.tokens, n0, Ln, qn, qs, Lp, uni(wave - 1u) * KVR_WAVE, blockDim.x - KVR_WAVE, &ell_sh[cur]);
     }
     if (wave == 0) clock_mark<PT>(&clk, KVR_PHASE_ROUTE);
     __syncthreads();
@@ -566,81 +617,83 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
 // ---------------------------------------------------------------- pipelined step kernel
 //
 // RLT with prompts only, LBGR or a baseline router, no approximate router
-// and single-query processing (the benchmark's path).  The evictions of an
-// insertion only touch the routed worker's cache, and nothing the routing of
-// the next query reads depends on them but that worker's h of the next
-// query.  So a separate wave, the evicting wave, runs the back half of each
-// insertion (evictions, marks of the loaded tokens, header) while the
-// routing wave routes the next query and runs the front half of its
-// insertion (marking walk, split, rank, load of the new leaf).  The routing
-// wave takes the routed worker's h of the next query on the tree after the
-// load and before the evictions: the evictions never remove a token of the
-// inserted path, so when that match ends on the inserted path (h equal to
-// the two queries' longest common prefix) it is exact; otherwise it is taken
-// again once the evictions are done.  One insertion is evicted at a time:
-// the routing wave waits for the evicting wave before it hands it the next
-// insertion or inserts into the worker being evicted.
+// and single-query processing (the benchmark's path).  A step is bound by
+// latency: the route of a query needs its h on every worker, and the routed
+// worker's h needs the insertion of the query before it.  So everything that
+// need not lie on that chain is taken off it:
+//   * the next queries are matched on every worker before this one is routed.  A
+//     worker's tree changes only when a query is routed to it, so only the
+//     routed worker's match is looked at again after the load, and it follows
+//     from the one before;
+//   * the routing wave only scores, commits and loads the new leaf; the marks,
+//     the leaf list and the evictions follow on an evicting wave, several
+//     insertions (of different workers) at a time;
+//   * LBGR state, tree state and query data live in LDS for the launch.
 //
-// Waves: 0 routes and runs front halves, 1 evicts, 2.. are helpers (stage
-// the next query, compute draw words, rank the new leaf, apply completions
-// and decay, match the next query on the other workers).  They synchronise
-// through the counters below (LDS, workgroup scope, release/acquire); every
-// wait is bounded and checks the stop flag, so an error ends every loop.
+// Waves: 0 routes and loads leaves, 1..NE evict, the rest are helpers: they
+// stage queries, match, compute draw words, rank new leaves and apply
+// completions and decay, whichever is due first.
+//
+// A worker's matches and insertions are ordered by its state word: the number
+// of queries matched on it, and below it five flags.  A wave takes the match of
+// query m by exchanging (m, no reader) for (m, reader), so each match is taken
+// once and in order.  The routing wave sets the owner flag and waits for a
+// reader before it loads a leaf; once that is done (loaded flag), matches go
+// on beside the evictions: the next query's at once, later ones after the
+// marks (marked flag), which read the trail that the match after the next
+// writes.  One that the evictions could still change is put off (deferred
+// flag) until they end and the owner's flags are cleared.
+// Waves synchronise through these words and the counters below (LDS,
+// workgroup scope, release/acquire); every wait is bounded and sees the stop
+// flag, so an error ends every loop.
+
+constexpr uint32_t kReader = 1u, kOwner = 2u, kLoaded = 4u, kMarked = 8u, kDeferred = 16u;
+constexpr uint32_t kCountShift = 5;
+constexpr uint32_t kCountMask = 0x7ffffffu;  // counts are compared modulo 2^27
 
 struct PipeFlags {
-  uint32_t top;         // the routing wave has begun query top - 1: q_top may be staged
-  uint32_t routed;      // queries routed (route, evictions and slots of query routed - 1 published)
-  uint32_t staged;      // staging waves done, over all queries
-  uint32_t matched;     // helper matches done, over all queries (W - 1 per query)
-  uint32_t decayed;     // arrivals whose completions and decay are applied
-  uint32_t handed;      // insertions handed to the evicting wave
-  uint32_t evicted;     // insertions it has finished
-  uint32_t ework;       // worker of its current insertion, kNoWorker when idle
-  uint32_t ework_size;  // that worker's |S| once the insertion is done
-  uint32_t end;         // no more insertions will be handed
-  uint32_t stop;        // an error stopped the replica
-  uint32_t next[2];     // helper match items taken, by query parity
-  uint32_t last_worker; // worker of the last insertion handed to the evicting wave
-  uint32_t pad;
-  // the next query's matches, claimed per worker (bit i) by the wave that
-  // takes them, by query parity: a helper, or the evicting wave for its
-  // worker once its evictions end
-  unsigned long long claim[2];
+  uint32_t routed;   // queries routed
+  uint32_t fronts;   // leaves loaded: the buffer of query fronts - 1 is free
+  uint32_t staged;   // helpers done staging, over all queries
+  uint32_t decayed;  // arrivals whose completions and decay are applied
+  uint32_t handed;   // insertions handed to the evicting waves
+  uint32_t ticket;   // insertions they have taken
+  uint32_t end;      // every query is routed and handed
+  uint32_t stop;     // an error stopped the replica
+  uint32_t bad;      // the verdict on the batch
+  uint32_t pad[7];
 };
+constexpr int kFlagWords = 16;
+static_assert(sizeof(PipeFlags) == 4 * kFlagWords, "one flag word per lane of a row");
 
-constexpr uint32_t kNoWorker = 0xffffffffu;
 // 16-byte compare loads in flight per lane in the pipelined kernel's matches
-// (its next-query matches are on the routing wave's path)
 #ifndef KVR_PIPE_MATCH_UNROLL
 #define KVR_PIPE_MATCH_UNROLL 8
 #endif
 constexpr int kPipeMatchUnroll = KVR_PIPE_MATCH_UNROLL;
-// ... in the matches taken from the shared item counter (most of them, on
-// the helper waves, whose registers are not the kernel's peak)
-#ifndef KVR_PIPE_ITEM_UNROLL
-#define KVR_PIPE_ITEM_UNROLL 8
-#endif
-constexpr int kPipeItemUnroll = KVR_PIPE_ITEM_UNROLL;
 constexpr uint32_t kSpinLimit = 1u << 24;
+// insertions between routing and the end of their evictions, at most
+constexpr uint32_t kJobs = 4;
+// Waves per workgroup.  Three per SIMD leave 168 registers a lane, which the
+// roles' separate loops need not exceed by much (32 bytes of scratch); against
+// 8 waves, multi-turn 51.0 ms a simulation instead of 55.3, the paper's groups
+// in round-robin order 67.9 instead of 77.8, long prompts 144 instead of 188,
+// the rest within 3%.  16 waves (128 registers) lose 1 to 11%.
 #ifndef KVR_PIPE_WAVES
-#define KVR_PIPE_WAVES 8
+#define KVR_PIPE_WAVES 12
 #endif
 constexpr uint32_t kPipeWaves = KVR_PIPE_WAVES;
-// Waves per workgroup for replicas of many workers: four more helpers for
-// the next query's matches, at a register cap of 168 VGPRs instead of 256
-// (the routing wave's loop state then partly lives in scratch).  Measured
-// faster at 32 workers and slower at 16, so used from 17 on.
-#ifndef KVR_PIPE_WAVES_WIDE
-#define KVR_PIPE_WAVES_WIDE 12
+// Two evicting waves: an insertion's second half takes 6 to 9 us of one wave
+// against 8 to 10 us of a whole step, so one wave would be the step's bound, and
+// a third (one helper fewer) gained nothing on the two-level workload and lost
+// 4% on the long-prompt one.
+#ifndef KVR_PIPE_EVICTORS
+#define KVR_PIPE_EVICTORS 2
 #endif
-#ifndef KVR_PIPE_WIDE_WORKERS
-#define KVR_PIPE_WIDE_WORKERS 17
-#endif
-constexpr uint32_t kPipeWavesWide = KVR_PIPE_WAVES_WIDE;
-constexpr uint32_t kPipeWideWorkers = KVR_PIPE_WIDE_WORKERS;
+constexpr uint32_t kPipeEvictors = KVR_PIPE_EVICTORS;
 
 __device__ __forceinline__ uint32_t ld_acq(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return uni(__hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
 }
 
 // Publish v (lane 0, after every lane's earlier writes).
@@ -672,588 +725,749 @@ __device__ __forceinline__ void pipe_stop(GlobalHdr* g, PipeFlags* f, uint32_t r
   }
 }
 
-// Wait until *p >= target (or, with ne, until *p != target).  False when
-// the replica was stopped; a wait that runs out stops it (check id 90 +
-// site, an internal error).
-template <bool kNe = false>
+#ifndef KVR_POLL_SLEEP
+#define KVR_POLL_SLEEP 1
+#endif
+// One poll of a wait: false once the replica was stopped; a wait that has
+// run out stops it (check id 90 + site, an internal error).
+__device__ __forceinline__ bool pipe_poll(uint32_t& spins, PipeFlags* f, GlobalHdr* g, uint32_t r, uint64_t jg,
+                                          int site) {
+  if (ld_acq(&f->stop)) return false;
+  if (++spins > kSpinLimit) {
+    const int64_t dbg[4] = {90 + site, (int64_t)f->routed, (int64_t)f->handed, (int64_t)f->staged};
+    pipe_stop(g, f, r, jg, KVR_DEV_INTERNAL, dbg);
+    return false;
+  }
+  __builtin_amdgcn_s_sleep(KVR_POLL_SLEEP);
+  return true;
+}
+
+// Wait until *p >= target.  False when the replica was stopped.
 __device__ __forceinline__ bool pipe_wait(const uint32_t* p, uint32_t target, PipeFlags* f, GlobalHdr* g, uint32_t r,
                                           uint64_t jg, int site) {
   uint32_t spins = 0;
-  for (;;) {
-    const uint32_t v = ld_acq(p);
-    if (kNe ? v != target : v >= target) return true;
-    if (__hip_atomic_load(&f->stop, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) return false;
-    if (++spins > kSpinLimit) {
-      const int64_t dbg[4] = {90 + site, (int64_t)v, (int64_t)target, 0};
-      pipe_stop(g, f, r, jg, KVR_DEV_INTERNAL, dbg);
-      return false;
+  while (ld_acq(p) < target)
+    if (!pipe_poll(spins, f, g, r, jg, site)) return false;
+  return true;
+}
+
+// The leaf list and the worker state of an evicting wave: the new leaf's rank
+// comes from a helper, and is waited for only when something needs the list;
+// the state goes back to LDS.
+struct PipeHook {
+  bool todo;
+  PipeJob job;
+  const uint32_t* ready;  // rank_ready of the job's slot
+  const int32_t* rank;
+  uint32_t* state;        // the worker's state words
+  const uint32_t* stop;
+  __device__ __forceinline__ void before_list(const Ptrs& P, St& s) {
+    if (!todo) return;
+    todo = false;
+    const uint32_t want = ((job.k + 1u) << 2) | 3u;
+    uint32_t spins = 0;
+    while (ld_acq(ready) != want) {
+      if (ld_acq(stop) || ++spins > kSpinLimit) {
+        KVR_FAIL_CHECK(s, 5, job.k, job.worker, spins);
+        return;
+      }
+      __builtin_amdgcn_s_sleep(1);
     }
-    __builtin_amdgcn_s_sleep(1);
+    const int32_t pos = uni(*rank);
+    if (pos < 0 || (uint32_t)pos > s.nleaves) {
+      KVR_FAIL_CHECK(s, 4, pos, s.nleaves, job.a);
+      return;
+    }
+    if (job.replace) {
+      if (lane_id() == 0) P.leaf[pos] = job.l;
+    } else {
+      arr_insert(P.leaf, s.nleaves, (uint32_t)pos, job.l, false);
+      s.nleaves += 1;
+    }
+    wave_mem_sync();
   }
+  __device__ __forceinline__ void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
+};
+
+// May the match of query m be taken on a worker in this state, owned (if so)
+// by the insertion of query k?  (nbuf: how many queries have a trail.)
+__device__ __forceinline__ bool can_match(uint32_t sv, uint32_t m, uint32_t k, uint32_t nbuf) {
+  const uint32_t c = m << kCountShift;
+  return sv == c || sv == (c | kOwner | kLoaded | kMarked) || (sv == (c | kOwner | kLoaded) && m - k < nbuf);
 }
 
-// Root filters of the pipelined kernel: per worker a 256-bit Bloom filter
-// (in LDS) of the first tokens of its root's children, two bits per token,
-// built when the kernel starts and extended when an insertion adds a child
-// to the root.  A clear bit proves that no cached path starts with the
-// token, so a match that starts at the root is 0 without a memory access; a
-// set bit (also one left by a child evicted since) only means the tree is
-// walked.  (512- and 1,024-bit filters measured within 1% of this.)
-#ifndef KVR_ROOT_FILTER_LOG2_BITS
-#define KVR_ROOT_FILTER_LOG2_BITS 8
-#endif
-constexpr uint32_t kRootFilterBits = 1u << KVR_ROOT_FILTER_LOG2_BITS;
-constexpr uint32_t kRootFilterWords = kRootFilterBits / 32u;
-
-__device__ __forceinline__ uint32_t rf_bit1(int32_t t) {
-  return ((uint32_t)t * 0x9E3779B1u) >> (32 - KVR_ROOT_FILTER_LOG2_BITS);
-}
-__device__ __forceinline__ uint32_t rf_bit2(int32_t t) {
-  return ((uint32_t)t * 0x85EBCA6Bu + 0x632BE5ABu) >> (32 - KVR_ROOT_FILTER_LOG2_BITS);
+// Take the match that state sv allows; false when another wave was first.
+__device__ __forceinline__ bool claim_match(uint32_t* st, uint32_t sv) {
+  uint32_t old = 0;
+  if (lane_id() == 0) old = atomicCAS(st, sv, sv | kReader);
+  return uni(old) == sv;
 }
 
-__device__ __forceinline__ void rf_add(uint32_t* rf, int32_t t) {
-  atomicOr(&rf[rf_bit1(t) >> 5], 1u << (rf_bit1(t) & 31u));
-  atomicOr(&rf[rf_bit2(t) >> 5], 1u << (rf_bit2(t) & 31u));
-}
-
-__device__ __forceinline__ bool rf_may(const uint32_t* rf, int32_t t) {
-  return ((rf[rf_bit1(t) >> 5] >> (rf_bit1(t) & 31u)) & 1u) && ((rf[rf_bit2(t) >> 5] >> (rf_bit2(t) & 31u)) & 1u);
-}
-
-// h of qn[0, Ln) on a worker from its recorded path (match_incremental);
-// sel = the active semispace, or -1 to read it from the header when the tree
-// is walked.  A match that would start at the root is settled by the root
-// filter when it rules out qn[0].
-template <int kU = kPipeMatchUnroll>
-__device__ __forceinline__ int32_t match_pipe(const Ptrs& P, int32_t sel, const uint32_t* rf, const int32_t* qn,
-                                              int32_t Ln, int32_t h_old, int32_t ell, const PathRef& pr) {
-  if ((ell == 0 || *pr.cnt > kPathMax) && !rf_may(rf, qn[0])) {
-    if (lane_id() == 0) *pr.cnt = 0;
-    return 0;
-  }
-  if (sel < 0) return match_incremental_lazy<kU>(P, qn, Ln, h_old, ell, pr);
-  return match_incremental<kU>(P, (uint32_t)sel, qn, Ln, h_old, ell, pr);
-}
-
-// The next query's h on the workers other than the routed one (best) of
-// query parity cur, taken one item at a time from the LDS counter; the
-// worker being evicted is left to the evicting wave, and every other is
-// claimed first (the evicting wave may have taken it).  Returns the number
-// of matches done (the caller publishes them).
-template <int kU>
-__device__ __forceinline__ uint32_t take_matches_pipe(const StepArgs& a, uint32_t r, uint32_t W, uint32_t cur,
-                                                      uint32_t best, uint32_t prev, const int32_t* qn, int32_t Ln,
-                                                      int32_t ell, const int32_t* h_cur, int32_t* h_next, PipeFlags* f,
-                                                      unsigned long long* mtok, const uint32_t* rootf,
-                                                      const PathArea& paths) {
-  uint32_t mine = 0;
-  for (uint32_t it = 0; it < W; ++it) {
-    uint32_t got = 0;
-    if (lane_id() == 0) got = atomicAdd(&f->next[cur], 1u);
-    const uint32_t item = (uint32_t)__builtin_amdgcn_readlane((int)got, 0);
-    if (item >= W) break;
-    const uint32_t w = (prev + 1u + item) % W;
-    if (w == best) continue;
-    if (__hip_atomic_load(&f->ework, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_WORKGROUP) == w) continue;
-    unsigned long long old = 0ull;
-    if (lane_id() == 0) old = atomicOr(&f->claim[cur], 1ull << w);
-    const uint32_t taken = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((old >> w) & 1ull), 0);
-    if (taken) continue;
-    Ptrs Pw = worker_ptrs(a.ws, a.L, r, w);
-    count_mtok(mtok, w,
-               match_pipe<kU>(Pw, -1, rootf + w * kRootFilterWords, qn, Ln, h_cur[w], ell, paths.of(w)),
-               &h_next[w]);
-    ++mine;
-  }
-  return mine;
-}
-
-// NW = waves per workgroup (the kernel itself takes it from blockDim).
-template <bool PT, uint32_t NW>
+// NW waves, NE of them evicting.
+template <bool PT, uint32_t NW, uint32_t NE>
 __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
-  // dynamic LDS: two query buffers, the draw words of two insertions, the
-  // match paths, the staged candidate list
-  extern __shared__ int32_t smem[];
+  constexpr uint32_t nh = NW - 1u - NE;  // helper waves
+  // half of the helpers compute draw words, from the second on (the first
+  // applies completions and decay)
+  constexpr uint32_t ndraw = nh / 2u;
+  static_assert(nh >= 2u && ndraw >= 1u && ndraw < nh && ndraw <= 16u, "too few or too many waves");
+  constexpr uint32_t nd = ndraw * KVR_WAVE;  // drawing threads
+  extern __shared__ __align__(16) int32_t smem[];
   const uint32_t W = a.L.W;
-  const uint32_t qstride = (a.L.maxL + 3u) & ~3u;
-  uint32_t* rwb = reinterpret_cast<uint32_t*>(smem + 2 * qstride);  // [2][rcap]
-  PathArea paths;
-  paths.base = reinterpret_cast<int32_t*>(rwb + 2 * a.rcap);
-  paths.W = W;
-  // root filters (kRootFilterWords words per worker), then the candidates
-  uint32_t* rootf = reinterpret_cast<uint32_t*>(paths.base + (size_t)W * (3 * kPathMax + 1));
-  UStage ustage;
-  {
-    int32_t* ub = reinterpret_cast<int32_t*>(rootf + (size_t)W * kRootFilterWords);
-    ustage.node = ub;
-    ustage.len = ub + a.ucap;
-    ustage.top = ub + 2 * a.ucap;
-    ustage.par = ub + 3 * a.ucap;
-    ustage.cap = a.ucap;
-  }
-  __shared__ int32_t h_sh[2][kMaxWorkers];  // h of q_k in slot k & 1
-  __shared__ double eh_sh[kMaxWorkers];
-  __shared__ int32_t ell_sh[2];             // LCP(q_k, q_k+1) in slot k & 1
-  __shared__ int32_t best_sh[2];
-  __shared__ uint32_t rn_sh[2];             // draw words of insertion k precomputed in slot k & 1
-  __shared__ uint32_t prog_sh[2][16];       // rounds of them each drawing wave has written
-  __shared__ int32_t rank_sh;
-  __shared__ uint32_t rank_ready_sh;
+  // dynamic LDS: nbuf query buffers, the LBGR state, the workers' tree states,
+  // the trails of nbuf queries, the root filters, the ring of draw words, the
+  // evicting waves' staged candidates
+  const uint32_t qwords = query_words(a.L.maxL);
+  LbgrLds lb;
+  lb.W = W;
+  lb.P = reinterpret_cast<double*>(smem + a.nbuf * qwords);
+  lb.theta = lb.P + W;
+  lb.Wb = reinterpret_cast<int64_t*>(lb.theta + 4 * W);
+  lb.done_at = lb.Wb + W;
+  lb.head = reinterpret_cast<uint32_t*>(lb.done_at + W);
+  lb.count = lb.head + W;
+  lb.size = lb.count + W;
+  uint32_t* st_sh = lb.size + W;                   // state words
+  uint32_t* tree_sh = st_sh + W;                   // kStWords per worker
+  int32_t* trail_sh = reinterpret_cast<int32_t*>(tree_sh + kStWords * W);  // [nbuf][W][kTrailWords]
+  uint32_t* rootf = reinterpret_cast<uint32_t*>(trail_sh + a.nbuf * kTrailWords * W);
+  uint32_t* ring = rootf + kRootFilterWords * W;   // rcap draw words
+  int32_t* stage_base = reinterpret_cast<int32_t*>(ring + a.rcap);
+
   __shared__ PipeFlags f;
-  __shared__ EvictJob job_sh[2];            // by insertion count parity
-  // per handed insertion (same parity): the routed worker's h of the next
-  // query not taken yet (0), taken and exact (1), taken but to be taken
-  // again after the evictions (2)
-  __shared__ uint32_t early_sh[2];
+  __shared__ int32_t h_sh[3][kMaxWorkers];  // h of q_k in slot query_slot(k)
+  __shared__ double eh_sh[kMaxWorkers];
+  __shared__ int32_t ell_sh[4];             // LCP(q_k, q_k+1) in slot k & 3
+  __shared__ int32_t len_sh[4], olen_sh[4]; // length and output length of q_k
+  __shared__ int64_t arr_sh[4];             // its arrival
+  __shared__ PipeJob job_sh[kJobs];         // insertion k in slot k % kJobs
+  __shared__ uint32_t jdone_sh[kJobs];      // k + 1 once it is finished
+  __shared__ uint32_t owner_sh[kMaxWorkers]; // the insertion that owns a worker
+  __shared__ uint32_t best_sh[kJobs], r0_sh[kJobs];
+  __shared__ int32_t hit_sh[kJobs];         // h of the routed worker
+  __shared__ uint64_t rn_sh[kJobs];         // ((k + 1) << 32) | its precomputed draw words
+  __shared__ uint32_t prog_sh[kJobs][16];   // rounds of them each drawing wave has written
+  __shared__ int32_t rank_sh[kJobs];        // the new leaf's rank
+  __shared__ uint32_t rank_ready_sh[kJobs]; // 0, or ((k + 1) << 2) | 1 wanted, 2 being computed, 3 there
   __shared__ unsigned long long eticks_sh[KVR_PHASES];  // evicting and helper waves' ticks
   // matched tokens per worker over the batch (added to the headers at the end)
   __shared__ unsigned long long mtok_sh[kMaxWorkers];
 
   const uint32_t r = blockIdx.x;
   const int lane = lane_id();
-  const uint32_t wave = threadIdx.x / KVR_WAVE;
-  const uint32_t nwaves = blockDim.x / KVR_WAVE;
-  const uint32_t nh = nwaves - 2;  // helper waves (>= 2)
-  // the last helper ranks new leaves; half of the helpers compute the draw
-  // words first, the rest start on the next query's matches at once (both
-  // are due about when the front half of the insertion ends)
-  const uint32_t ndraw = nh / 2u < 16u ? nh / 2u : 16u;
-  const uint32_t nd = ndraw * KVR_WAVE;  // drawing threads
+  const uint32_t wave = uni((uint32_t)(threadIdx.x / KVR_WAVE));
   GlobalHdr* g = reinterpret_cast<GlobalHdr*>(a.ws + a.L.off_global);
   ReplicaHdr* rh = reinterpret_cast<ReplicaHdr*>(a.ws + a.L.off_rhdr) + r;
 
-  if (threadIdx.x == 0) {
-    f.top = 1;  // q_1 may be staged at once (its buffer is free)
-    f.routed = f.staged = f.matched = f.handed = f.evicted = f.end = 0;
-    f.decayed = 0;
-    f.ework = kNoWorker;
-    f.ework_size = 0;
-    f.next[0] = f.next[1] = 0;
-    f.claim[0] = f.claim[1] = 0ull;
-    f.last_worker = kNoWorker;
-    f.pad = 0;
-    f.stop = __atomic_load_n(&g->status, __ATOMIC_RELAXED) ? 1u : 0u;
-    ell_sh[0] = ell_sh[1] = 0x7fffffff;
-    rank_ready_sh = 0;
-    for (uint32_t i = 0; i < kMaxWorkers; ++i) mtok_sh[i] = 0ull;
-    for (int p = 0; p < KVR_PHASES; ++p) eticks_sh[p] = 0;
+  // ---- the launch's state: nothing here depends on anything else but the
+  // root filters on the tree state, so its loads are under way together; what
+  // changes the replica's state (the decay to the first arrival with the rest)
+  // comes after the verdict on the batch
+  const int64_t tprev = rh->tprev;
+  if (threadIdx.x < kFlagWords) reinterpret_cast<uint32_t*>(&f)[threadIdx.x] = 0u;
+  if (threadIdx.x < KVR_PHASES) eticks_sh[threadIdx.x] = 0ull;
+  if (threadIdx.x < kMaxWorkers) {
+    mtok_sh[threadIdx.x] = 0ull;
+    h_sh[0][threadIdx.x] = h_sh[1][threadIdx.x] = h_sh[2][threadIdx.x] = 0;
   }
-  for (uint32_t x = threadIdx.x; x < W * kRootFilterWords; x += blockDim.x) rootf[x] = 0u;
+  if (threadIdx.x < kJobs) {
+    ell_sh[threadIdx.x] = 0x7fffffff;
+    jdone_sh[threadIdx.x] = 0u;
+    rank_ready_sh[threadIdx.x] = 0u;
+    rn_sh[threadIdx.x] = 0ull;
+  }
+  for (uint32_t x = threadIdx.x; x < W * kRootFilterWords; x += 64 * NW) rootf[x] = 0u;
   __syncthreads();
-  if (f.stop) return;
-
-  // query 0: stage it; completions and decay at its arrival; full matches
-  {
-    const uint64_t o0 = a.offsets[0];
-    const int32_t L0 = (int32_t)(a.offsets[1] - o0);
-    for (int32_t x = (int32_t)threadIdx.x; x < L0; x += (int32_t)blockDim.x) smem[x] = a.tokens[o0 + x];
-    if (wave == 0 && (uint32_t)lane < W)
-      complete_and_decay(a.C, worker_ptrs(a.ws, a.L, r, (uint32_t)lane), a.arrival[0], rh->tprev);
-    // the root filters: the first token of every child of every root
-    for (uint32_t i = wave; i < W; i += nwaves) {
-      Ptrs P = worker_ptrs(a.ws, a.L, r, i);
-      const int32_t* ar = arena_of(P, P.hdr->arena_sel);
-      const NodeRec root = P.nodes[0];
-      for (int32_t c = lane; c < root.nchild; c += KVR_WAVE) rf_add(rootf + i * kRootFilterWords, ar[root.coff + 2 * c]);
-    }
-    __syncthreads();
-    for (uint32_t i = wave; i < W; i += nwaves) {
-      Ptrs P = worker_ptrs(a.ws, a.L, r, i);
-      count_mtok(mtok_sh, i, match_lcp<kPipeMatchUnroll>(P, P.hdr->arena_sel, smem, L0, paths.of(i)), &h_sh[0][i]);
-    }
-    if (threadIdx.x == 0) f.decayed = 1;
-    __syncthreads();
+  for (uint32_t x = threadIdx.x; x < W * (uint32_t)kStWords; x += 64 * NW) {
+    const uint32_t* hw = reinterpret_cast<const uint32_t*>(worker_ptrs(a.ws, a.L, r, x / kStWords).hdr);
+    tree_sh[x] = hw[x % kStWords];
   }
+  if (threadIdx.x < W) {
+    const uint32_t w = threadIdx.x;
+    const Ptrs P = worker_ptrs(a.ws, a.L, r, w);
+    const WorkerHdr* h = P.hdr;
+    lb.P[w] = h->P;
+    for (int k = 0; k < 4; ++k) lb.theta[k * W + w] = h->theta[k];
+    lb.Wb[w] = h->Wb;
+    lb.head[w] = h->pend_head;
+    lb.count[w] = h->pend_count;
+    lb.done_at[w] = h->pend_count > 0 ? P.pend[h->pend_head].t_done : kNever;
+    lb.size[w] = h->size;
+    st_sh[w] = 0u;
+    for (uint32_t b = 0; b < a.nbuf; ++b) trail_sh[(b * W + w) * kTrailWords] = 0;
+  }
+  // the root filters: the first token of every child of every root
+  for (uint32_t i = wave; i < W; i += NW) {
+    const Ptrs P = worker_ptrs(a.ws, a.L, r, i);
+    const NodeRec root = load_node(P.nodes, 0);
+    const int32_t* ar = arena_of(P, uni(P.hdr->arena_sel));
+    for (int32_t c = lane; c < root.nchild; c += KVR_WAVE) rf_add(rootf + i * kRootFilterWords, ar[root.coff + 2 * c]);
+  }
+  check_batch(a, g, tprev, &f.bad);
+  __syncthreads();
+  if (!batch_ok(g, f.bad)) return;
 
+  const uint32_t n = a.n;
+  PhaseClock clk;
+  clock_start<PT>(&clk);
+  // progress of this wave: the next query to route (routing wave); the
+  // insertion taken (evicting waves); the next query to stage and to serve once
+  // routed (helpers)
+  uint32_t kq = 0, sN = 0, dN = 0;
+  uint32_t spins = 0, seen = 0;
+  uint32_t ring_head = 0;
+  bool ticket = false;
+  uint64_t chain = 0, routed_total = 0;
+  int64_t tick_prev = 0;
+  if (wave == NE + 1u) {
+    chain = rh->route_digest;
+    routed_total = rh->queries;
+    // completions and decay at the first arrival
+    const int64_t t = a.arrival[0], tick = t / a.C.dt_us;
+    if ((uint32_t)lane < W) {
+      const Ptrs P = worker_ptrs(a.ws, a.L, r, (uint32_t)lane);
+      decay_lds(a.C, lb, (uint32_t)lane, P.hdr, P.pend, P.PC, t, tprev, tick, tprev / a.C.dt_us);
+    }
+    tick_prev = tick;
+    st_rel(&f.decayed, 1u);
+  }
+  // Take the (claimed) match of query mm on worker mw, whose state was msv.
+  const auto match_one = [&](uint32_t mm, uint32_t mw, uint32_t msv) __attribute__((always_inline)) {
+    const uint32_t mp = query_slot(mm, a.nbuf), mq = query_slot(mm + a.nbuf - 1u, a.nbuf);  // its slot, the last one's
+    const int32_t h_old = uni(h_sh[mq][mw]);
+    const int32_t ell = mm > 0u ? uni(ell_sh[(mm - 1u) & 3u]) : 0;
+    const Ptrs P = worker_ptrs(a.ws, a.L, r, mw);
+    MatchEnd me{};
+    bool walked = false;
+    const int32_t h = match_ahead<kPipeMatchUnroll>(
+        P.nodes, arena_of(P, uni(tree_sh[mw * kStWords + 12])), rootf + mw * kRootFilterWords, P.A,
+        smem + mp * qwords + kQueryPad, uni(len_sh[mm & 3u]), h_old, ell,
+        trail_sh + (mq * W + mw) * kTrailWords, trail_sh + (mp * W + mw) * kTrailWords, walked, me);
+    bool stays = true;
+    if (msv & kOwner) {
+      // beside the evictions of an earlier query's insertion: this match
+      // and the inserted path agree at least up to the LCPs in between
+      const uint32_t jk = uni(owner_sh[mw]);
+      int32_t on_path = jk + 1u == mm ? ell : 0;
+      if (jk + 2u == mm) {
+        const int32_t e0 = uni(ell_sh[jk & 3u]);
+        on_path = e0 < ell ? e0 : ell;
+      }
+      stays = match_stays(P.nodes, load_job(&job_sh[jk % kJobs]), h, on_path, walked, me);
+    }
+    if (stays && lane == 0) {
+      h_sh[mp][mw] = h;
+      atomicAdd(&mtok_sh[mw], (unsigned long long)(uint32_t)h);
+    }
+    if (stays) {  // one more query matched, and no reader
+      add_rel(&st_sh[mw], (1u << kCountShift) - kReader);
+    } else if (lane == 0) {
+      // put off until the owner is done, or to be taken again if it just was
+      if (atomicCAS(&st_sh[mw], msv | kReader, msv | kDeferred) != (msv | kReader)) atomicAnd(&st_sh[mw], ~kReader);
+    }
+  };
+
+#ifdef KVR_PRIO
+  if (wave == 0) __builtin_amdgcn_s_setprio(3);
+  else if (wave <= NE) __builtin_amdgcn_s_setprio(2);
+#endif
   if (wave == 0) {
-    // ---------------------------------------------------------- routing wave
-    uint64_t chain = rh->route_digest, routed = rh->queries;
-    PhaseClock clk;
-    clock_start<PT>(&clk);
-    uint32_t issued = 0;    // insertions handed to the evicting wave
-    uint32_t last_job = 0;  // query index (in the batch) of the last one
-    for (uint32_t k = 0; k < a.n; ++k) {
-      const uint32_t cur = k & 1u;
-      const uint64_t jg = a.j0 + k;
-      const uint64_t o0 = a.offsets[k];
-      const int32_t Lp = (int32_t)(a.offsets[k + 1] - o0);
-      const int64_t t = a.arrival[k];
-      const int32_t olen = query_out_len(a.out_len, k);
-      const bool has_next = k + 1 < a.n;
-      const int32_t Ln = has_next ? (int32_t)(a.offsets[k + 2] - a.offsets[k + 1]) : 0;
-      int32_t* qs = smem + cur * qstride;
-      const int32_t* qn = smem + (cur ^ 1u) * qstride;
-      // h of q_k on every worker (taking any match no other wave has taken
-      // yet), completions and decay at its arrival
-      if (k > 0) {
-        const uint32_t pc = cur ^ 1u;
-        const int32_t Lprev = (int32_t)(a.offsets[k] - a.offsets[k - 1]);
-        const int32_t ellp = ell_sh[pc];
-        const int32_t ell_r = ellp < Lp ? ellp : Lp;
-        const int32_t ell = ell_r < Lprev ? ell_r : Lprev;
-        const uint32_t prev = k > 1 ? (uint32_t)best_sh[cur] : 0u;
-        const uint32_t mine = take_matches_pipe<kPipeMatchUnroll>(a, r, W, pc, (uint32_t)best_sh[pc], prev, qs, Lp, ell, h_sh[pc],
-                                                h_sh[cur], &f, mtok_sh, rootf, paths);
-        if (mine) add_rel(&f.matched, mine);
-        clock_mark<PT>(&clk, KVR_PHASE_MATCH);
-      }
-      // every worker's h of q_k: W per query from q_1 on (the routed
-      // worker's from this wave or the evicting wave, the others' from the
-      // helpers, this wave or the evicting wave)
-      if (k > 0 && !pipe_wait(&f.matched, k * W, &f, g, r, jg, 0)) break;
-      if (!pipe_wait(&f.decayed, k + 1, &f, g, r, jg, 1)) break;
-      clock_mark<PT>(&clk, KVR_PHASE_JOIN);
-
-      // the draw words and rounds of this parity are reused below: the
-      // evicting wave must be done with the insertion that used them
-      if (issued > 0 && (last_job & 1u) == cur && !pipe_wait(&f.evicted, issued, &f, g, r, jg, 11)) break;
-      // ---- route: scores, argmin, commit
-      const uint32_t ew = ld_acq(&f.ework);
-      const uint32_t ew_size = __hip_atomic_load(&f.ework_size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      double eh = __builtin_huge_val(), ch = 0.0;
-      RouteView v{};
-      if ((uint32_t)lane < W) {
-        v = load_view(worker_ptrs(a.ws, a.L, r, (uint32_t)lane).hdr);
-        // the worker being evicted: its size once the evictions are done
-        if ((uint32_t)lane == ew) v.size = ew_size;
-        eh = lbgr_score(a.C, v, h_sh[cur][lane], Lp, &ch);
-        eh_sh[lane] = eh;
-      }
-      __builtin_amdgcn_wave_barrier();
-      const uint32_t best = route_choice(a, r, k, W, eh, h_sh[cur], Lp, eh_sh, v);
-      Ptrs P = worker_ptrs(a.ws, a.L, r, best);
-      const int32_t hb = h_sh[cur][best];
-      uint32_t cerr = 0;
-      if ((uint32_t)lane == best) cerr = commit_route(a.C, P, v, ch, hb, hb, Lp, t, olen);
-      const uint32_t err0 = (uint32_t)__builtin_amdgcn_readlane((int)cerr, (int)best);
-      const uint32_t size = (uint32_t)__builtin_amdgcn_readlane((int)v.size, (int)best);
-      const uint32_t nload = (uint32_t)(Lp - hb);
-      const uint32_t nfree = a.L.B - size;
-      const uint32_t nev = nload > nfree ? nload - nfree : 0u;
-      const uint32_t rn = nev < a.rcap ? nev : a.rcap;
-      if ((uint32_t)lane < 16u) prog_sh[cur][lane] = 0u;
-      if (lane == 0) {
-        best_sh[cur] = (int32_t)best;
-        rn_sh[cur] = rn;
-        f.next[cur] = 0;
-        f.claim[cur] = 0ull;
-        rank_ready_sh = 0;
-        const uint64_t orow = (uint64_t)r * a.n + k;
-        if (a.route) a.route[orow] = (int32_t)best;
-        if (a.hits) a.hits[orow] = hb;
-        if (!err0) {
-          chain = route_chain(chain, jg, best, hb);
-          routed += 1;
-        }
-      }
-      if (a.all_hits && (uint32_t)lane < W) a.all_hits[((uint64_t)r * a.n + k) * W + (uint32_t)lane] = h_sh[cur][lane];
-      if (err0) {
-        const int64_t dbg[4] = {0, 0, 0, 0};
-        pipe_stop(g, &f, r, jg, err0, dbg);
-        break;
-      }
-      st_rel(&f.routed, k + 1);
-      clock_mark<PT>(&clk, KVR_PHASE_ROUTE);
-
-      // ---- front half of the insertion of q_k (the worker being evicted first
-      // finishes its evictions)
-      if (ew == best && !pipe_wait(&f.evicted, issued, &f, g, r, jg, 3)) break;
-      clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
-      EvictJob& job = job_sh[issued & 1u];
-      {
-        InsertArgs ia;
-        ia.seed = a.C.seed;
-        ia.jg = jg;
-        ia.worker = best;
-        ia.replica = r;
-        ia.B = a.L.B;
-        ia.rn = rn;
-        ia.rw = rwb + (size_t)cur * a.rcap;
-        ia.prog = rn ? prog_sh[cur] : nullptr;
-        ia.nprog = ndraw;
-        ia.round = 2u * nd;
-        ia.rank = hb < Lp ? &rank_sh : nullptr;
-        ia.rank_ready = &rank_ready_sh;
-        int64_t dbg[4] = {0, 0, 0, 0};
-        const uint32_t err = rlt_insert_front<PT>(P, ia, qs, Lp, hb, paths.of(best), dbg, job, &clk);
-        if (err) {
-          pipe_stop(g, &f, r, jg, err, dbg);
-          break;
-        }
-      }
-      // a new child of the root: its first token joins the root filter
-      if (hb == 0 && lane == 0) rf_add(rootf + best * kRootFilterWords, qs[0]);
-      // q_k's buffer is free: q_k+2 may be staged (its LCP with q_k+1 goes to
-      // the slot of LCP(q_k-1, q_k), which nothing reads any more)
-      if (lane == 0) ell_sh[cur ^ 1u] = 0x7fffffff;
-      st_rel(&f.top, k + 2);
-      // ---- nothing to evict: the routed worker's h of the next query (on
-      // the tree after the load, which is final) and the back half here;
-      // else both on the evicting wave once it is free
-      if (job.nev == 0) {
-        if (has_next) {
-          if (!pipe_wait(&f.staged, (k + 1) * nh, &f, g, r, jg, 4)) break;
-          clock_mark<PT>(&clk, KVR_PHASE_STAGE_WAIT);
-          const int32_t ellp = ell_sh[cur];
-          const int32_t ell_r = ellp < Ln ? ellp : Ln;
-          count_mtok(mtok_sh, best,
-                     match_pipe(P, (int32_t)job.s.arena_sel, rootf + best * kRootFilterWords, qn, Ln, Lp, ell_r,
-                                paths.of(best)),
-                     &h_sh[cur ^ 1u][best]);
-          add_rel(&f.matched, 1u);
-          clock_mark<PT>(&clk, KVR_PHASE_MATCH);
-        }
-        int64_t dbg[4] = {0, 0, 0, 0};
-        const uint32_t err = rlt_insert_back<PT>(P, job, ustage, dbg, &clk);
-        if (err) {
-          pipe_stop(g, &f, r, jg, err, dbg);
-          break;
+    for (;;) {
+      // -------------------------------------------------------- routing wave
+      // h of q_kq on every worker
+      if (kq == n) break;
+      // the match to take this round, if any: query mm on worker mw, whose state
+      // was msv
+      uint32_t msv = 0, mm = 0, mw = 0;
+      const uint32_t sv =
+          (uint32_t)lane < W ? __hip_atomic_load(&st_sh[lane], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
+      const uint64_t open = __ballot((uint32_t)lane < W && (sv >> kCountShift) == (kq & kCountMask));
+      if (open) {
+        const uint64_t can = __ballot((uint32_t)lane < W && can_match(sv, kq, owner_sh[lane], a.nbuf));
+        if (can && ld_acq(&f.staged) >= (kq + 1u) * nh) {
+          mw = (uint32_t)first_lane(can);
+          mm = kq;
+          msv = (uint32_t)__builtin_amdgcn_readlane((int)sv, (int)mw);
+          if (!claim_match(&st_sh[mw], msv)) continue;
+        } else {
+          if (!pipe_poll(spins, &f, g, r, a.j0 + kq, 0)) break;
+          continue;
         }
       } else {
-        // the evicting wave takes the routed worker's h of the next query
-        // before its evictions; while it still evicts for an earlier
-        // insertion, this wave takes that match here first
-        uint32_t early = 0;
-        if (has_next && ld_acq(&f.evicted) < issued) {
-          if (!pipe_wait(&f.staged, (k + 1) * nh, &f, g, r, jg, 4)) break;
+        {
+          // ---- route q_kq
+          spins = 0;
+          const uint32_t k = kq, cur = query_slot(k, a.nbuf), nxt = query_slot(k + 1u, a.nbuf), slot = k % kJobs;
+          const uint64_t jg = a.j0 + k;
+          clock_mark<PT>(&clk, KVR_PHASE_JOIN);
+          if (!pipe_wait(&f.decayed, k + 1u, &f, g, r, jg, 1)) break;
           clock_mark<PT>(&clk, KVR_PHASE_STAGE_WAIT);
-          const int32_t ellp = ell_sh[cur];
-          const int32_t ell_r = ellp < Ln ? ellp : Ln;
-          const int32_t h = match_pipe(P, (int32_t)job.s.arena_sel, rootf + best * kRootFilterWords, qn, Ln, Lp,
-                                       ell_r, paths.of(best));
-          if (h == ell_r) {
-            count_mtok(mtok_sh, best, h, &h_sh[cur ^ 1u][best]);
-            add_rel(&f.matched, 1u);
-            early = 1;
-          } else {
-            early = 2;
+          // the slot of insertion k - kJobs is reused
+          if (k >= kJobs) {
+            bool ok = true;
+            while (ld_acq(&jdone_sh[slot]) != k - kJobs + 1u)
+              if (!(ok = pipe_poll(spins, &f, g, r, jg, 2))) break;
+            if (!ok) break;
           }
-          clock_mark<PT>(&clk, KVR_PHASE_MATCH);
+          clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
+          const int32_t Lp = uni(len_sh[k & 3u]);
+          double eh = __builtin_huge_val(), ch = 0.0;
+          RouteView v{};
+          if ((uint32_t)lane < W) {
+            v.P = lb.P[lane];
+            for (int x = 0; x < 4; ++x) v.theta[x] = lb.theta[x * W + lane];
+            v.Wb = lb.Wb[lane];
+            v.pend_head = lb.head[lane];
+            v.pend_count = lb.count[lane];
+            v.size = lb.size[lane];
+            eh = lbgr_score(a.C, v, h_sh[cur][lane], Lp, &ch);
+            eh_sh[lane] = eh;
+          }
+          __builtin_amdgcn_wave_barrier();
+          const uint32_t best = uni(route_choice(a, r, k, W, eh, h_sh[cur], Lp, eh_sh, v));
+          const Ptrs P = worker_ptrs(a.ws, a.L, r, best);
+          const int32_t hb = uni(h_sh[cur][best]);
+          const uint32_t size = (uint32_t)__builtin_amdgcn_readlane((int)v.size, (int)best);
+          const uint32_t nload = (uint32_t)(Lp - hb);
+          const uint32_t nfree = a.L.B - size;
+          const uint32_t nev = nload > nfree ? nload - nfree : 0u;
+          // commit: the routed worker's lane
+          uint32_t err0 = 0;
+          if ((uint32_t)lane == best) {
+            err0 = commit_lds(a.C, P, lb, best, v, ch, hb, Lp, arr_sh[k & 3u], olen_sh[k & 3u]);
+            lb.size[best] = size + nload - nev;
+          }
+          err0 = (uint32_t)__builtin_amdgcn_readlane((int)err0, (int)best);
+          // draw words: a stretch of the ring that no unfinished insertion uses
+          uint32_t rn = nev, r0 = 0;
+          if (nev > 0) {
+            uint32_t jd = 0, j0 = 0, jn = 0;
+            // lane i looks at insertion k - kJobs + 1 + i (the oldest first)
+            const uint32_t ji = k - kJobs + 1u + (uint32_t)lane;
+            bool used = false;
+            if ((uint32_t)lane < kJobs - 1u && ji < k) {
+              const uint32_t js = ji % kJobs;
+              jd = jdone_sh[js];
+              j0 = r0_sh[js];
+              jn = (uint32_t)rn_sh[js];
+              used = jd != ji + 1u && jn > 0u;
+            }
+            const uint64_t um = __ballot(used);
+            uint32_t room = a.rcap;
+            if (um) {
+              const uint32_t tail = (uint32_t)__builtin_amdgcn_readlane((int)j0, first_lane(um));
+              if (ring_head > tail) {
+                const uint32_t after = a.rcap - ring_head;
+                r0 = after >= nev || after >= tail ? ring_head : 0u;
+                room = r0 ? after : tail;
+              } else {
+                r0 = ring_head;
+                room = tail - ring_head;
+              }
+            }
+            rn = nev < room ? nev : room;
+            ring_head = r0 + rn;
+          }
+          if ((uint32_t)lane < 16u) prog_sh[slot][lane] = 0u;
+          if (lane == 0) {
+            best_sh[slot] = best;
+            hit_sh[slot] = hb;
+            r0_sh[slot] = r0;
+            rn_sh[slot] = ((uint64_t)(k + 1u) << 32) | rn;
+            rank_ready_sh[slot] = 0u;
+          }
+          if (err0) {
+            if (lane == 0) {
+              const uint64_t orow = (uint64_t)r * n + k;
+              if (a.route) a.route[orow] = (int32_t)best;
+              if (a.hits) a.hits[orow] = hb;
+            }
+            const int64_t dbg[4] = {0, 0, 0, 0};
+            pipe_stop(g, &f, r, jg, err0, dbg);
+            break;
+          }
+          st_rel(&f.routed, k + 1u);
+          clock_mark<PT>(&clk, KVR_PHASE_ROUTE);
+          // ---- own the worker: its earlier insertion first finishes, and so
+          // does a match of q_k+1 on it
+          uint32_t pre = 0;  // matches of later queries taken on it
+          {
+            bool ok = true;
+            while (ld_acq(&st_sh[best]) & kOwner)
+              if (!(ok = pipe_poll(spins, &f, g, r, jg, 3))) break;
+            if (!ok) break;
+            if (lane == 0) atomicOr(&st_sh[best], kOwner);
+            uint32_t sb;
+            while ((sb = ld_acq(&st_sh[best])) & kReader)
+              if (!(ok = pipe_poll(spins, &f, g, r, jg, 4))) break;
+            if (!ok) break;
+            pre = ((sb >> kCountShift) - (k + 1u)) & kCountMask;
+            spins = 0;
+          }
+          clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
+          // ---- the load of the new leaf
+          St s = load_st_lds(tree_sh + best * kStWords);
+          PipeJob job;
+          int32_t split;
+          int32_t* tr = trail_sh + (cur * W + best) * kTrailWords;
+          const uint32_t err =
+              load_leaf(P, s, a.L.B, a.L.maxL, smem + cur * qwords + kQueryPad, Lp, hb, tr, job,
+                        split);
+          store_st_lds(tree_sh + best * kStWords, s);
+          if (err) {
+            const int64_t dbg[4] = {s.dbg_check, s.dbg_val[0], s.dbg_val[1], s.dbg_val[2]};
+            pipe_stop(g, &f, r, jg, err, dbg);
+            break;
+          }
+          // a new child of the root: its first token joins the root filter
+          if (hb == 0 && lane == 0) rf_add(rootf + best * kRootFilterWords, job.tok);
+          // matches taken on the tree before: what the load makes of that of
+          // q_k+1; that of q_k+2 is taken again
+          uint32_t state = kLoaded;
+          if (pre) {
+            const int32_t h_pre = uni(h_sh[nxt][best]);
+            bool stays;
+            const int32_t h = match_after_load(P.nodes, job, split, h_pre, uni(ell_sh[k & 3u]), tr,
+                                               trail_sh + (nxt * W + best) * kTrailWords, stays);
+            int32_t diff = (stays ? h : 0) - h_pre;
+            if (pre > 1u) {
+              diff -= uni(h_sh[query_slot(k + 2u, a.nbuf)][best]);
+              state -= 1u << kCountShift;
+            }
+            if (lane == 0) {
+              h_sh[nxt][best] = h;
+              atomicAdd(&mtok_sh[best], (unsigned long long)(int64_t)diff);
+            }
+            // (put off: one match fewer, to be taken after the evictions)
+            if (!stays) state += kDeferred - (1u << kCountShift);
+          }
+          if (lane == 0) {
+            PipeJob& j = job_sh[slot];
+            j.k = k;
+            j.worker = best;
+            j.h = job.h;
+            j.L = job.L;
+            j.l = job.l;
+            j.a = job.a;
+            j.tok = job.tok;
+            j.nfree = job.nfree;
+            j.nev = job.nev;
+            j.rn = rn;
+            j.r0 = r0;
+            j.replace = job.replace;
+            j.marked = job.marked;
+            j.calm = job.calm;
+            j.phase = job.phase;
+            owner_sh[best] = k;
+            h_sh[cur][best] = Lp;  // all of q_k is cached here now
+            // q_k's buffer is free, and so is the slot of the LCP of the query
+            // that will be staged there with the one before it
+            ell_sh[(k + a.nbuf - 1u) & 3u] = 0x7fffffff;
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+          if (lane == 0) {
+            __hip_atomic_fetch_add(&st_sh[best], state, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&f.fronts, k + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&f.handed, k + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (hb < Lp)
+              __hip_atomic_store(&rank_ready_sh[slot], ((k + 1u) << 2) | 1u, __ATOMIC_RELEASE,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+          kq = k + 1u;
+          clock_mark<PT>(&clk, KVR_PHASE_LOAD);
+          continue;
         }
-        if (!pipe_wait(&f.evicted, issued, &f, g, r, jg, 5)) break;
-        clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
-        if (lane == 0) {
-          early_sh[issued & 1u] = early;
-          __hip_atomic_store(&f.ework, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_store(&f.ework_size, job.final_size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        issued += 1;
-        last_job = k;
-        st_rel(&f.handed, issued);
       }
+      match_one(mm, mw, msv);
+      clock_mark<PT>(&clk, KVR_PHASE_MATCH);
     }
-    st_rel(&f.end, 1u);
-    if (lane == 0) {
-      rh->route_digest = chain;
-      rh->queries = routed;
-      if constexpr (PT)
-        for (int p = 0; p < KVR_PHASES; ++p) rh->phase_ticks[p] += clk.acc[p];
-    }
-  } else if (wave == 1) {
+  } else if (wave <= NE) {
     // ---------------------------------------------------------- evicting wave
-    PhaseClock clk;
-    clock_start<PT>(&clk);
-    uint32_t done = 0;
     for (;;) {
-      // the next insertion, or the end (the bound on the wait restarts
-      // whenever the routing wave routes a query)
-      uint32_t spins = 0, seen = ld_acq(&f.routed);
-      bool quit = false;
-      for (;;) {
-        if (ld_acq(&f.handed) > done) break;
+      if (!ticket) {
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(&f.ticket, 1u);
+        kq = uni(t);
+        ticket = true;
+        spins = 0;
+      }
+      if (ld_acq(&f.handed) <= kq) {  // wait for that insertion
+        if (ld_acq(&f.end)) break;  // every insertion has been handed by then
         const uint32_t now = ld_acq(&f.routed);
         if (now != seen) {
           seen = now;
           spins = 0;
         }
-        if (ld_acq(&f.end) && ld_acq(&f.handed) == done) {
-          quit = true;
-          break;
-        }
-        if (__hip_atomic_load(&f.stop, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-          quit = true;
-          break;
-        }
-        if (++spins > kSpinLimit) {
-          const int64_t dbg[4] = {96, (int64_t)done, 0, 0};
-          pipe_stop(g, &f, r, a.j0, KVR_DEV_INTERNAL, dbg);
-          quit = true;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
+        if (!pipe_poll(spins, &f, g, r, a.j0 + kq, 6)) break;
+        continue;
       }
-      if (quit) break;
       clock_mark<PT>(&clk, KVR_PHASE_E_IDLE);
-      const EvictJob& job = job_sh[done & 1u];
-      const uint32_t w = job.worker;
-      const Ptrs Pw = worker_ptrs(a.ws, a.L, r, w);
-      // the routed worker's h of the next query q_kq+1, first on the tree
-      // after the load: exact when it ends where q_kq+1 leaves the inserted
-      // path (depth LCP(q_kq, q_kq+1), marked, so no eviction shortens it;
-      // no child can match there later, as evictions only remove tokens),
-      // else taken again after the evictions
-      const uint32_t kq = (uint32_t)(job.ia.jg - a.j0);
-      const bool has_next = kq + 1u < a.n;
-      const uint32_t early = early_sh[done & 1u];
-      bool exact = early != 2u;
-      int32_t Lnx = 0, ell_r = 0;
-      const int32_t* qnx = smem + ((kq + 1u) & 1u) * qstride;
-      if (has_next) {
-        if (!pipe_wait(&f.staged, (kq + 1u) * nh, &f, g, r, job.ia.jg, 13)) break;
-        Lnx = (int32_t)(a.offsets[kq + 2] - a.offsets[kq + 1]);
-        const int32_t ellp = ell_sh[kq & 1u];
-        ell_r = ellp < Lnx ? ellp : Lnx;
-      }
-      if (has_next && early == 0u) {
-        const int32_t h = match_pipe(Pw, (int32_t)job.s.arena_sel, rootf + w * kRootFilterWords, qnx, Lnx, job.L,
-                                     ell_r, paths.of(w));
-        exact = h == ell_r;
-        if (exact) {
-          count_mtok(mtok_sh, w, h, &h_sh[(kq + 1u) & 1u][w]);
-          add_rel(&f.matched, 1u);
-        }
-        clock_mark<PT>(&clk, KVR_PHASE_E_MATCH);
-      }
-      int64_t dbg[4] = {0, 0, 0, 0};
-      const uint32_t err = rlt_insert_back<PT>(Pw, job, ustage, dbg, &clk, KVR_PHASE_E_EVICT, KVR_PHASE_E_FINISH);
-      if (err) {
-        pipe_stop(g, &f, r, job.ia.jg, err, dbg);
-        break;
-      }
-      if (has_next && !exact) {
-        count_mtok(mtok_sh, w,
-                   match_pipe(Pw, -1, rootf + w * kRootFilterWords, qnx, Lnx, job.L, ell_r, paths.of(w)),
-                   &h_sh[(kq + 1u) & 1u][w]);
-        add_rel(&f.matched, 1u);
-        clock_mark<PT>(&clk, KVR_PHASE_E_MATCH);
-      }
-      if (lane == 0) __hip_atomic_store(&f.ework, kNoWorker, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_WORKGROUP);
-      done += 1;
-      st_rel(&f.evicted, done);
-      // the helpers may be matching q_s+1 (s = the last query routed) and
-      // have left this worker to this wave: take that match unless a helper
-      // claimed it (or the worker is the one q_s went to)
+      ticket = false;
       {
-        const uint32_t rt = __hip_atomic_load(&f.routed, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (rt > 0 && rt < a.n) {
-          const uint32_t sq = rt - 1u, sc = sq & 1u;
-          unsigned long long old = 0ull;
-          if ((uint32_t)best_sh[sc] != w && lane == 0) old = atomicOr(&f.claim[sc], 1ull << w);
-          old = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(old >> 32), 0) << 32) |
-                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)old, 0);
-          if ((uint32_t)best_sh[sc] != w && !(old & (1ull << w))) {
-            if (!pipe_wait(&f.staged, rt * nh, &f, g, r, a.j0 + rt, 12)) break;
-            const int32_t Ls = (int32_t)(a.offsets[sq + 1] - a.offsets[sq]);
-            const int32_t Lnx = (int32_t)(a.offsets[sq + 2] - a.offsets[sq + 1]);
-            const int32_t ellp = ell_sh[sc];
-            const int32_t ell_r = ellp < Lnx ? ellp : Lnx;
-            const int32_t ell = ell_r < Ls ? ell_r : Ls;
-            Ptrs Pw = worker_ptrs(a.ws, a.L, r, w);
-            count_mtok(mtok_sh, w,
-                       match_pipe(Pw, -1, rootf + w * kRootFilterWords, smem + (sc ^ 1u) * qstride, Lnx, h_sh[sc][w],
-                                  ell, paths.of(w)),
-                       &h_sh[sc ^ 1u][w]);
-            add_rel(&f.matched, 1u);
-          }
+        // ---- marks, leaf list, evictions
+        PipeHook hook;
+        const uint32_t slot = kq % kJobs;
+        const PipeJob job = load_job(&job_sh[slot]);
+        const Ptrs P = worker_ptrs(a.ws, a.L, r, job.worker);
+        EvictJob ej;
+        ej.s = load_st_lds(tree_sh + job.worker * kStWords);
+        if (!job.marked) mark_cached(P, ej.s, a.L.B, job, 
+                                      trail_sh + (query_slot(kq, a.nbuf) * W + job.worker) * kTrailWords);
+        // the trail has been read
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane == 0) atomicOr(&st_sh[job.worker], kMarked);
+        clock_mark<PT>(&clk, KVR_PHASE_E_FINISH);
+        hook.todo = job.h < job.L;
+        hook.job = job;
+        hook.ready = &rank_ready_sh[slot];
+        hook.rank = &rank_sh[slot];
+        hook.state = tree_sh + job.worker * kStWords;
+        hook.stop = &f.stop;
+        ej.ia.seed = a.C.seed;
+        ej.ia.jg = a.j0 + kq;
+        ej.ia.worker = job.worker;
+        ej.ia.replica = r;
+        ej.ia.B = a.L.B;
+        ej.ia.rn = job.rn;
+        ej.ia.rw = ring + job.r0;
+        ej.ia.prog = job.rn ? prog_sh[slot] : nullptr;
+        ej.ia.nprog = ndraw;
+        ej.ia.round = 2u * nd;
+        ej.ia.rank = nullptr;
+        ej.ia.rank_ready = nullptr;
+        ej.h = job.h;
+        ej.L = job.L;
+        ej.l = job.l;
+        ej.nfree = job.nfree;
+        ej.nev = job.nev;
+        ej.c0 = ej.s.cnt;
+        ej.reset_at = job.h < job.L && ej.c0 + (uint32_t)(job.L - job.h) >= a.L.B + 1u ? job.h + (int32_t)(a.L.B - ej.c0)
+                                                                                       : -1;
+        ej.worker = job.worker;
+        ej.final_size = 0;
+        UStage us;
+        us.node = stage_base + (wave - 1u) * 4u * a.ucap;
+        us.len = us.node + a.ucap;
+        us.top = us.len + a.ucap;
+        us.par = us.top + a.ucap;
+        us.cap = a.ucap;
+        int64_t dbg[4] = {0, 0, 0, 0};
+        uint32_t err = ej.s.err;
+        if (err) {
+          dbg[0] = ej.s.dbg_check;
+          dbg[1] = ej.s.dbg_val[0];
+          dbg[2] = ej.s.dbg_val[1];
+          dbg[3] = ej.s.dbg_val[2];
+        } else {
+          err = rlt_evict<PT>(P, ej, us, dbg, &clk, KVR_PHASE_E_EVICT, KVR_PHASE_E_FINISH, hook);
         }
+        if (err) {
+          pipe_stop(g, &f, r, a.j0 + kq, err, dbg);
+          break;
+        }
+        // finished: the worker is free again
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane == 0) {
+          __hip_atomic_fetch_and(&st_sh[job.worker], ~(kOwner | kLoaded | kMarked | kDeferred), __ATOMIC_RELEASE,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_store(&jdone_sh[slot], kq + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        continue;
       }
     }
-    if constexpr (PT)
-      if (lane == 0)
-        for (int p = KVR_PHASE_E_EVICT; p < KVR_PHASES; ++p)
-          if (p <= KVR_PHASE_E_IDLE || p == KVR_PHASE_E_MATCH) atomicAdd(&eticks_sh[p], (unsigned long long)clk.acc[p]);
   } else {
-    // ---------------------------------------------------------- helper waves
-    const uint32_t hw = wave - 2u;  // 0 .. nh-1
-    PhaseClock clk;
-    clock_start<PT>(&clk);
-    for (uint32_t k = 0; k < a.n; ++k) {
-      const uint32_t cur = k & 1u;
-      const uint64_t jg = a.j0 + k;
-      const uint64_t o0 = a.offsets[k];
-      const int32_t Lp = (int32_t)(a.offsets[k + 1] - o0);
-      const int64_t t = a.arrival[k];
-      const bool has_next = k + 1 < a.n;
-      const uint64_t n0 = has_next ? a.offsets[k + 1] : 0;
-      const int32_t Ln = has_next ? (int32_t)(a.offsets[k + 2] - n0) : 0;
-      const int32_t* qs = smem + cur * qstride;
-      int32_t* qn = smem + (cur ^ 1u) * qstride;
-      // stage q_k+1 once the routing wave has begun q_k
-      if (has_next) {
-        if (!pipe_wait(&f.top, k + 1, &f, g, r, jg, 6)) break;
+    // ---------------------------------------------------------- helper wave
+    for (;;) {
+      // the match to take this round, if any: query mm on worker mw, whose state
+      // was msv
+      uint32_t msv = 0, mm = 0, mw = 0;
+      bool take = false;
+      const uint32_t hw = wave - NE - 1u;
+      const uint32_t fv = __hip_atomic_load(reinterpret_cast<uint32_t*>(&f) + (lane & (kFlagWords - 1)),
+                                            __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t routed = (uint32_t)__builtin_amdgcn_readlane((int)fv, 0);
+      const uint32_t fronts = (uint32_t)__builtin_amdgcn_readlane((int)fv, 1);
+      const uint32_t staged = (uint32_t)__builtin_amdgcn_readlane((int)fv, 2);
+      const uint32_t ended = (uint32_t)__builtin_amdgcn_readlane((int)fv, 6);
+      const uint32_t stopped = (uint32_t)__builtin_amdgcn_readlane((int)fv, 7);
+      if (dN < routed && (hw > 0 || stopped || sN > dN + 1u || dN + 1u == n)) {
+        // ---- what a routed query needs from this wave (the first helper
+        // needs the next arrival, which it puts down when it stages the query)
         clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
-        stage_next(a.tokens, n0, Ln, qn, qs, Lp, hw * KVR_WAVE + (uint32_t)lane, nh * KVR_WAVE, &ell_sh[cur]);
-        add_rel(&f.staged, 1u);
-        clock_mark<PT>(&clk, KVR_PHASE_H_STAGE);
+        const uint32_t k = dN, slot = k % kJobs;
+        dN += 1;
+        spins = 0;
+        if (hw == 0) {
+          // its outputs, then completions and decay at the next arrival
+          const uint32_t best = uni(best_sh[slot]);
+          const int32_t hb = uni(hit_sh[slot]);
+          const uint64_t orow = (uint64_t)r * n + k;
+          if (lane == 0) {
+            if (a.route) a.route[orow] = (int32_t)best;
+            if (a.hits) a.hits[orow] = hb;
+          }
+          if (a.all_hits && (uint32_t)lane < W) a.all_hits[orow * W + (uint32_t)lane] = (uint32_t)lane == best ? hb : h_sh[query_slot(k, a.nbuf)][lane];
+          if (k + 1u < n && !stopped) {
+            const int64_t t = arr_sh[(k + 1u) & 3u], tp = arr_sh[k & 3u];
+            const int64_t tick = t / a.C.dt_us;
+            if ((uint32_t)lane < W) {
+              const Ptrs P = worker_ptrs(a.ws, a.L, r, (uint32_t)lane);
+              decay_lds(a.C, lb, (uint32_t)lane, P.hdr, P.pend, P.PC, t, tp, tick, tick_prev);
+            }
+            tick_prev = tick;
+            st_rel(&f.decayed, k + 2u);
+          }
+          chain = route_chain(chain, a.j0 + k, best, hb);
+          routed_total += 1;
+          clock_mark<PT>(&clk, KVR_PHASE_H_OTHER);
+        } else if (hw <= ndraw && !stopped) {
+          // draw words, a round of 2 nd words at a time; each round written is
+          // published
+          const uint64_t info = rn_sh[slot];
+          const uint32_t rn = uni((uint32_t)info);
+          if (uni((uint32_t)(info >> 32)) == k + 1u && rn > 0u) {
+            const uint32_t best = uni(best_sh[slot]);
+            uint32_t* rw = ring + uni(r0_sh[slot]);
+            uint32_t rounds = 0;
+            for (uint32_t base = 0; base < rn; base += 2u * nd) {
+              const uint32_t d0 = base + (hw - 1u) * KVR_WAVE + (uint32_t)lane, d1 = d0 + nd;
+              const uint64_t w0 = philox_word0(a.j0 + k, best, d0, 0ull, a.C.seed, r);
+              const uint64_t w1 = philox_word0(a.j0 + k, best, d1, 0ull, a.C.seed, r);
+              if (d0 < rn) rw[d0] = (uint32_t)(w0 >> 32);
+              if (d1 < rn) rw[d1] = (uint32_t)(w1 >> 32);
+              ++rounds;
+              st_rel(&prog_sh[slot][hw - 1u], rounds);
+            }
+          }
+          clock_mark<PT>(&clk, KVR_PHASE_H_DRAW);
+        }
+        continue;
       }
-      if (!pipe_wait(&f.routed, k + 1, &f, g, r, jg, 7)) break;
-      clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
-      const uint32_t best = (uint32_t)best_sh[cur];
-      const uint32_t rn = rn_sh[cur];
-      // completions and decay at the next arrival (the first helper)
-      if (hw == 0 && has_next) {
-        if ((uint32_t)lane < W)
-          complete_and_decay(a.C, worker_ptrs(a.ws, a.L, r, (uint32_t)lane), a.arrival[k + 1], t);
-        st_rel(&f.decayed, k + 2);
-        clock_mark<PT>(&clk, KVR_PHASE_H_OTHER);
-      }
-      const int32_t hb = h_sh[cur][best];
-      if (hw == nh - 1u) {
-        // the last helper ranks the new leaf (on the tree before the
-        // insertion; the worker's previous evictions come first)
-        if (hb < Lp) {
-          if (!pipe_wait<true>(&f.ework, best, &f, g, r, jg, 8)) break;
-          rank_for_insertion(worker_ptrs(a.ws, a.L, r, best), paths.of(best), qs, hb, &rank_sh, &rank_ready_sh);
+      if (stopped) break;
+      // ---- a new leaf's rank that nobody has taken
+      const uint32_t rv = (uint32_t)lane < kJobs ? __hip_atomic_load(&rank_ready_sh[lane], __ATOMIC_ACQUIRE,
+                                                                     __HIP_MEMORY_SCOPE_WORKGROUP)
+                                                 : 0u;
+      const uint64_t rm = __ballot((rv & 3u) == 1u);
+      if (rm) {
+        clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
+        const int slot = first_lane(rm);
+        const uint32_t want = (uint32_t)__builtin_amdgcn_readlane((int)rv, slot);
+        uint32_t old = 0;
+        if (lane == 0) old = atomicCAS(&rank_ready_sh[slot], want, want + 1u);
+        if (uni(old) == want) {
+          const PipeJob job = load_job(&job_sh[slot]);
+          const St s = load_st_lds(tree_sh + job.worker * kStWords);
+          const Ptrs P = worker_ptrs(a.ws, a.L, r, job.worker);
+          const int32_t pos = rank_of_leaf(P, s.hwm, s.nleaves, arena_of(P, s.arena_sel), job);
+          if (lane == 0) rank_sh[slot] = pos;
+          st_rel(&rank_ready_sh[slot], want + 2u);
           clock_mark<PT>(&clk, KVR_PHASE_H_OTHER);
         }
-      } else if (hw < ndraw) {
-        // the drawing helpers compute the draw words, a round of 2*nd words
-        // at a time, and publish each round they complete
-        uint32_t* rw = rwb + (size_t)cur * a.rcap;
-        uint32_t rounds = 0;
-        for (uint32_t base = 0; base < rn; base += 2u * nd) {
-          const uint32_t d0 = base + hw * KVR_WAVE + (uint32_t)lane, d1 = d0 + nd;
-          const uint64_t w0 = philox_word0(jg, best, d0, 0ull, a.C.seed, r);
-          const uint64_t w1 = philox_word0(jg, best, d1, 0ull, a.C.seed, r);
-          if (d0 < rn) rw[d0] = (uint32_t)(w0 >> 32);
-          if (d1 < rn) rw[d1] = (uint32_t)(w1 >> 32);
-          ++rounds;
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          if (lane == 0) __hip_atomic_store(&prog_sh[cur][hw], rounds, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        clock_mark<PT>(&clk, KVR_PHASE_H_DRAW);
+        spins = 0;
+        continue;
       }
-      // h of q_k+1 on every worker but the routed one, the worker whose
-      // evictions may still run taken last
-      if (has_next) {
-        if (!pipe_wait(&f.staged, (k + 1) * nh, &f, g, r, jg, 9)) break;
+      // ---- stage the next query whose buffer is free
+      if (sN < n && sN < fronts + a.nbuf && staged >= sN * nh) {
         clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
-        const int32_t ellp = ell_sh[cur];
-        const int32_t ell_r = ellp < Ln ? ellp : Ln;
-        const int32_t ell = ell_r < Lp ? ell_r : Lp;
-        const uint32_t prev = k > 0 ? (uint32_t)best_sh[cur ^ 1u] : 0u;
-        bool ok = true;
-        const uint32_t mine = take_matches_pipe<kPipeItemUnroll>(a, r, W, cur, best, prev, qn, Ln, ell, h_sh[cur], h_sh[cur ^ 1u], &f,
-                                                mtok_sh, rootf, paths);
-        // this wave's matches, published at once
-        add_rel(&f.matched, mine);
-        clock_mark<PT>(&clk, KVR_PHASE_H_MATCH);
-        if (!ok) break;
+        const uint64_t o0 = a.offsets[sN];
+        const int32_t Ln = (int32_t)(a.offsets[sN + 1u] - o0);
+        const int32_t Lc = sN > 0u ? uni(len_sh[(sN - 1u) & 3u]) : 0;
+        if (hw == 0 && lane == 0) {
+          len_sh[sN & 3u] = Ln;
+          olen_sh[sN & 3u] = query_out_len(a.out_len, sN);
+          arr_sh[sN & 3u] = a.arrival[sN];
+        }
+        int32_t* qn = smem + query_slot(sN, a.nbuf) * qwords + kQueryPad;
+        const int32_t* qc = smem + query_slot(sN + a.nbuf - 1u, a.nbuf) * qwords + kQueryPad;
+        stage_query<4>(a.tokens, o0, Ln, qn, qc, Lc, hw * KVR_WAVE, nh * KVR_WAVE, &ell_sh[(sN - 1u) & 3u]);
+        add_rel(&f.staged, 1u);
+        sN += 1;
+        spins = 0;
+        clock_mark<PT>(&clk, KVR_PHASE_H_STAGE);
+        continue;
       }
+      // ---- a match: on each worker the next query not matched there, as far
+      // as queries are staged and their trails' slots are free (q_m takes that
+      // of q_m-nbuf, whose leaf must be loaded); the earliest query first, and
+      // each helper from another worker on
+      if (routed < n) {
+        const uint32_t whole = staged / nh;  // queries staged
+        uint32_t lim = fronts + a.nbuf;
+        if (lim > whole) lim = whole;        // matches of queries below this
+        const uint32_t sv = (uint32_t)lane < W ? __hip_atomic_load(&st_sh[lane], __ATOMIC_ACQUIRE,
+                                                                   __HIP_MEMORY_SCOPE_WORKGROUP)
+                                               : 0u;
+        const uint32_t m = routed + (((sv >> kCountShift) - routed) & kCountMask);
+        const bool ok = (uint32_t)lane < W && m < lim && can_match(sv, m, owner_sh[lane & (kMaxWorkers - 1u)], a.nbuf);
+        uint64_t can = __ballot(ok && m == routed);
+        if (!can) can = __ballot(ok && m == routed + 1u);
+        if (!can) can = __ballot(ok);
+        if (can) {
+          clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
+          const uint64_t hi = can & (~0ull << (hw * W / nh));
+          if (hi) can = hi;
+          mw = (uint32_t)first_lane(can);
+          mm = (uint32_t)__builtin_amdgcn_readlane((int)m, (int)mw);
+          msv = (uint32_t)__builtin_amdgcn_readlane((int)sv, (int)mw);
+          if (!claim_match(&st_sh[mw], msv)) continue;
+          take = true;
+          spins = 0;
+        }
+      }
+      if (!take) {
+        if (ended && dN >= routed) break;  // (and no rank is wanted)
+        const uint32_t now = routed + fronts + staged;
+        if (now != seen) {
+          seen = now;
+          spins = 0;
+        }
+#ifdef KVR_H_SLEEP
+        __builtin_amdgcn_s_sleep(KVR_H_SLEEP);
+#endif
+        if (!pipe_poll(spins, &f, g, r, a.j0 + routed, 9)) continue;  // (the duties of routed queries first)
+        continue;
+      }
+      match_one(mm, mw, msv);
+      clock_mark<PT>(&clk, KVR_PHASE_H_MATCH);
     }
+  }
+  if (wave == 0) {
+    st_rel(&f.end, 1u);
     if constexpr (PT)
       if (lane == 0)
-        for (int p = KVR_PHASE_H_STAGE; p <= KVR_PHASE_H_MATCH; ++p) atomicAdd(&eticks_sh[p], (unsigned long long)clk.acc[p]);
+        for (int p = 0; p < KVR_PHASES; ++p) rh->phase_ticks[p] += clk.acc[p];
+  } else {
+    if constexpr (PT)
+      if (lane == 0)
+        for (int p = KVR_PHASE_E_EVICT; p < KVR_PHASES; ++p) atomicAdd(&eticks_sh[p], (unsigned long long)clk.acc[p]);
+    if (wave == NE + 1u && lane == 0) {
+      rh->route_digest = chain;
+      rh->queries = routed_total;
+    }
   }
   __syncthreads();
-  if (threadIdx.x < W) worker_ptrs(a.ws, a.L, r, threadIdx.x).hdr->matched_tokens += mtok_sh[threadIdx.x];
+  // ---- the launch's state back to the headers
+  for (uint32_t x = threadIdx.x; x < W * (uint32_t)kStWords; x += 64 * NW)
+    if (x % kStWords < (uint32_t)kStWords - 1u)
+      reinterpret_cast<uint32_t*>(worker_ptrs(a.ws, a.L, r, x / kStWords).hdr)[x % kStWords] = tree_sh[x];
+  if (threadIdx.x < W) {
+    const uint32_t w = threadIdx.x;
+    WorkerHdr* h = worker_ptrs(a.ws, a.L, r, w).hdr;
+    h->P = lb.P[w];
+    for (int k = 0; k < 4; ++k) h->theta[k] = lb.theta[k * W + w];
+    h->Wb = lb.Wb[w];
+    if (f.decayed > 0u) h->tl = a.arrival[f.decayed - 1u];
+    h->pend_head = lb.head[w];
+    h->pend_count = lb.count[w];
+    h->matched_tokens += mtok_sh[w];
+  }
   if (threadIdx.x == 0) {
     if constexpr (PT)
       for (int p = KVR_PHASE_E_EVICT; p < KVR_PHASES; ++p) rh->phase_ticks[p] += eticks_sh[p];
-    if (!f.stop && a.n > 0) {
-      rh->tprev = a.arrival[a.n - 1];
-      if (r == 0) g->last_arrival = a.arrival[a.n - 1];
+    if (!f.stop) {
+      rh->tprev = a.arrival[n - 1u];
+      if (r == 0) g->last_arrival = a.arrival[n - 1u];
     }
   }
 }
@@ -1354,19 +1568,22 @@ __global__ void __launch_bounds__(64) stats_kernel(char* ws, Layout L, uint64_t 
 // ---------------------------------------------------------------- launchers (host)
 
 size_t step_lds_bytes(uint32_t maxL, uint32_t W, uint32_t ucap, uint32_t rcap, uint32_t path_sets) {
-  return 2 * (size_t)((maxL + 3u) & ~3u) * sizeof(int32_t) + (size_t)rcap * sizeof(uint32_t) +
+  return 2 * (size_t)query_words(maxL) * sizeof(int32_t) + (size_t)rcap * sizeof(uint32_t) +
          (size_t)path_sets * W * (3 * kPathMax + 1) * sizeof(int32_t) + (size_t)ucap * 4u * sizeof(int32_t);
 }
 
 
-// Dynamic LDS of the pipelined step kernel: two query buffers, the draw
-// words of two insertions (rcap each), the match paths, the root filters,
-// ucap staged candidates.
-size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t ucap, uint32_t rcap) {
-  return 2 * (size_t)((maxL + 3u) & ~3u) * sizeof(int32_t) + 2 * (size_t)rcap * sizeof(uint32_t) +
-         (size_t)W * (3 * kPathMax + 1) * sizeof(int32_t) + (size_t)W * kRootFilterWords * sizeof(uint32_t) +
-         (size_t)ucap * 4u * sizeof(int32_t);
+// Dynamic LDS of the pipelined step kernel: nbuf query buffers; per worker the
+// LBGR and tree state, the state word, nbuf trails and the root filter; rcap
+// draw words; ucap staged candidates per evicting wave.
+size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t nbuf, uint32_t ucap, uint32_t rcap) {
+  return (size_t)nbuf * query_words(maxL) * 4u +
+         (size_t)W * (kLbgrBytes + 4u * (1u + (uint32_t)kStWords + nbuf * (uint32_t)kTrailWords + kRootFilterWords)) +
+         (size_t)rcap * 4u + (size_t)kPipeEvictors * ucap * 16u;
 }
+
+uint32_t step_pipe_evictors() { return kPipeEvictors; }
+uint32_t step_pipe_jobs() { return kJobs; }
 
 hipError_t launch_init(char* ws, const Layout& L, double rls_p0, hipStream_t st) {
   const uint64_t work = (uint64_t)L.R * L.W > L.R ? (uint64_t)L.R * L.W : L.R;
@@ -1380,31 +1597,37 @@ hipError_t launch_init(char* ws, const Layout& L, double rls_p0, hipStream_t st)
   return hipGetLastError();
 }
 
-hipError_t launch_step(const StepArgs& a, hipStream_t st) {
-  const uint32_t blocks_v = (a.n + 255) / 256 < 1024 ? (a.n + 255) / 256 : 1024;
-  hipLaunchKernelGGL(validate_kernel, dim3(blocks_v ? blocks_v : 1), dim3(256), 0, st, a.ws, a.L,
-                     a.offsets, a.arrival, a.out_len, a.C.cache_responses, a.n);
-  hipLaunchKernelGGL(validate_tokens_kernel, dim3(1024), dim3(256), 0, st, a.ws, a.L, a.tokens,
-                     a.offsets, a.n);
+// Batches of at most this many tokens (at the longest) are checked by the step
+// kernel itself, each workgroup for itself, instead of by two kernels before it:
+// 3 us less a call up to 256 replicas (26.7 to 22.4 us for one short query).  At
+// 33,000 tokens the two are equal (217 us), above it the kernels are ahead.
+#ifndef KVR_CHECK_TOKENS
+#define KVR_CHECK_TOKENS 8192
+#endif
+constexpr uint64_t kCheckTokens = KVR_CHECK_TOKENS;
+constexpr uint32_t kCheckQueries = 256;  // (four rounds of a wave's lanes over their lengths)
+
+hipError_t launch_step(const StepArgs& args, hipStream_t st) {
+  StepArgs a = args;
+  a.check = a.n <= kCheckQueries && (uint64_t)a.n * a.L.maxL <= kCheckTokens ? 1u : 0u;
+  if (!a.check) {
+    const uint32_t blocks_v = (a.n + 255) / 256 < 1024 ? (a.n + 255) / 256 : 1024;
+    hipLaunchKernelGGL(validate_kernel, dim3(blocks_v ? blocks_v : 1), dim3(256), 0, st, a.ws, a.L,
+                       a.offsets, a.arrival, a.out_len, a.C.cache_responses, a.n);
+    hipLaunchKernelGGL(validate_tokens_kernel, dim3(1024), dim3(256), 0, st, a.ws, a.L, a.tokens,
+                       a.offsets, a.n);
+  }
   const uint32_t waves = a.L.W < kMaxWavesPerBlock ? a.L.W : kMaxWavesPerBlock;
   const size_t lds = step_lds_bytes(a.L.maxL, a.L.W, a.ucap, a.rcap, a.L.has_router ? 2u : 1u);
   const bool rt = a.L.has_router != 0, ba = a.L.beta > 1;
   if (a.pipe) {
-    const size_t lds_p = step_lds_bytes_pipe(a.L.maxL, a.L.W, a.ucap, a.rcap);
-    const bool wide = a.L.W >= kPipeWideWorkers;
-    if (a.C.phase_timers) {
-      if (wide)
-        hipLaunchKernelGGL((step_kernel_pipe<true, kPipeWavesWide>), dim3(a.L.R), dim3(64 * kPipeWavesWide), lds_p, st,
-                           a);
-      else
-        hipLaunchKernelGGL((step_kernel_pipe<true, kPipeWaves>), dim3(a.L.R), dim3(64 * kPipeWaves), lds_p, st, a);
-    } else {
-      if (wide)
-        hipLaunchKernelGGL((step_kernel_pipe<false, kPipeWavesWide>), dim3(a.L.R), dim3(64 * kPipeWavesWide), lds_p,
-                           st, a);
-      else
-        hipLaunchKernelGGL((step_kernel_pipe<false, kPipeWaves>), dim3(a.L.R), dim3(64 * kPipeWaves), lds_p, st, a);
-    }
+    const size_t lds_p = step_lds_bytes_pipe(a.L.maxL, a.L.W, a.nbuf, a.ucap, a.rcap);
+    if (a.C.phase_timers)
+      hipLaunchKernelGGL((step_kernel_pipe<true, kPipeWaves, kPipeEvictors>), dim3(a.L.R), dim3(64 * kPipeWaves), lds_p,
+                         st, a);
+    else
+      hipLaunchKernelGGL((step_kernel_pipe<false, kPipeWaves, kPipeEvictors>), dim3(a.L.R), dim3(64 * kPipeWaves),
+                         lds_p, st, a);
   } else if (rt && ba)
     hipLaunchKernelGGL((step_kernel<true, true, false>), dim3(a.L.R), dim3(64 * waves), lds, st, a);
   else if (rt)
@@ -1463,11 +1686,9 @@ hipError_t launch_stats_into(char* ws, const Layout& L, uint64_t w0, uint32_t n,
   return hipGetLastError();
 }
 
-static const void* const kStepKernels[9] = {
-    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWaves>),
-    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWaves>),
-    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWavesWide>),
-    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWavesWide>),
+static const void* const kStepKernels[7] = {
+    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWaves, kPipeEvictors>),
+    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWaves, kPipeEvictors>),
     reinterpret_cast<const void*>(step_kernel<false, false, false>),
     reinterpret_cast<const void*>(step_kernel<false, true, false>),
     reinterpret_cast<const void*>(step_kernel<true, false, false>),

@@ -49,7 +49,7 @@ constexpr uint32_t kMaxWavesPerBlock = KVR_MAX_WAVES;
 // Marks: positions [0, ma) are marked when mphase equals the worker phase;
 // one further interval per worker (WorkerHdr::rnode/rlo/rhi/rphase) holds
 // the marks left by a phase reset in the middle of an edge.
-struct NodeRec {
+struct alignas(8) NodeRec {
   int32_t parent;   // -1 for the root, -2 for a free slot
   uint32_t off;     // edge offset in the active arena; free slot: next free id
   int32_t len;      // edge length in tokens
@@ -161,9 +161,11 @@ struct StepArgs {
   int32_t* all_hits;
   uint32_t n;
   uint32_t ucap;  // candidate entries staged in LDS (0: U stays in global memory)
-  uint32_t rcap;  // draw words precomputed in LDS per insertion
+  uint32_t rcap;  // draw words precomputed in LDS: per insertion, or (pipelined kernel) the ring that insertions share
   uint64_t j0;
-  uint32_t pipe;  // 1: the pipelined step kernel (a separate evicting wave)
+  uint32_t pipe;  // 1: the pipelined step kernel (separate evicting waves)
+  uint32_t nbuf;  // its query buffers in LDS (2 or 3)
+  uint32_t check; // 1: the step kernel checks the batch before it changes anything
   uint32_t pad2;
 };
 

@@ -1,0 +1,785 @@
+// kvr_trail.h - per-wave tree logic of the pipelined step kernel (included by
+// kvr_device.hip and by the single-lane replay): matches taken a query ahead
+// along recorded trails, the two halves of an insertion (the load of the new
+// leaf on the routing wave; marks, leaf list and evictions on an evicting
+// wave), and completions and decay on state kept in LDS.
+//
+// Everything a wave decides on is wave-uniform and is read as such: a node
+// record, a worker's state and a job are each read with one load, a word per
+// lane, and taken to scalar registers with readlane.  One instance of the
+// matching code serves every wave (step_kernel_pipe calls it at one place):
+// the kernel's code has to fit the 64 KB instruction cache that two compute
+// units share.
+#ifndef KVR_TRAIL_H
+#define KVR_TRAIL_H
+
+#include "kvr_core.h"
+
+namespace kvr {
+
+// ---------------------------------------------------------------- a worker's tree state in LDS
+
+constexpr int kStWords = 16;  // the words of St that a header holds, padded
+
+__device__ __forceinline__ St load_st_lds(const uint32_t* p) {
+  uint32_t f[kStWords - 1];
+  if (KVR_WAVE == 1) {
+    for (int k = 0; k < kStWords - 1; ++k) f[k] = p[k];
+  } else {
+    const uint32_t v = p[lane_id() & (kStWords - 1)];
+#pragma unroll
+    for (int k = 0; k < kStWords - 1; ++k) f[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
+  }
+  St s;
+  s.phase = f[0];
+  s.cnt = f[1];
+  s.size = f[2];
+  s.hwm = f[3];
+  s.free_head = (int32_t)f[4];
+  s.nleaves = f[5];
+  s.nU = f[6];
+  s.U_valid = f[7];
+  s.rnode = (int32_t)f[8];
+  s.rlo = (int32_t)f[9];
+  s.rhi = (int32_t)f[10];
+  s.rphase = f[11];
+  s.arena_sel = f[12];
+  s.arena_top = f[13];
+  s.nnodes = f[14];
+  s.err = 0;
+  s.dbg_check = 0;
+  s.dbg_val[0] = s.dbg_val[1] = s.dbg_val[2] = 0;
+  return s;
+}
+
+__device__ __forceinline__ void store_st_lds(uint32_t* p, const St& s) {
+  if (lane_id() != 0) return;
+  p[0] = s.phase;
+  p[1] = s.cnt;
+  p[2] = s.size;
+  p[3] = s.hwm;
+  p[4] = (uint32_t)s.free_head;
+  p[5] = s.nleaves;
+  p[6] = s.nU;
+  p[7] = s.U_valid;
+  p[8] = (uint32_t)s.rnode;
+  p[9] = (uint32_t)s.rlo;
+  p[10] = (uint32_t)s.rhi;
+  p[11] = s.rphase;
+  p[12] = s.arena_sel;
+  p[13] = s.arena_top;
+  p[14] = s.nnodes;
+}
+
+// ---------------------------------------------------------------- root filters
+// Per worker a 256-bit Bloom filter (in LDS) of the first tokens of its
+// root's children, two bits per token, built when the kernel starts and
+// extended when an insertion adds a child to the root.  A clear bit proves
+// that no cached path starts with the token, so a match that starts at the
+// root is 0 without a memory access; a set bit (also one left by a child
+// evicted since) only means the tree is walked.  (512- and 1,024-bit filters
+// measured within 1% of this.)
+#ifndef KVR_ROOT_FILTER_LOG2_BITS
+#define KVR_ROOT_FILTER_LOG2_BITS 8
+#endif
+constexpr uint32_t kRootFilterBits = 1u << KVR_ROOT_FILTER_LOG2_BITS;
+constexpr uint32_t kRootFilterWords = kRootFilterBits / 32u;
+
+__device__ __forceinline__ uint32_t rf_bit1(int32_t t) {
+  return ((uint32_t)t * 0x9E3779B1u) >> (32 - KVR_ROOT_FILTER_LOG2_BITS);
+}
+__device__ __forceinline__ uint32_t rf_bit2(int32_t t) {
+  return ((uint32_t)t * 0x85EBCA6Bu + 0x632BE5ABu) >> (32 - KVR_ROOT_FILTER_LOG2_BITS);
+}
+
+__device__ __forceinline__ void rf_add(uint32_t* rf, int32_t t) {
+  atomicOr(&rf[rf_bit1(t) >> 5], 1u << (rf_bit1(t) & 31u));
+  atomicOr(&rf[rf_bit2(t) >> 5], 1u << (rf_bit2(t) & 31u));
+}
+
+__device__ __forceinline__ bool rf_may(const uint32_t* rf, int32_t t) {
+  return ((rf[rf_bit1(t) >> 5] >> (rf_bit1(t) & 31u)) & 1u) && ((rf[rf_bit2(t) >> 5] >> (rf_bit2(t) & 31u)) & 1u);
+}
+
+// ---------------------------------------------------------------- trails
+// The trail of a match: the nodes it entered, [0] = their number (kPathMax + 1
+// when there were more or they are unknown), then the nodes, then the depth
+// after each node's edge (entry e starts where entry e - 1 ends).  A worker
+// has one for the odd and one for the even queries, so that the next query
+// can be matched while the insertion of this one still needs its trail.
+constexpr int32_t kTrailWords = 2 * kPathMax + 1;
+
+__device__ __forceinline__ int32_t* trail_node(int32_t* t) { return t + 1; }
+__device__ __forceinline__ const int32_t* trail_node(const int32_t* t) { return t + 1; }
+__device__ __forceinline__ int32_t* trail_end(int32_t* t) { return t + 1 + kPathMax; }
+__device__ __forceinline__ const int32_t* trail_end(const int32_t* t) { return t + 1 + kPathMax; }
+
+__device__ __forceinline__ void trail_add(int32_t* t, int32_t& pc, int32_t node, int32_t end) {
+  if (pc < kPathMax && lane_id() == 0) {
+    trail_node(t)[pc] = node;
+    trail_end(t)[pc] = end;
+  }
+  pc = pc < kPathMax ? pc + 1 : kPathMax + 1;
+}
+
+// The last of n entries that starts above depth d > 0 (it holds depth d if
+// any does), with its node, start and end; -1 when n is 0.
+__device__ __forceinline__ int32_t trail_at(const int32_t* t, int32_t n, int32_t d, int32_t& node, int32_t& start,
+                                            int32_t& end) {
+  int32_t e = -1;
+  for (int32_t b = 0; b < n; b += KVR_WAVE) {
+    const int32_t k = b + lane_id();
+    const bool above = k < n && (k == 0 || trail_end(t)[k - 1] < d);
+    const uint64_t m = __ballot(above);
+    if (m) e = b + 63 - __clzll((long long)m);
+  }
+  if (e < 0) return -1;
+  node = uni(trail_node(t)[e]);
+  start = e > 0 ? uni(trail_end(t)[e - 1]) : 0;
+  end = uni(trail_end(t)[e]);
+  return e;
+}
+
+// ---------------------------------------------------------------- matching
+
+// Where a match ended: `pos` tokens into the edge of `node` (0: at the root).
+struct MatchEnd {
+  int32_t node, pos;
+};
+
+// h = length of the longest prefix of q[0, L) in a worker's tree, whose match
+// of the previous query is recorded in src (h_old = its h; ell = LCP of the
+// two queries).  Up to depth min(h_old, ell) both walks are the same.  If the
+// old match stopped first, the new one stops there; else the new one leaves
+// the old query's path at depth ell: inside an edge that the old match
+// followed further it stops, otherwise it goes on from there.  The new trail
+// is written to dst (another array).  `walked` is false when no node was read,
+// and me is then unset.  The tree may be one whose evictions are under way (see
+// match_stays): a node freed meanwhile holds the free list's next entry in
+// place of its offset, so offsets are checked against the semispace's size A.
+template <int kU>
+__device__ __forceinline__ int32_t match_ahead(const NodeRec* nodes, const int32_t* ar, const uint32_t* rf,
+                                               uint32_t A, const int32_t* q, int32_t L, int32_t h_old, int32_t ell,
+                                               const int32_t* src, int32_t* dst, bool& walked, MatchEnd& me) {
+  const int32_t have = uni(src[0]);
+  int32_t x = 0, off = 0, d = 0, pc = 0;
+  bool walk = true;
+  if (ell > 0 && have <= kPathMax) {
+    if (h_old < ell) {
+      pc = have;
+      d = h_old;
+      walk = false;
+    } else {
+      int32_t nx = 0, st = 0, en = 0;
+      const int32_t e = trail_at(src, have, ell, nx, st, en);
+      if (e >= 0 && en >= ell) {  // (always, for a consistent record)
+        pc = e + 1;
+        d = ell;
+        if (ell == L || (ell < en && h_old > ell)) {
+          walk = false;
+        } else {
+          x = nx;
+          off = ell - st;
+        }
+      }
+    }
+  }
+  if (walk && x == 0 && !rf_may(rf, q[0])) walk = false;
+  for (int32_t k = lane_id(); k < pc; k += KVR_WAVE) {
+    const int32_t n = trail_node(src)[k], en = trail_end(src)[k];
+    trail_node(dst)[k] = n;
+    trail_end(dst)[k] = en;
+  }
+  walked = walk;
+  if (walk) {
+    NodeRec nx = load_node(nodes, x);
+    while (d < L) {
+      if (off < nx.len) {  // the rest of this edge
+        const int32_t rest = nx.len - off;
+        const int32_t n = rest < L - d ? rest : L - d;
+        const int32_t k = same_words<kU>(ar, nx.off + (uint32_t)off, q, d, n);
+        d += k;
+        off += k;
+        if (k < rest) break;
+        continue;
+      }
+      const int32_t c = child_find(ar, nx, uni(q[d]));
+      if (c < 0) break;
+      x = c;
+      off = 0;
+      nx = load_node(nodes, c);
+      if (nx.len <= 0 || (uint64_t)nx.off + (uint32_t)nx.len > A) break;  // freed meanwhile
+      trail_add(dst, pc, c, d + nx.len);
+      d += 1;  // the child entry holds the edge's first token
+      off = 1;
+    }
+    me.node = x;
+    me.pos = off;
+  }
+  if (lane_id() == 0) dst[0] = pc;
+  return d;
+}
+
+// ---------------------------------------------------------------- insertion, first half
+
+// What an insertion leaves to its second half (LDS, one word per lane).
+struct PipeJob {
+  uint32_t k;       // query index in the batch
+  uint32_t worker;
+  int32_t h, L;     // cached length and length of the path
+  int32_t l, a;     // the new leaf holding q[h, L) and the node it hangs from (h < L)
+  int32_t tok;      // q[h]
+  uint32_t nfree;   // free token slots before the load
+  uint32_t nev;     // evictions the load needs
+  uint32_t rn, r0;  // its draw words: how many, and where in the ring
+  uint32_t replace; // a was a leaf
+  uint32_t marked;  // the cached part is marked already
+  uint32_t calm;    // no new phase can start in this insertion (match_stays)
+  uint32_t phase;   // the phase before it
+  uint32_t pad;
+};
+constexpr int kJobWords = sizeof(PipeJob) / 4;
+static_assert(kJobWords == 16, "a job is one word per lane of a row");
+
+__device__ __forceinline__ PipeJob load_job(const PipeJob* p) {
+  if (KVR_WAVE == 1) return *p;
+  const uint32_t v = reinterpret_cast<const uint32_t*>(p)[lane_id() & (kJobWords - 1)];
+  PipeJob j;
+  uint32_t f[15];
+#pragma unroll
+  for (int k = 0; k < 15; ++k) f[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
+  j.k = f[0];
+  j.worker = f[1];
+  j.h = (int32_t)f[2];
+  j.L = (int32_t)f[3];
+  j.l = (int32_t)f[4];
+  j.a = (int32_t)f[5];
+  j.tok = (int32_t)f[6];
+  j.nfree = f[7];
+  j.nev = f[8];
+  j.rn = f[9];
+  j.r0 = f[10];
+  j.replace = f[11];
+  j.marked = f[12];
+  j.calm = f[13];
+  j.phase = f[14];
+  return j;
+}
+
+// A node id, its free list's next entry read by the caller (fh, fh_next).
+__device__ __forceinline__ int32_t take_node(const Ptrs& P, St& s, int32_t fh, uint32_t fh_next) {
+  if (fh >= 0 && s.free_head == fh) {
+    s.free_head = (int32_t)fh_next;
+    s.nnodes += 1;
+    return fh;
+  }
+  return node_alloc(P, s);
+}
+
+// Prefix marks of node c: phase and length in one store (a match may read
+// them meanwhile).
+__device__ __forceinline__ void put_marks(const Ptrs& P, int32_t c, uint32_t phase, int32_t ma) {
+  if (lane_id() == 0)
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(P.nodes + c) + offsetof(NodeRec, mphase)), ((uint64_t)(uint32_t)ma << 32) | phase,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One edge of Algorithm 1's marking walk: the first cov tokens of node c's
+// edge (record nc) join the marking set, with the reset to the current token
+// when it would exceed B; a candidate whose leaf token is marked leaves U.
+// `leaf`: c is (or, before this insertion, was) a leaf.
+__device__ __forceinline__ void mark_edge(const Ptrs& P, St& s, uint32_t B, int32_t c, const NodeRec& nc, int32_t cov,
+                                          bool leaf) {
+  const bool was_cand = leaf && !is_marked(s, nc, c, nc.len - 1);
+  int32_t ma = (nc.mphase == s.phase) ? nc.ma : 0;
+  bool rv = (s.rphase == s.phase) && (s.rnode == c);
+  const int32_t rlo = s.rlo, rhi = s.rhi;
+  if (rv && rlo <= ma) {  // the reset interval touches the prefix: merge
+    ma = ma > rhi ? ma : rhi;
+    rv = false;
+    s.rphase = 0;
+  }
+  const int32_t m1 = ma < cov ? ma : cov;
+  int32_t m2 = 0;
+  if (rv) {
+    const int32_t e = rhi < cov ? rhi : cov;
+    m2 = e - rlo > 0 ? e - rlo : 0;
+  }
+  const int32_t newly = cov - m1 - m2;
+  if (s.cnt + (uint32_t)newly <= B) {
+    s.cnt += (uint32_t)newly;
+    int32_t nma = ma > cov ? ma : cov;
+    if (rv && rlo <= nma) {
+      nma = nma > rhi ? nma : rhi;
+      s.rphase = 0;
+    }
+    put_marks(P, c, s.phase, nma);
+  } else {
+    // |T| reaches B+1 at the `need`-th newly marked position of this edge
+    const int32_t need = (int32_t)(B + 1u - s.cnt);
+    int32_t rp;
+    if (!rv) {
+      rp = ma + need - 1;
+    } else {
+      const int32_t e1 = rlo < cov ? rlo : cov;
+      const int32_t s1 = e1 - ma > 0 ? e1 - ma : 0;
+      rp = need <= s1 ? ma + need - 1 : rhi + (need - s1) - 1;
+    }
+    s.phase += 1;
+    s.U_valid = 0;
+    s.cnt = (uint32_t)(cov - rp);
+    if (rp == 0) {
+      put_marks(P, c, s.phase, cov);
+    } else {
+      s.rnode = c;
+      s.rlo = rp;
+      s.rhi = cov;
+      s.rphase = s.phase;
+    }
+  }
+  if (was_cand && s.U_valid && cov == nc.len) {
+    const int32_t pos = arr_find(P.U, s.nU, c);
+    if (pos >= 0) {
+      arr_erase(P.U, s.nU, (uint32_t)pos);
+      s.nU -= 1;
+    }
+  }
+}
+
+// Split node x (record nx, read in semispace sel_read) at edge offset k: a new
+// head node takes positions [0, k) and x keeps the rest below it, so every
+// leaf keeps its id.  The head's child array, with room for the leaf that
+// the insertion adds, and its record are returned; the head's id, or -1.
+__device__ __forceinline__ int32_t split_for_leaf(const Ptrs& P, St& s, int32_t x, NodeRec nx, int32_t k, int32_t fh,
+                                                  uint32_t fh_next, NodeRec& nh) {
+  const uint32_t sel_read = s.arena_sel;
+  uint32_t coff;
+  if (!arena_alloc(P, s, 4u, true, coff)) return -1;
+  const int32_t hd = take_node(P, s, fh, fh_next);
+  if (hd < 0) return -1;
+  if (s.arena_sel != sel_read) nx = load_node(P.nodes, x);  // a collection has moved it
+  int32_t* ar = arena_of(P, s.arena_sel);
+  const int32_t tail_tok = uni(ar[nx.off + (uint32_t)k]);
+  const NodeRec np = load_node(P.nodes, nx.parent);
+  nh.parent = nx.parent;
+  nh.off = nx.off;
+  nh.len = k;
+  nh.nchild = 1;
+  nh.coff = coff;
+  nh.ccap = 2;
+  nh.mphase = nx.mphase;
+  nh.ma = nx.ma < k ? nx.ma : k;
+  uint32_t tphase = nx.mphase;
+  int32_t tma = nx.ma - k > 0 ? nx.ma - k : 0;
+  if (s.rnode == x) {
+    if (s.rphase != s.phase) {
+      s.rphase = 0;
+    } else if (s.rhi <= k) {
+      s.rnode = hd;
+    } else if (s.rlo >= k) {
+      s.rlo -= k;
+      s.rhi -= k;
+    } else {
+      const int32_t t = s.rhi - k;
+      s.rnode = hd;
+      s.rhi = k;
+      if (tphase == s.phase) {
+        tma = tma > t ? tma : t;
+      } else {
+        tphase = s.phase;
+        tma = t;
+      }
+    }
+  }
+  const int32_t pos = child_slot(ar, np, x);
+  if (pos < 0) {
+    KVR_FAIL_CHECK(s, 3, x, nx.parent, hd);
+    return -1;
+  }
+  if (lane_id() == 0) {
+    ar[coff] = tail_tok;
+    ar[coff + 1] = x;
+    ar[np.coff + 2 * pos + 1] = hd;
+    P.nodes[hd] = nh;
+    P.nodes[x].parent = hd;
+    P.nodes[x].off = nx.off + (uint32_t)k;
+    P.nodes[x].len = nx.len - k;
+    P.nodes[x].mphase = tphase;
+    P.nodes[x].ma = tma;
+  }
+  return hd;
+}
+
+// First half of the RLT insertion of q[0, L) (in LDS) into the worker's cache
+// (h = LCP(q, cache), t = the trail of that match): what the matches of later
+// queries need, the split of the edge the match ends in and the load of
+// q[h, L) as one new leaf.  t then holds q's trail in the updated cache.  The
+// marks, the leaf list and the evictions are left to the second half, except
+// that a path too deep for a trail is marked here.  Fills job's fields from h
+// on but for the draw words; split = the node whose edge was split (its head is
+// job.a), or 0.  KVR_DEV_* bits (0: done).
+__device__ __forceinline__ uint32_t load_leaf(const Ptrs& P, St& s, uint32_t B, uint32_t maxL, const int32_t* q,
+                                              int32_t L, int32_t h, int32_t* t, PipeJob& job, int32_t& split) {
+  int32_t have = uni(t[0]);
+  int32_t last = 0, start = 0, end = 0, e = -1;
+  if (h > 0 && have <= kPathMax) {
+    e = trail_at(t, have, h, last, start, end);
+    if (e < 0 || end < h || last <= 0 || (uint32_t)last >= s.hwm) {
+      KVR_FAIL_CHECK(s, 1, e, h, last);
+      return s.err;
+    }
+  }
+  job.h = h;
+  job.L = L;
+  job.l = job.a = job.tok = 0;
+  split = 0;
+  job.replace = job.marked = 0;
+  job.nfree = B - s.size;
+  const uint32_t nload = (uint32_t)(L - h);
+  job.nev = nload > job.nfree ? nload - job.nfree : 0u;
+  if (h > 0 && (have > kPathMax || (e + 1 == kPathMax && h < L))) {
+    // no trail, or none after this insertion: walk and mark by child lookups
+    const int32_t* ar = arena_of(P, s.arena_sel);
+    int32_t d = 0;
+    NodeRec nx = load_node(P.nodes, 0);
+    last = 0;
+    while (d < h) {
+      const int32_t c = child_find(ar, nx, uni(q[d]));
+      if (c <= 0 || (uint32_t)c >= s.hwm) {
+        KVR_FAIL_CHECK(s, 1, last, d, h);
+        return s.err;
+      }
+      nx = load_node(P.nodes, c);
+      const int32_t cov = nx.len < h - d ? nx.len : h - d;
+      if (cov <= 0) {
+        KVR_FAIL_CHECK(s, 2, c, nx.len, d);
+        return s.err;
+      }
+      mark_edge(P, s, B, c, nx, cov, nx.nchild == 0);
+      last = c;
+      start = d;
+      d += cov;
+    }
+    wave_mem_sync();  // the marks above are read again below
+    have = kPathMax + 1;
+    job.marked = 1;
+  }
+  const uint32_t join = job.marked ? nload : (uint32_t)L;  // tokens that may join the marking set
+  job.phase = s.phase;
+  job.calm = (uint64_t)s.cnt + join <= B && (uint64_t)s.size >= (uint64_t)s.cnt + (join - nload) + job.nev + maxL;
+  int32_t pc = have <= kPathMax ? e + 1 : kPathMax + 1;
+  if (h < L) {
+    const NodeRec lr = load_node(P.nodes, last);
+    // the free list's next entry, read before the stores below
+    const int32_t fh = s.free_head;
+    uint32_t fh_next = 0;
+    if (fh >= 0) fh_next = uni(P.nodes[fh].off);
+    const int32_t cov = h - start;
+    int32_t a = last, fl = fh;
+    uint32_t sel = s.arena_sel;
+    int32_t known[3] = {lr.nchild, lr.ccap, (int32_t)lr.coff};
+    if (last != 0 && cov < lr.len) {
+      NodeRec nh;
+      a = split_for_leaf(P, s, last, lr, cov, fh, fh_next, nh);
+      if (a < 0) return s.err ? s.err : (uint32_t)KVR_DEV_INTERNAL;
+      split = last;
+      fl = -1;
+      sel = s.arena_sel;
+      known[0] = nh.nchild;
+      known[1] = nh.ccap;
+      known[2] = (int32_t)nh.coff;
+      wave_mem_sync();
+      if (pc <= kPathMax && lane_id() == 0) trail_node(t)[pc - 1] = a;
+    }
+    // the walked part ends here (its last entry may have ended deeper: a split
+    // edge, or one trimmed since)
+    if (pc > 0 && pc <= kPathMax && lane_id() == 0) trail_end(t)[pc - 1] = h;
+    job.replace = a != 0 && known[0] == 0;
+    uint32_t eoff;
+    if (!place_edge(P, s, nload, (uint32_t)h, eoff)) return s.err;
+    // no fence: nothing reads the new edge's words before the fence that
+    // ends this half (a collection fences first)
+    copy_words(arena_of(P, s.arena_sel), eoff, q, h, (int32_t)nload);
+    const int32_t l = take_node(P, s, fl, fh_next);
+    if (l < 0) return s.err;
+    if (lane_id() == 0) {
+      NodeRec nl;
+      nl.parent = a;
+      nl.off = eoff;
+      nl.len = (int32_t)nload;
+      nl.nchild = 0;
+      nl.coff = 0;
+      nl.ccap = 0;
+      nl.mphase = 0;
+      nl.ma = 0;
+      P.nodes[l] = nl;
+    }
+    job.tok = uni(q[h]);
+    if (!child_add(P, s, a, job.tok, l, known, sel, false)) return s.err;
+    job.l = l;
+    job.a = a;
+    if (pc <= kPathMax) trail_add(t, pc, l, L);
+  }
+  if (lane_id() == 0) t[0] = pc;
+  wave_mem_sync();
+  return 0;
+}
+
+// ---------------------------------------------------------------- insertion, second half
+
+// The marking walk over the cached part of the path, along its trail in the
+// updated tree (the records of all its nodes loaded at once, one lane each).
+__device__ __forceinline__ void mark_cached(const Ptrs& P, St& s, uint32_t B, const PipeJob& job, const int32_t* t) {
+  const int32_t pc = uni(t[0]);
+  NodeRec pre;
+  pre.parent = pre.len = pre.nchild = pre.ccap = pre.ma = 0;
+  pre.off = pre.coff = pre.mphase = 0;
+  if (KVR_WAVE >= kPathMax && lane_id() < pc) pre = P.nodes[trail_node(t)[lane_id()]];
+  int32_t d = 0;
+  for (int32_t e = 0; e < pc && d < job.h; ++e) {
+    const int32_t c = uni(trail_node(t)[e]);
+    const NodeRec nc = KVR_WAVE >= kPathMax ? node_from_lane(pre, e) : P.nodes[c];
+    const int32_t cov = nc.len < job.h - d ? nc.len : job.h - d;
+    if (c <= 0 || (uint32_t)c >= s.hwm || cov <= 0) {
+      KVR_FAIL_CHECK(s, 2, c, nc.len, d);
+      return;
+    }
+    mark_edge(P, s, B, c, nc, cov, nc.nchild == 0 || (job.replace && c == job.a));
+    d += cov;
+  }
+  if (d < job.h) KVR_FAIL_CHECK(s, 1, pc, d, job.h);
+  wave_mem_sync();  // the marks above are read again below
+}
+
+// Is a match of query m on the worker of an insertion (of query job.k < m),
+// taken after that insertion's load and before its evictions end, the match
+// that the evictions leave?  They only remove tokens, so it never grows; it is
+// as long as it was while its last token stays:
+//   * a token of the inserted path stays (that path's leaf is no candidate,
+//     and an eviction takes leaf tokens only): h <= on_path, a lower bound of the
+//     LCP of the two queries;
+//   * a token of the last match taken here stays (that one was final), so a
+//     match that read no node is final;
+//   * a token marked in the current phase stays while no new phase starts
+//     (job.calm): |T| stays at most B, as at most L tokens join, and U never
+//     runs empty, since of the |S| - |T| unmarked tokens only those of one path,
+//     left unmarked above the token that started a phase, can stay internal.
+// The evictions may run meanwhile.  What they change on the way of a match
+// that this accepts is the child arrays of its nodes, where a removed entry's
+// slot takes a copy of the last entry before the count drops, so a child that
+// stays is always found.
+__device__ __forceinline__ bool match_stays(const NodeRec* nodes, const PipeJob& job, int32_t h, int32_t on_path,
+                                            bool walked, const MatchEnd& me) {
+  if (job.nev == 0 || !walked || h <= on_path || h == 0) return true;
+  if (!job.calm || me.node == 0) return false;
+  // the phase and length of the node's prefix marks, written together
+  const uint64_t m = __hip_atomic_load(reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(nodes + me.node) + offsetof(NodeRec, mphase)), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+  return uni((uint32_t)m) == job.phase && uni((int32_t)(m >> 32)) >= me.pos;
+}
+
+// The match of the next query on the worker of an insertion, after its load,
+// from the match taken before it (h_pre and its trail in tn; tk = the trail of
+// the inserted query, ell = LCP of the two queries).  The load adds the
+// inserted path's prefixes only, so h = max(h_pre, ell) and no node is read:
+// where the next query leaves the inserted path, that path's trail up to
+// there is its trail; else its own stands, with the head of the split edge
+// (which both pass, as then ell is the depth of the split) in front of it.
+// `stays` as match_stays says.
+__device__ __forceinline__ int32_t match_after_load(const NodeRec* nodes, const PipeJob& job, int32_t split,
+                                                    int32_t h_pre, int32_t ell, const int32_t* tk, int32_t* tn,
+                                                    bool& stays) {
+  stays = true;
+  if (h_pre <= ell) {
+    const int32_t have = uni(tk[0]);
+    int32_t pc = have;
+    if (have <= kPathMax) {
+      int32_t x, st, en;
+      pc = ell > 0 ? trail_at(tk, have, ell, x, st, en) + 1 : 0;
+      for (int32_t k = lane_id(); k < pc; k += KVR_WAVE) {
+        const int32_t n = trail_node(tk)[k], e = trail_end(tk)[k];
+        trail_node(tn)[k] = n;
+        trail_end(tn)[k] = e;
+      }
+    }
+    if (lane_id() == 0) tn[0] = pc;
+    return ell;
+  }
+  int32_t have = uni(tn[0]);
+  MatchEnd me{0, 0};
+  if (have > 0 && have <= kPathMax) {
+    if (split > 0) {
+      int32_t at = -1;
+      for (int32_t k = 0; k < have; k += KVR_WAVE) {
+        const uint64_t m = __ballot(k + lane_id() < have && trail_node(tn)[k + lane_id()] == split);
+        if (m) at = k + first_lane(m);
+      }
+      if (at >= 0 && have == kPathMax) {
+        have = kPathMax + 1;
+      } else if (at >= 0) {
+        // entries from `at` on move up by one (from the top, a word per lane)
+        for (int32_t b = have - 1; b >= at; b -= KVR_WAVE) {
+          const int32_t k = b - lane_id();
+          int32_t n = 0, e = 0;
+          if (k >= at) {
+            n = trail_node(tn)[k];
+            e = trail_end(tn)[k];
+          }
+          __builtin_amdgcn_wave_barrier();
+          if (k >= at) {
+            trail_node(tn)[k + 1] = n;
+            trail_end(tn)[k + 1] = e;
+          }
+        }
+        if (lane_id() == 0) {
+          trail_node(tn)[at] = job.a;
+          trail_end(tn)[at] = job.h;
+        }
+        have += 1;
+      }
+      if (lane_id() == 0) tn[0] = have;
+    }
+    if (have <= kPathMax) {
+      me.node = uni(trail_node(tn)[have - 1]);
+      me.pos = h_pre - (have > 1 ? uni(trail_end(tn)[have - 2]) : 0);
+    }
+  }
+  stays = match_stays(nodes, job, h_pre, ell, true, me);
+  return h_pre;
+}
+
+// Rank in the leaf list of the leaf that an insertion added (its entry still
+// missing from the list): the place of its parent when that was a leaf, else
+// next to its neighbours among the parent's children.  -1: an inconsistency.
+__device__ __forceinline__ int32_t rank_of_leaf(const Ptrs& P, uint32_t hwm, uint32_t nleaves, const int32_t* ar,
+                                                const PipeJob& job) {
+  int32_t x = job.a;
+  bool after = false;
+  if (!job.replace) {
+    const NodeRec na = load_node(P.nodes, job.a);
+    x = uni(child_neighbor(ar, na, job.tok, true));
+    after = x >= 0;
+    if (!after) x = uni(child_neighbor(ar, na, job.tok, false));
+    if (x < 0) return 0;  // the only leaf
+    // down to the last (first) leaf of that child's subtree
+    for (uint32_t steps = 0; steps <= hwm; ++steps) {
+      if (x <= 0 || (uint32_t)x >= hwm) return -1;
+      const NodeRec nx = load_node(P.nodes, x);
+      if (nx.nchild == 0) break;
+      x = uni(after ? child_neighbor(ar, nx, (int64_t)1 << 32, true) : child_neighbor(ar, nx, -1, false));
+    }
+  }
+  const int32_t pos = arr_find(P.leaf, nleaves, x);
+  return pos < 0 ? -1 : (after ? pos + 1 : pos);
+}
+
+// ---------------------------------------------------------------- completions and decay
+
+// The LBGR state of the replica's workers in LDS, one lane per worker.
+struct LbgrLds {
+  double* P;          // load estimate
+  double* theta;      // [4][W] residual model
+  int64_t* Wb;        // observed-latency backlog
+  int64_t* done_at;   // completion time of the oldest pending record (INT64_MAX: none)
+  uint32_t* head;     // pending ring
+  uint32_t* count;
+  uint32_t* size;     // |S| once the insertions routed so far are done
+  uint32_t W;
+};
+constexpr uint32_t kLbgrBytes = 8 * 7 + 4 * 3;  // per worker
+
+constexpr int64_t kNever = 0x7fffffffffffffffll;
+
+// Completions with t_done <= t of worker w (FIFO), then decay to t and drain
+// the observed-latency backlog.  tick, tick_prev = t / dt and tprev / dt.
+__device__ __forceinline__ void decay_lds(const Consts& C, const LbgrLds& b, uint32_t w, WorkerHdr* hdr,
+                                          const PendRec* pend, uint32_t PC, int64_t t, int64_t tprev, int64_t tick,
+                                          int64_t tick_prev) {
+  double Pl = b.P[w];
+  int64_t at = b.done_at[w], tl = tick_prev;
+  if (at <= t) {
+    uint32_t head = b.head[w], cnt = b.count[w];
+    double theta[4];
+    for (int a = 0; a < 4; ++a) theta[a] = b.theta[a * b.W + w];
+    uint64_t done = 0;
+    do {
+      const uint32_t next = head + 1 == PC ? 0u : head + 1;
+      const PendRec pr = pend[head];
+      const int64_t at2 = pend[next].t_done;
+      const int64_t td = pr.t_done / C.dt_us;
+      Pl = Pl * pow_int(C.rho, (uint64_t)(td - tl));
+      tl = td;
+      const double rem = pr.chat * pow_int(C.rho, (uint64_t)(td - pr.t_route / C.dt_us));
+      const double np = Pl - rem;
+      Pl = np > 0.0 ? np : 0.0;
+      double phi[4];
+      phi[0] = (double)pr.h * 0.001;
+      phi[1] = (double)(pr.L - pr.h) * 0.001;
+      phi[2] = pr.x3;
+      phi[3] = 1.0;
+      double res = theta[0] * phi[0];
+      res = res + theta[1] * phi[1];
+      res = res + theta[2] * phi[2];
+      res = res + theta[3] * phi[3];
+      const double ehat_now = pr.base + res;
+      const double e_obs = (double)(pr.t_done - pr.t_route) * 1e-6;
+      online_update(C, theta, hdr->Pm, phi, e_obs - ehat_now);
+      head = next;
+      cnt -= 1;
+      done += 1;
+      at = cnt > 0 ? at2 : kNever;
+    } while (at <= t);
+    for (int a = 0; a < 4; ++a) b.theta[a * b.W + w] = theta[a];
+    b.head[w] = head;
+    b.count[w] = cnt;
+    b.done_at[w] = at;
+    __hip_atomic_fetch_add(&hdr->completions, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  b.P[w] = Pl * pow_int(C.rho, (uint64_t)(tick - tl));
+  const int64_t nb = b.Wb[w] - (t - tprev);
+  b.Wb[w] = nb > 0 ? nb : 0;
+}
+
+// commit_route on that state: the routed worker's lane adds the estimated
+// service time to the load estimate, advances the observed-latency queue and
+// queues the completion record.  The counters go to the header as atomics
+// whose results nothing waits for.  KVR_DEV_* bits.
+__device__ __forceinline__ uint32_t commit_lds(const Consts& C, const Ptrs& P, const LbgrLds& b, uint32_t w,
+                                               const RouteView& v, double chat, int32_t h, int32_t L, int64_t t,
+                                               int32_t olen) {
+  WorkerHdr* hdr = P.hdr;
+  b.P[w] = v.P + chat;
+  const int64_t cost = C.true_cached_us * h + C.true_miss_us * (int64_t)(L - h) + C.true_out_us * (int64_t)olen;
+  const int64_t e_us = v.Wb + cost;
+  b.Wb[w] = e_us;
+  uint32_t err = 0;
+  if (v.pend_count >= P.PC) {
+    err |= KVR_DEV_PENDING_FULL;
+  } else {
+    uint32_t slot = v.pend_head + v.pend_count;
+    if (slot >= P.PC) slot -= P.PC;
+    PendRec pr;
+    pr.t_route = t;
+    pr.t_done = t + e_us;
+    pr.chat = chat;
+    pr.base = chat + v.P;
+    pr.x3 = v.P;
+    pr.h = h;
+    pr.L = L;
+    P.pend[slot] = pr;
+    b.count[w] = v.pend_count + 1u;
+    if (v.pend_count == 0u) b.done_at[w] = pr.t_done;
+    __hip_atomic_fetch_max(&hdr->pending_max, (uint64_t)(v.pend_count + 1u), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __hip_atomic_fetch_add(&hdr->routed, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_fetch_add(&hdr->prompt_tokens, (uint64_t)L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_fetch_add(&hdr->hit_tokens, (uint64_t)h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_fetch_add(&hdr->lat_sum_us, (uint64_t)e_us, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __hip_atomic_fetch_max(&hdr->lat_max_us, (uint64_t)e_us, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return err;
+}
+
+}  // namespace kvr
+
+#endif  // KVR_TRAIL_H
