@@ -174,29 +174,30 @@ typedef struct kvr_worker_stats {
 } kvr_worker_stats;
 
 /* Parts of a step timed with phase_timers = 1 (kvr_replica_stats.phase_ticks):
- * ticks of the routing wave (0-8) and, when a separate evicting wave runs
- * the evictions of each insertion while the routing wave goes on to the
- * next query, of the evicting wave (9-11, 17) and of the helper waves,
- * summed over them (12-16). */
+ * ticks of the routing wave (0-8) and, when separate evicting waves run the
+ * insertions while the routing wave goes on to the next queries, of the evicting
+ * waves, summed over them (9-11, 17), and of the helper waves, summed over them
+ * (12-16).  Parts 2, 4 and 5 are then the evicting waves' and stay 0. */
 enum {
   KVR_PHASE_ROUTE = 0,        /* scores, argmin and commit (Algorithm 2 routing thread) */
-  KVR_PHASE_STAGE_WAIT = 1,   /* waiting for the next query's staging                  */
+  KVR_PHASE_STAGE_WAIT = 1,   /* waiting for the next query's staging, or its decay    */
   KVR_PHASE_MARK = 2,         /* RLT insertion: marking walk over the cached part      */
-  KVR_PHASE_LOAD = 3,         /* split, new leaf's rank, edge copy, tree and list edits */
+  KVR_PHASE_LOAD = 3,         /* split, new leaf's rank, edge copy, tree and list edits;
+                                 with evicting waves: planning the insertion           */
   KVR_PHASE_EVICT = 4,        /* evictions of the loaded tokens (Algorithm 1)          */
   KVR_PHASE_FINISH = 5,       /* marks of the loaded tokens, cache header              */
-  KVR_PHASE_MATCH = 6,        /* h of the next query (routed worker), any left by helpers */
+  KVR_PHASE_MATCH = 6,        /* h of a query on any worker left by the helpers        */
   KVR_PHASE_JOIN = 7,         /* waiting for the other workers' h of the next query    */
-  KVR_PHASE_EVICTOR_WAIT = 8, /* waiting for the evicting wave                         */
-  KVR_PHASE_E_EVICT = 9,      /* evicting wave: evictions                              */
-  KVR_PHASE_E_FINISH = 10,    /* evicting wave: marks of the loaded tokens, header     */
-  KVR_PHASE_E_IDLE = 11,      /* evicting wave: waiting for the next insertion         */
-  KVR_PHASE_H_STAGE = 12,     /* helper waves (summed): staging the next query         */
-  KVR_PHASE_H_WAIT = 13,      /* helper waves: waiting for the routing wave            */
+  KVR_PHASE_EVICTOR_WAIT = 8, /* waiting for an evicting wave                          */
+  KVR_PHASE_E_EVICT = 9,      /* evicting waves: evictions                             */
+  KVR_PHASE_E_FINISH = 10,    /* evicting waves: marks, cache state                    */
+  KVR_PHASE_E_IDLE = 11,      /* evicting waves: waiting for the next insertion        */
+  KVR_PHASE_H_STAGE = 12,     /* helper waves (summed): staging queries                */
+  KVR_PHASE_H_WAIT = 13,      /* helper waves: nothing due                             */
   KVR_PHASE_H_DRAW = 14,      /* helper waves: draw words (Philox4x64-10)              */
   KVR_PHASE_H_OTHER = 15,     /* helper waves: completions, decay, new leaf's rank     */
-  KVR_PHASE_H_MATCH = 16,     /* helper waves: h of the next query on the other workers */
-  KVR_PHASE_E_MATCH = 17,     /* evicting wave: the routed worker's h of the next query */
+  KVR_PHASE_H_MATCH = 16,     /* helper waves: h of the next queries                   */
+  KVR_PHASE_E_MATCH = 17,     /* evicting waves: the load of the new leaf              */
   KVR_PHASES = 18
 };
 

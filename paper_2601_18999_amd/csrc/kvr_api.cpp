@@ -24,7 +24,6 @@ hipError_t step_static_lds(size_t* bytes);
 size_t step_lds_bytes(uint32_t maxL, uint32_t W, uint32_t ucap, uint32_t rcap, uint32_t path_sets);
 size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t nbuf, uint32_t ucap, uint32_t rcap);
 uint32_t step_pipe_evictors();
-uint32_t step_pipe_jobs();
 hipError_t noalloc_scratch(int device, void** ptr, size_t* bytes);
 hipError_t launch_stats_into(char* ws, const Layout& L, uint64_t w0, uint32_t n, uint64_t* fifo, uint64_t fifo_words,
                              kvr_worker_stats* out, hipStream_t st);
@@ -49,6 +48,11 @@ struct kvr_ctx {
 };
 
 namespace {
+
+#ifndef KVR_MAX_BUF
+#define KVR_MAX_BUF 4
+#endif
+constexpr uint32_t kMaxBuf = KVR_MAX_BUF;  // query buffers of the pipelined step kernel
 
 thread_local std::string g_err;
 
@@ -248,12 +252,13 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
     // 512 staged candidates per evicting wave first (the candidate lists are
     // short on these workloads), then a third query buffer where the draw
     // words of two whole insertions still fit beside it, then the draw words
-    // of as many insertions as can be under way, then more candidates
+    // of one insertion more than are evicted at once, then more candidates
     const size_t ufirst = ne * 512u * 16u;
-    if (kvr::step_lds_bytes_pipe(L.maxL, L.W, 3, 512, 2u * L.maxL) <= lds_room) nbuf = 3;
+    for (uint32_t b = 3; b <= kMaxBuf; ++b)
+      if (kvr::step_lds_bytes_pipe(L.maxL, L.W, b, 512, 2u * L.maxL) <= lds_room) nbuf = b;
     size_t left = lds_room - kvr::step_lds_bytes_pipe(L.maxL, L.W, nbuf, 0, 0);
     rcap_p = (left > ufirst ? left - ufirst : 0u) / 4u;
-    const size_t most = (size_t)(kvr::step_pipe_jobs() - 1u) * L.maxL;
+    const size_t most = (ne + 1u) * L.maxL;
     if (rcap_p > most) rcap_p = most;
     left -= rcap_p * 4u;
     ucap_p = left / (ne * 16u);

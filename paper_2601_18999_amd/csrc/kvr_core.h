@@ -623,9 +623,10 @@ __device__ __forceinline__ bool collect(const Ptrs& P, St& s) {
       collect_arena(P.nodes, arena_of(P, s.arena_sel), arena_of(P, s.arena_sel ^ 1u), s.hwm, P.A,
                     P.stamp0 ? P.stamp0 + (size_t)s.arena_sel * P.A : nullptr,
                     P.stamp0 ? P.stamp0 + (size_t)(s.arena_sel ^ 1u) * P.A : nullptr);
-  if (top == ~0ull) return false;
+  const uint32_t top_lo = uni((uint32_t)top);  // (an out-of-line call's result is wave-uniform, but not known to be)
+  if (uni((uint32_t)(top >> 32)) != 0u) return false;
   s.arena_sel ^= 1u;
-  s.arena_top = (uint32_t)top;
+  s.arena_top = top_lo;
   hdr_count(&P.hdr->gc_runs, 1u);
   return true;
 }

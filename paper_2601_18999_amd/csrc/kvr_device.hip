@@ -77,8 +77,10 @@ __device__ __forceinline__ void count_matched(const Ptrs& P, int32_t h, int32_t*
 constexpr uint32_t kQueryPad = 4;
 __host__ __device__ constexpr uint32_t query_words(uint32_t maxL) { return ((maxL + 3u) & ~3u) + 2u * kQueryPad; }
 
-// The buffer of query k (nbuf = 2 or 3).
-__device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) { return nbuf == 2u ? k & 1u : k % 3u; }
+// The buffer of query k (nbuf = 2, 3 or 4).
+__device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) {
+  return nbuf == 3u ? k % 3u : k & (nbuf - 1u);
+}
 
 // Stage q_next[0, Ln) (threads t0, t0 + stride, ...) and fold each thread's
 // first position where it differs from q_cur into *ell (LDS minimum), so
@@ -144,43 +146,34 @@ __device__ __forceinline__ uint32_t wave_argmin_u32(uint32_t v, uint32_t W) {
   return (uint32_t)(wave_min_u64(key) & 0xffffffffull);
 }
 
+// The baseline routers of Sec. 5 (out of line: the learned router's step is
+// the one that has to be short).  One lane per worker.
+__device__ __noinline__ uint32_t route_baseline(int32_t router, uint64_t jg, uint64_t seed, uint32_t r, uint32_t W,
+                                                uint32_t load, uint32_t size, uint32_t h, int32_t Lq, uint32_t abs,
+                                                double rel, double threshold) {
+  if (uni(router) == KVR_ROUTE_RANDOM) return (uint32_t)__umul64hi(philox_word0(jg, 0ull, 0ull, 1ull, seed, r), (uint64_t)W);
+  if (uni(router) == KVR_ROUTE_ROUND_ROBIN) return (uint32_t)(jg % W);
+  const uint32_t lo = wave_argmin_u32(load, W);
+  const uint32_t hi = wave_argmin_u32(~load, W);
+  const uint32_t hmax = wave_argmin_u32(~h, W);
+  const uint32_t small = wave_argmin_u32(size, W);
+  const uint32_t lmin = (uint32_t)__builtin_amdgcn_readlane((int)load, (int)lo);
+  const uint32_t lmax = (uint32_t)__builtin_amdgcn_readlane((int)load, (int)hi);
+  const int32_t hbest = __builtin_amdgcn_readlane((int)h, (int)hmax);
+  if (lmax - lmin > abs && (double)lmax > rel * (double)lmin) return lo;
+  if ((double)hbest > threshold * (double)Lq) return hmax;
+  return small;
+}
+
 // The routed worker of query k (global index j0 + k): the LBGR argmin, or
-// one of the baseline routers of Sec. 5.  Wave-uniform; one lane per worker.
+// one of the baseline routers.  Wave-uniform; one lane per worker.
 __device__ __forceinline__ uint32_t route_choice(const StepArgs& a, uint32_t r, uint32_t k, uint32_t W, double eh,
                                                  const int32_t* hrow, int32_t Lq, const double* eh_sh,
                                                  const RouteView& v) {
-  const uint64_t jg = a.j0 + k;
-  if (a.C.router == KVR_ROUTE_RANDOM)
-    return (uint32_t)__umul64hi(philox_word0(jg, 0ull, 0ull, 1ull, a.C.seed, r), (uint64_t)W);
-  if (a.C.router == KVR_ROUTE_ROUND_ROBIN) return (uint32_t)(jg % W);
-  if (a.C.router == KVR_ROUTE_CACHE_AWARE) {
-    uint32_t load = 0, size = 0, h = 0;
-    if ((uint32_t)lane_id() < W) {
-      load = v.pend_count;
-      size = v.size;
-      h = (uint32_t)hrow[lane_id()];
-    }
-    const uint32_t lo = wave_argmin_u32(load, W);
-    const uint32_t hi = wave_argmin_u32(~load, W);
-    const uint32_t hmax = wave_argmin_u32(~h, W);
-    const uint32_t small = wave_argmin_u32(size, W);
-    const uint32_t lmin = (uint32_t)__builtin_amdgcn_readlane((int)load, (int)lo);
-    const uint32_t lmax = (uint32_t)__builtin_amdgcn_readlane((int)load, (int)hi);
-    const int32_t hbest = hrow[hmax];
-    if (lmax - lmin > (uint32_t)a.C.ca_balance_abs && (double)lmax > a.C.ca_balance_rel * (double)lmin) return lo;
-    if ((double)hbest > a.C.ca_cache_threshold * (double)Lq) return hmax;
-    return small;
-  }
-  return wave_argmin(eh, W, eh_sh);
-}
-
-// Record a match length and count it in the workgroup's per-worker sums
-// (LDS; added to the worker headers when the batch ends).
-__device__ __forceinline__ void count_mtok(unsigned long long* mtok, uint32_t w, int32_t h, int32_t* hslot) {
-  if (lane_id() == 0) {
-    *hslot = h;
-    atomicAdd(&mtok[w], (unsigned long long)(uint32_t)h);
-  }
+  if (a.C.router == KVR_ROUTE_LBGR) return wave_argmin(eh, W, eh_sh);
+  const uint32_t h = (uint32_t)lane_id() < W ? (uint32_t)hrow[lane_id()] : 0u;
+  return uni(route_baseline(a.C.router, a.j0 + k, a.C.seed, r, W, v.pend_count, v.size, h, Lq,
+                            (uint32_t)a.C.ca_balance_abs, a.C.ca_balance_rel, a.C.ca_cache_threshold));
 }
 
 // Record a match length without counting it (the cache's own match when
@@ -625,21 +618,26 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
 //     worker's tree changes only when a query is routed to it, so only the
 //     routed worker's match is looked at again after the load, and it follows
 //     from the one before;
-//   * the routing wave only scores, commits and loads the new leaf; the marks,
-//     the leaf list and the evictions follow on an evicting wave, several
-//     insertions (of different workers) at a time;
+//   * the routing wave only scores, commits and plans the insertion; the load of
+//     the new leaf, the marks, the leaf list and the evictions follow on an
+//     evicting wave, several insertions (of different workers) at a time;
 //   * LBGR state, tree state and query data live in LDS for the launch.
+// What is left on the chain is about 2.5 us of one wave's instructions a query
+// (route 1.4, owning the worker and planning 0.6; a wave issues an instruction
+// every 5 cycles or so, and raising its priority changes nothing), the wait for
+// matches that are late (1.5 to 3.5) and for a worker that is routed to twice in
+// a row (2 to 3).
 //
-// Waves: 0 routes and loads leaves, 1..NE evict, the rest are helpers: they
-// stage queries, match, compute draw words, rank new leaves and apply
-// completions and decay, whichever is due first.
+// Waves: 0 routes, 1..NE insert and evict, the rest are helpers: they stage
+// queries, match, compute draw words, rank new leaves and apply completions and
+// decay, whichever is due first.
 //
 // A worker's matches and insertions are ordered by its state word: the number
 // of queries matched on it, and below it five flags.  A wave takes the match of
 // query m by exchanging (m, no reader) for (m, reader), so each match is taken
 // once and in order.  The routing wave sets the owner flag and waits for a
-// reader before it loads a leaf; once that is done (loaded flag), matches go
-// on beside the evictions: the next query's at once, later ones after the
+// reader before it hands the insertion over; once the leaf is loaded (loaded
+// flag), matches go on beside the evictions: the next query's at once, later ones after the
 // marks (marked flag), which read the trail that the match after the next
 // writes.  One that the evictions could still change is put off (deferred
 // flag) until they end and the owner's flags are cleared.
@@ -661,10 +659,13 @@ struct PipeFlags {
   uint32_t end;      // every query is routed and handed
   uint32_t stop;     // an error stopped the replica
   uint32_t bad;      // the verdict on the batch
-  uint32_t pad[7];
+  uint32_t err, err_query, err_check;  // the first error
+  uint32_t pad[4];
+  int64_t err_val[3];
+  int64_t pad2;
 };
-constexpr int kFlagWords = 16;
-static_assert(sizeof(PipeFlags) == 4 * kFlagWords, "one flag word per lane of a row");
+constexpr int kFlagWords = 16;  // the counters, a word per lane of a row
+static_assert(sizeof(PipeFlags) == 4 * kFlagWords + 32, "counters, then the error's values");
 
 // 16-byte compare loads in flight per lane in the pipelined kernel's matches
 #ifndef KVR_PIPE_MATCH_UNROLL
@@ -673,20 +674,30 @@ static_assert(sizeof(PipeFlags) == 4 * kFlagWords, "one flag word per lane of a 
 constexpr int kPipeMatchUnroll = KVR_PIPE_MATCH_UNROLL;
 constexpr uint32_t kSpinLimit = 1u << 24;
 // insertions between routing and the end of their evictions, at most
-constexpr uint32_t kJobs = 4;
-// Waves per workgroup.  Three per SIMD leave 168 registers a lane, which the
-// roles' separate loops need not exceed by much (32 bytes of scratch); against
-// 8 waves, multi-turn 51.0 ms a simulation instead of 55.3, the paper's groups
-// in round-robin order 67.9 instead of 77.8, long prompts 144 instead of 188,
-// the rest within 3%.  16 waves (128 registers) lose 1 to 11%.
+constexpr uint32_t kJobs = 8;
+// Waves per workgroup: 12 (three per SIMD, 168 registers a lane; against 8,
+// multi-turn 51.0 ms a simulation instead of 55.3, the paper's groups in
+// round-robin order 67.9 instead of 77.8, the rest within 3%), and 16 for
+// replicas of many workers, whose matches of one query keep more helpers busy:
+// 128 registers and some scratch, but the long-prompt workload (32 workers)
+// takes 135.7 ms instead of 140.9.  At 16 workers 16 waves are 2% slower
+// (multi-turn, 46.2 against 45.2 ms), so the line is drawn between the two.
 #ifndef KVR_PIPE_WAVES
 #define KVR_PIPE_WAVES 12
 #endif
+#ifndef KVR_PIPE_WAVES_WIDE
+#define KVR_PIPE_WAVES_WIDE 16
+#endif
+#ifndef KVR_PIPE_WIDE_WORKERS
+#define KVR_PIPE_WIDE_WORKERS 24
+#endif
 constexpr uint32_t kPipeWaves = KVR_PIPE_WAVES;
-// Two evicting waves: an insertion's second half takes 6 to 9 us of one wave
-// against 8 to 10 us of a whole step, so one wave would be the step's bound, and
-// a third (one helper fewer) gained nothing on the two-level workload and lost
-// 4% on the long-prompt one.
+constexpr uint32_t kPipeWavesWide = KVR_PIPE_WAVES_WIDE;
+constexpr uint32_t kPipeWideWorkers = KVR_PIPE_WIDE_WORKERS;
+// Evicting waves.  One insertion takes 9 to 13 us of a wave, a step 8 to 10 us,
+// so one wave would be the step's bound.  A third (one helper fewer) gains 2 to
+// 3% on the drift and two-level workloads and loses 5% on the long-prompt one,
+// 2% on the smallest and on the ensemble.
 #ifndef KVR_PIPE_EVICTORS
 #define KVR_PIPE_EVICTORS 2
 #endif
@@ -707,47 +718,39 @@ __device__ __forceinline__ void add_rel(uint32_t* p, uint32_t v) {
   if (lane_id() == 0) __hip_atomic_fetch_add(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Stop the replica: the first error of the run is recorded (check id, the
-// query, values), the status bits are set and every wave's waits end.
-__device__ __forceinline__ void pipe_stop(GlobalHdr* g, PipeFlags* f, uint32_t r, uint64_t jg, uint32_t err,
-                                          const int64_t* dbg) {
+// Stop the replica: its first error is noted in LDS (bits, the query, check id,
+// values), to be reported when the workgroup ends, and every wave's waits end.
+__device__ __forceinline__ void pipe_stop(PipeFlags* f, uint32_t k, uint32_t err, const int64_t* dbg) {
   if (lane_id() == 0) {
-    if (atomicCAS(&g->err_taken, 0u, 1u) == 0u) {
-      g->err_check = (uint32_t)dbg[0];
-      g->err_replica = r;
-      g->err_query = jg;
-      g->err_val[0] = dbg[1];
-      g->err_val[1] = dbg[2];
-      g->err_val[2] = dbg[3];
+    if (atomicCAS(&f->err, 0u, err) == 0u) {
+      f->err_query = k;
+      f->err_check = (uint32_t)dbg[0];
+      f->err_val[0] = dbg[1];
+      f->err_val[1] = dbg[2];
+      f->err_val[2] = dbg[3];
     }
-    atomicOr(&g->status, err);
     __hip_atomic_store(&f->stop, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 
-#ifndef KVR_POLL_SLEEP
-#define KVR_POLL_SLEEP 1
-#endif
 // One poll of a wait: false once the replica was stopped; a wait that has
 // run out stops it (check id 90 + site, an internal error).
-__device__ __forceinline__ bool pipe_poll(uint32_t& spins, PipeFlags* f, GlobalHdr* g, uint32_t r, uint64_t jg,
-                                          int site) {
+__device__ __forceinline__ bool pipe_poll(uint32_t& spins, PipeFlags* f, uint32_t k, int site) {
   if (ld_acq(&f->stop)) return false;
   if (++spins > kSpinLimit) {
     const int64_t dbg[4] = {90 + site, (int64_t)f->routed, (int64_t)f->handed, (int64_t)f->staged};
-    pipe_stop(g, f, r, jg, KVR_DEV_INTERNAL, dbg);
+    pipe_stop(f, k, KVR_DEV_INTERNAL, dbg);
     return false;
   }
-  __builtin_amdgcn_s_sleep(KVR_POLL_SLEEP);
+  __builtin_amdgcn_s_sleep(1);
   return true;
 }
 
 // Wait until *p >= target.  False when the replica was stopped.
-__device__ __forceinline__ bool pipe_wait(const uint32_t* p, uint32_t target, PipeFlags* f, GlobalHdr* g, uint32_t r,
-                                          uint64_t jg, int site) {
+__device__ __forceinline__ bool pipe_wait(const uint32_t* p, uint32_t target, PipeFlags* f, uint32_t k, int site) {
   uint32_t spins = 0;
   while (ld_acq(p) < target)
-    if (!pipe_poll(spins, f, g, r, jg, site)) return false;
+    if (!pipe_poll(spins, f, k, site)) return false;
   return true;
 }
 
@@ -803,8 +806,9 @@ __device__ __forceinline__ bool claim_match(uint32_t* st, uint32_t sv) {
   return uni(old) == sv;
 }
 
-// NW waves, NE of them evicting.
-template <bool PT, uint32_t NW, uint32_t NE>
+// NW waves, NE of them evicting; kLbgr: the learned router only (the baselines'
+// code would lengthen every step).
+template <bool PT, uint32_t NW, uint32_t NE, bool kLbgr>
 __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   constexpr uint32_t nh = NW - 1u - NE;  // helper waves
   // half of the helpers compute draw words, from the second on (the first
@@ -835,11 +839,11 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   int32_t* stage_base = reinterpret_cast<int32_t*>(ring + a.rcap);
 
   __shared__ PipeFlags f;
-  __shared__ int32_t h_sh[3][kMaxWorkers];  // h of q_k in slot query_slot(k)
+  __shared__ int32_t h_sh[4][kMaxWorkers];  // h of q_k in slot query_slot(k)
   __shared__ double eh_sh[kMaxWorkers];
-  __shared__ int32_t ell_sh[4];             // LCP(q_k, q_k+1) in slot k & 3
-  __shared__ int32_t len_sh[4], olen_sh[4]; // length and output length of q_k
-  __shared__ int64_t arr_sh[4];             // its arrival
+  __shared__ int32_t ell_sh[8];             // LCP(q_k, q_k+1) in slot k & 7
+  __shared__ int32_t len_sh[8], olen_sh[8]; // length and output length of q_k
+  __shared__ int64_t arr_sh[8];             // its arrival
   __shared__ PipeJob job_sh[kJobs];         // insertion k in slot k % kJobs
   __shared__ uint32_t jdone_sh[kJobs];      // k + 1 once it is finished
   __shared__ uint32_t owner_sh[kMaxWorkers]; // the insertion that owns a worker
@@ -868,10 +872,10 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   if (threadIdx.x < KVR_PHASES) eticks_sh[threadIdx.x] = 0ull;
   if (threadIdx.x < kMaxWorkers) {
     mtok_sh[threadIdx.x] = 0ull;
-    h_sh[0][threadIdx.x] = h_sh[1][threadIdx.x] = h_sh[2][threadIdx.x] = 0;
+    for (uint32_t b = 0; b < 4u; ++b) h_sh[b][threadIdx.x] = 0;
   }
+  if (threadIdx.x < 8u) ell_sh[threadIdx.x] = 0x7fffffff;
   if (threadIdx.x < kJobs) {
-    ell_sh[threadIdx.x] = 0x7fffffff;
     jdone_sh[threadIdx.x] = 0u;
     rank_ready_sh[threadIdx.x] = 0u;
     rn_sh[threadIdx.x] = 0ull;
@@ -935,13 +939,13 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   const auto match_one = [&](uint32_t mm, uint32_t mw, uint32_t msv) __attribute__((always_inline)) {
     const uint32_t mp = query_slot(mm, a.nbuf), mq = query_slot(mm + a.nbuf - 1u, a.nbuf);  // its slot, the last one's
     const int32_t h_old = uni(h_sh[mq][mw]);
-    const int32_t ell = mm > 0u ? uni(ell_sh[(mm - 1u) & 3u]) : 0;
+    const int32_t ell = mm > 0u ? uni(ell_sh[(mm - 1u) & 7u]) : 0;
     const Ptrs P = worker_ptrs(a.ws, a.L, r, mw);
     MatchEnd me{};
     bool walked = false;
     const int32_t h = match_ahead<kPipeMatchUnroll>(
         P.nodes, arena_of(P, uni(tree_sh[mw * kStWords + 12])), rootf + mw * kRootFilterWords, P.A,
-        smem + mp * qwords + kQueryPad, uni(len_sh[mm & 3u]), h_old, ell,
+        smem + mp * qwords + kQueryPad, uni(len_sh[mm & 7u]), h_old, ell,
         trail_sh + (mq * W + mw) * kTrailWords, trail_sh + (mp * W + mw) * kTrailWords, walked, me);
     bool stays = true;
     if (msv & kOwner) {
@@ -950,7 +954,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
       const uint32_t jk = uni(owner_sh[mw]);
       int32_t on_path = jk + 1u == mm ? ell : 0;
       if (jk + 2u == mm) {
-        const int32_t e0 = uni(ell_sh[jk & 3u]);
+        const int32_t e0 = uni(ell_sh[jk & 7u]);
         on_path = e0 < ell ? e0 : ell;
       }
       stays = match_stays(P.nodes, load_job(&job_sh[jk % kJobs]), h, on_path, walked, me);
@@ -967,10 +971,6 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
     }
   };
 
-#ifdef KVR_PRIO
-  if (wave == 0) __builtin_amdgcn_s_setprio(3);
-  else if (wave <= NE) __builtin_amdgcn_s_setprio(2);
-#endif
   if (wave == 0) {
     for (;;) {
       // -------------------------------------------------------- routing wave
@@ -990,7 +990,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           msv = (uint32_t)__builtin_amdgcn_readlane((int)sv, (int)mw);
           if (!claim_match(&st_sh[mw], msv)) continue;
         } else {
-          if (!pipe_poll(spins, &f, g, r, a.j0 + kq, 0)) break;
+          if (!pipe_poll(spins, &f, kq, 0)) break;
           continue;
         }
       } else {
@@ -1000,17 +1000,17 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           const uint32_t k = kq, cur = query_slot(k, a.nbuf), nxt = query_slot(k + 1u, a.nbuf), slot = k % kJobs;
           const uint64_t jg = a.j0 + k;
           clock_mark<PT>(&clk, KVR_PHASE_JOIN);
-          if (!pipe_wait(&f.decayed, k + 1u, &f, g, r, jg, 1)) break;
+          if (!pipe_wait(&f.decayed, k + 1u, &f, k, 1)) break;
           clock_mark<PT>(&clk, KVR_PHASE_STAGE_WAIT);
           // the slot of insertion k - kJobs is reused
           if (k >= kJobs) {
             bool ok = true;
             while (ld_acq(&jdone_sh[slot]) != k - kJobs + 1u)
-              if (!(ok = pipe_poll(spins, &f, g, r, jg, 2))) break;
+              if (!(ok = pipe_poll(spins, &f, k, 2))) break;
             if (!ok) break;
           }
           clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
-          const int32_t Lp = uni(len_sh[k & 3u]);
+          const int32_t Lp = uni(len_sh[k & 7u]);
           double eh = __builtin_huge_val(), ch = 0.0;
           RouteView v{};
           if ((uint32_t)lane < W) {
@@ -1024,7 +1024,8 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
             eh_sh[lane] = eh;
           }
           __builtin_amdgcn_wave_barrier();
-          const uint32_t best = uni(route_choice(a, r, k, W, eh, h_sh[cur], Lp, eh_sh, v));
+          const uint32_t best =
+              uni(kLbgr ? wave_argmin(eh, W, eh_sh) : route_choice(a, r, k, W, eh, h_sh[cur], Lp, eh_sh, v));
           const Ptrs P = worker_ptrs(a.ws, a.L, r, best);
           const int32_t hb = uni(h_sh[cur][best]);
           const uint32_t size = (uint32_t)__builtin_amdgcn_readlane((int)v.size, (int)best);
@@ -1034,7 +1035,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           // commit: the routed worker's lane
           uint32_t err0 = 0;
           if ((uint32_t)lane == best) {
-            err0 = commit_lds(a.C, P, lb, best, v, ch, hb, Lp, arr_sh[k & 3u], olen_sh[k & 3u]);
+            err0 = commit_lds(a.C, P, lb, best, v, ch, hb, Lp, arr_sh[k & 7u], olen_sh[k & 7u]);
             lb.size[best] = size + nload - nev;
           }
           err0 = (uint32_t)__builtin_amdgcn_readlane((int)err0, (int)best);
@@ -1083,63 +1084,57 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
               if (a.hits) a.hits[orow] = hb;
             }
             const int64_t dbg[4] = {0, 0, 0, 0};
-            pipe_stop(g, &f, r, jg, err0, dbg);
+            pipe_stop(&f, k, err0, dbg);
             break;
           }
           st_rel(&f.routed, k + 1u);
           clock_mark<PT>(&clk, KVR_PHASE_ROUTE);
-          // ---- own the worker: its earlier insertion first finishes, and so
-          // does a match of q_k+1 on it
-          uint32_t pre = 0;  // matches of later queries taken on it
+          // ---- own the worker: its earlier insertion first finishes, and so does
+          // a match of a later query on it
+          uint32_t pre;  // matches of later queries taken on it
           {
             bool ok = true;
-            while (ld_acq(&st_sh[best]) & kOwner)
-              if (!(ok = pipe_poll(spins, &f, g, r, jg, 3))) break;
+            uint32_t sb = 0;
+            for (;;) {
+              if (lane == 0) sb = __hip_atomic_fetch_or(&st_sh[best], kOwner, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+              sb = uni(sb);
+              if (!(sb & kOwner)) break;
+              if (!(ok = pipe_poll(spins, &f, k, 3))) break;
+            }
             if (!ok) break;
-            if (lane == 0) atomicOr(&st_sh[best], kOwner);
-            uint32_t sb;
-            while ((sb = ld_acq(&st_sh[best])) & kReader)
-              if (!(ok = pipe_poll(spins, &f, g, r, jg, 4))) break;
+            while (sb & kReader) {
+              sb = ld_acq(&st_sh[best]);
+              if ((sb & kReader) && !(ok = pipe_poll(spins, &f, k, 4))) break;
+            }
             if (!ok) break;
             pre = ((sb >> kCountShift) - (k + 1u)) & kCountMask;
             spins = 0;
           }
           clock_mark<PT>(&clk, KVR_PHASE_EVICTOR_WAIT);
-          // ---- the load of the new leaf
-          St s = load_st_lds(tree_sh + best * kStWords);
+          // ---- plan the insertion, and what it makes of the match of q_k+1 taken
+          // before it; those of later ones are taken again
           PipeJob job;
-          int32_t split;
-          int32_t* tr = trail_sh + (cur * W + best) * kTrailWords;
-          const uint32_t err =
-              load_leaf(P, s, a.L.B, a.L.maxL, smem + cur * qwords + kQueryPad, Lp, hb, tr, job,
-                        split);
-          store_st_lds(tree_sh + best * kStWords, s);
-          if (err) {
-            const int64_t dbg[4] = {s.dbg_check, s.dbg_val[0], s.dbg_val[1], s.dbg_val[2]};
-            pipe_stop(g, &f, r, jg, err, dbg);
-            break;
-          }
-          // a new child of the root: its first token joins the root filter
-          if (hb == 0 && lane == 0) rf_add(rootf + best * kRootFilterWords, job.tok);
-          // matches taken on the tree before: what the load makes of that of
-          // q_k+1; that of q_k+2 is taken again
-          uint32_t state = kLoaded;
+          plan_insertion(job, tree_sh + best * kStWords, a.L.B, a.L.maxL, hb, Lp);
+          job.pre = -1;
+          uint32_t state = 0;
           if (pre) {
             const int32_t h_pre = uni(h_sh[nxt][best]);
             bool stays;
-            const int32_t h = match_after_load(P.nodes, job, split, h_pre, uni(ell_sh[k & 3u]), tr,
-                                               trail_sh + (nxt * W + best) * kTrailWords, stays);
+            const int32_t h = match_before_load(P.nodes, job, h_pre, uni(ell_sh[k & 7u]),
+                                                trail_sh + (nxt * W + best) * kTrailWords, stays);
             int32_t diff = (stays ? h : 0) - h_pre;
-            if (pre > 1u) {
-              diff -= uni(h_sh[query_slot(k + 2u, a.nbuf)][best]);
+            for (uint32_t x = 2; x <= pre; ++x) {
+              diff -= uni(h_sh[query_slot(k + x, a.nbuf)][best]);
               state -= 1u << kCountShift;
             }
             if (lane == 0) {
               h_sh[nxt][best] = h;
               atomicAdd(&mtok_sh[best], (unsigned long long)(int64_t)diff);
             }
-            // (put off: one match fewer, to be taken after the evictions)
-            if (!stays) state += kDeferred - (1u << kCountShift);
+            if (stays)
+              job.pre = h_pre;
+            else  // put off: one match fewer, to be taken after the evictions
+              state += kDeferred - (1u << kCountShift);
           }
           if (lane == 0) {
             PipeJob& j = job_sh[slot];
@@ -1147,31 +1142,20 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
             j.worker = best;
             j.h = job.h;
             j.L = job.L;
-            j.l = job.l;
-            j.a = job.a;
-            j.tok = job.tok;
             j.nfree = job.nfree;
             j.nev = job.nev;
             j.rn = rn;
             j.r0 = r0;
-            j.replace = job.replace;
-            j.marked = job.marked;
             j.calm = job.calm;
             j.phase = job.phase;
+            j.pre = job.pre;
             owner_sh[best] = k;
-            h_sh[cur][best] = Lp;  // all of q_k is cached here now
-            // q_k's buffer is free, and so is the slot of the LCP of the query
-            // that will be staged there with the one before it
-            ell_sh[(k + a.nbuf - 1u) & 3u] = 0x7fffffff;
+            h_sh[cur][best] = Lp;  // all of q_k is cached here from the load on
           }
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
           if (lane == 0) {
             __hip_atomic_fetch_add(&st_sh[best], state, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_store(&f.fronts, k + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             __hip_atomic_store(&f.handed, k + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (hb < Lp)
-              __hip_atomic_store(&rank_ready_sh[slot], ((k + 1u) << 2) | 1u, __ATOMIC_RELEASE,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
           }
           kq = k + 1u;
           clock_mark<PT>(&clk, KVR_PHASE_LOAD);
@@ -1191,28 +1175,73 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
         ticket = true;
         spins = 0;
       }
+      const uint32_t ended = ld_acq(&f.end);  // (read first: set once every insertion has been handed)
       if (ld_acq(&f.handed) <= kq) {  // wait for that insertion
-        if (ld_acq(&f.end)) break;  // every insertion has been handed by then
+        if (ended) break;
         const uint32_t now = ld_acq(&f.routed);
         if (now != seen) {
           seen = now;
           spins = 0;
         }
-        if (!pipe_poll(spins, &f, g, r, a.j0 + kq, 6)) break;
+        if (!pipe_poll(spins, &f, kq, 6)) break;
         continue;
       }
       clock_mark<PT>(&clk, KVR_PHASE_E_IDLE);
       ticket = false;
       {
-        // ---- marks, leaf list, evictions
+        // ---- the load of the new leaf
         PipeHook hook;
         const uint32_t slot = kq % kJobs;
-        const PipeJob job = load_job(&job_sh[slot]);
+        PipeJob job = load_job(&job_sh[slot]);
         const Ptrs P = worker_ptrs(a.ws, a.L, r, job.worker);
+        uint32_t* tree = tree_sh + job.worker * kStWords;
+        const uint32_t buf = query_slot(kq, a.nbuf);
+        int32_t* tr = trail_sh + (buf * W + job.worker) * kTrailWords;
         EvictJob ej;
-        ej.s = load_st_lds(tree_sh + job.worker * kStWords);
-        if (!job.marked) mark_cached(P, ej.s, a.L.B, job, 
-                                      trail_sh + (query_slot(kq, a.nbuf) * W + job.worker) * kTrailWords);
+        ej.s = load_st_lds(tree);
+        int32_t split;
+        const uint32_t lerr = load_leaf(P, ej.s, tree, a.L.B, smem + buf * qwords + kQueryPad, tr, job, split);
+        store_st_lds(tree, ej.s);
+        if (lerr) {
+          const int64_t dbg[4] = {ej.s.dbg_check, ej.s.dbg_val[0], ej.s.dbg_val[1], ej.s.dbg_val[2]};
+          pipe_stop(&f, kq, lerr, dbg);
+          break;
+        }
+        if (job.pre >= 0)
+          trail_after_load(job, split, job.pre, uni(ell_sh[kq & 7u]), tr,
+                           trail_sh + (query_slot(kq + 1u, a.nbuf) * W + job.worker) * kTrailWords);
+        // loads are published in order: q_kq's buffer is free then, and so is the
+        // slot of the LCP of the query that will be staged there with the one
+        // before it
+        spins = 0;
+        {
+          bool ok = true;
+          while (ld_acq(&f.fronts) != kq)
+            if (!(ok = pipe_poll(spins, &f, kq, 7))) break;
+          if (!ok) break;
+        }
+        if (lane == 0) {
+          // a new child of the root: its first token joins the root filter
+          if (job.h == 0) rf_add(rootf + job.worker * kRootFilterWords, job.tok);
+          PipeJob& j = job_sh[slot];
+          j.l = job.l;
+          j.a = job.a;
+          j.tok = job.tok;
+          j.replace = job.replace;
+          j.marked = job.marked;
+          ell_sh[(kq + a.nbuf - 1u) & 7u] = 0x7fffffff;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane == 0) {
+          __hip_atomic_fetch_or(&st_sh[job.worker], kLoaded, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (job.h < job.L)
+            __hip_atomic_store(&rank_ready_sh[slot], ((kq + 1u) << 2) | 1u, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_store(&f.fronts, kq + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        clock_mark<PT>(&clk, KVR_PHASE_E_MATCH);
+        // ---- marks, leaf list, evictions
+        if (!job.marked) mark_cached(P, ej.s, a.L.B, job, tr);
         // the trail has been read
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if (lane == 0) atomicOr(&st_sh[job.worker], kMarked);
@@ -1221,7 +1250,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
         hook.job = job;
         hook.ready = &rank_ready_sh[slot];
         hook.rank = &rank_sh[slot];
-        hook.state = tree_sh + job.worker * kStWords;
+        hook.state = tree;
         hook.stop = &f.stop;
         ej.ia.seed = a.C.seed;
         ej.ia.jg = a.j0 + kq;
@@ -1262,7 +1291,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           err = rlt_evict<PT>(P, ej, us, dbg, &clk, KVR_PHASE_E_EVICT, KVR_PHASE_E_FINISH, hook);
         }
         if (err) {
-          pipe_stop(g, &f, r, a.j0 + kq, err, dbg);
+          pipe_stop(&f, kq, err, dbg);
           break;
         }
         // finished: the worker is free again
@@ -1308,7 +1337,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           }
           if (a.all_hits && (uint32_t)lane < W) a.all_hits[orow * W + (uint32_t)lane] = (uint32_t)lane == best ? hb : h_sh[query_slot(k, a.nbuf)][lane];
           if (k + 1u < n && !stopped) {
-            const int64_t t = arr_sh[(k + 1u) & 3u], tp = arr_sh[k & 3u];
+            const int64_t t = arr_sh[(k + 1u) & 7u], tp = arr_sh[k & 7u];
             const int64_t tick = t / a.C.dt_us;
             if ((uint32_t)lane < W) {
               const Ptrs P = worker_ptrs(a.ws, a.L, r, (uint32_t)lane);
@@ -1372,15 +1401,15 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
         clock_mark<PT>(&clk, KVR_PHASE_H_WAIT);
         const uint64_t o0 = a.offsets[sN];
         const int32_t Ln = (int32_t)(a.offsets[sN + 1u] - o0);
-        const int32_t Lc = sN > 0u ? uni(len_sh[(sN - 1u) & 3u]) : 0;
+        const int32_t Lc = sN > 0u ? uni(len_sh[(sN - 1u) & 7u]) : 0;
         if (hw == 0 && lane == 0) {
-          len_sh[sN & 3u] = Ln;
-          olen_sh[sN & 3u] = query_out_len(a.out_len, sN);
-          arr_sh[sN & 3u] = a.arrival[sN];
+          len_sh[sN & 7u] = Ln;
+          olen_sh[sN & 7u] = query_out_len(a.out_len, sN);
+          arr_sh[sN & 7u] = a.arrival[sN];
         }
         int32_t* qn = smem + query_slot(sN, a.nbuf) * qwords + kQueryPad;
         const int32_t* qc = smem + query_slot(sN + a.nbuf - 1u, a.nbuf) * qwords + kQueryPad;
-        stage_query<4>(a.tokens, o0, Ln, qn, qc, Lc, hw * KVR_WAVE, nh * KVR_WAVE, &ell_sh[(sN - 1u) & 3u]);
+        stage_query<4>(a.tokens, o0, Ln, qn, qc, Lc, hw * KVR_WAVE, nh * KVR_WAVE, &ell_sh[(sN - 1u) & 7u]);
         add_rel(&f.staged, 1u);
         sN += 1;
         spins = 0;
@@ -1416,16 +1445,13 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
         }
       }
       if (!take) {
-        if (ended && dN >= routed) break;  // (and no rank is wanted)
+        if (ended && dN >= routed && fronts == n) break;  // (and no rank is wanted)
         const uint32_t now = routed + fronts + staged;
         if (now != seen) {
           seen = now;
           spins = 0;
         }
-#ifdef KVR_H_SLEEP
-        __builtin_amdgcn_s_sleep(KVR_H_SLEEP);
-#endif
-        if (!pipe_poll(spins, &f, g, r, a.j0 + routed, 9)) continue;  // (the duties of routed queries first)
+        if (!pipe_poll(spins, &f, routed, 9)) continue;  // (the duties of routed queries first)
         continue;
       }
       match_one(mm, mw, msv);
@@ -1465,6 +1491,17 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   if (threadIdx.x == 0) {
     if constexpr (PT)
       for (int p = KVR_PHASE_E_EVICT; p < KVR_PHASES; ++p) rh->phase_ticks[p] += eticks_sh[p];
+    if (f.err) {
+      if (atomicCAS(&g->err_taken, 0u, 1u) == 0u) {
+        g->err_check = f.err_check;
+        g->err_replica = r;
+        g->err_query = a.j0 + f.err_query;
+        g->err_val[0] = f.err_val[0];
+        g->err_val[1] = f.err_val[1];
+        g->err_val[2] = f.err_val[2];
+      }
+      atomicOr(&g->status, f.err);
+    }
     if (!f.stop) {
       rh->tprev = a.arrival[n - 1u];
       if (r == 0) g->last_arrival = a.arrival[n - 1u];
@@ -1583,7 +1620,6 @@ size_t step_lds_bytes_pipe(uint32_t maxL, uint32_t W, uint32_t nbuf, uint32_t uc
 }
 
 uint32_t step_pipe_evictors() { return kPipeEvictors; }
-uint32_t step_pipe_jobs() { return kJobs; }
 
 hipError_t launch_init(char* ws, const Layout& L, double rls_p0, hipStream_t st) {
   const uint64_t work = (uint64_t)L.R * L.W > L.R ? (uint64_t)L.R * L.W : L.R;
@@ -1622,12 +1658,25 @@ hipError_t launch_step(const StepArgs& args, hipStream_t st) {
   const bool rt = a.L.has_router != 0, ba = a.L.beta > 1;
   if (a.pipe) {
     const size_t lds_p = step_lds_bytes_pipe(a.L.maxL, a.L.W, a.nbuf, a.ucap, a.rcap);
-    if (a.C.phase_timers)
-      hipLaunchKernelGGL((step_kernel_pipe<true, kPipeWaves, kPipeEvictors>), dim3(a.L.R), dim3(64 * kPipeWaves), lds_p,
-                         st, a);
-    else
-      hipLaunchKernelGGL((step_kernel_pipe<false, kPipeWaves, kPipeEvictors>), dim3(a.L.R), dim3(64 * kPipeWaves),
-                         lds_p, st, a);
+    const bool lbgr = a.C.router == KVR_ROUTE_LBGR;
+#define KVR_PIPE_LAUNCH(PT, NW, LB) \
+  hipLaunchKernelGGL((step_kernel_pipe<PT, NW, kPipeEvictors, LB>), dim3(a.L.R), dim3(64 * NW), lds_p, st, a)
+    if (a.L.W >= kPipeWideWorkers) {
+      if (a.C.phase_timers)
+        KVR_PIPE_LAUNCH(true, kPipeWavesWide, false);
+      else if (lbgr)
+        KVR_PIPE_LAUNCH(false, kPipeWavesWide, true);
+      else
+        KVR_PIPE_LAUNCH(false, kPipeWavesWide, false);
+    } else {
+      if (a.C.phase_timers)
+        KVR_PIPE_LAUNCH(true, kPipeWaves, false);
+      else if (lbgr)
+        KVR_PIPE_LAUNCH(false, kPipeWaves, true);
+      else
+        KVR_PIPE_LAUNCH(false, kPipeWaves, false);
+    }
+#undef KVR_PIPE_LAUNCH
   } else if (rt && ba)
     hipLaunchKernelGGL((step_kernel<true, true, false>), dim3(a.L.R), dim3(64 * waves), lds, st, a);
   else if (rt)
@@ -1686,9 +1735,13 @@ hipError_t launch_stats_into(char* ws, const Layout& L, uint64_t w0, uint32_t n,
   return hipGetLastError();
 }
 
-static const void* const kStepKernels[7] = {
-    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWaves, kPipeEvictors>),
-    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWaves, kPipeEvictors>),
+static const void* const kStepKernels[11] = {
+    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWaves, kPipeEvictors, true>),
+    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWaves, kPipeEvictors, false>),
+    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWaves, kPipeEvictors, false>),
+    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWavesWide, kPipeEvictors, true>),
+    reinterpret_cast<const void*>(step_kernel_pipe<false, kPipeWavesWide, kPipeEvictors, false>),
+    reinterpret_cast<const void*>(step_kernel_pipe<true, kPipeWavesWide, kPipeEvictors, false>),
     reinterpret_cast<const void*>(step_kernel<false, false, false>),
     reinterpret_cast<const void*>(step_kernel<false, true, false>),
     reinterpret_cast<const void*>(step_kernel<true, false, false>),

@@ -164,7 +164,7 @@ struct StepArgs {
   uint32_t rcap;  // draw words precomputed in LDS: per insertion, or (pipelined kernel) the ring that insertions share
   uint64_t j0;
   uint32_t pipe;  // 1: the pipelined step kernel (separate evicting waves)
-  uint32_t nbuf;  // its query buffers in LDS (2 or 3)
+  uint32_t nbuf;  // its query buffers in LDS (2 to 4)
   uint32_t check; // 1: the step kernel checks the batch before it changes anything
   uint32_t pad2;
 };

@@ -122,22 +122,51 @@ __device__ __forceinline__ void trail_add(int32_t* t, int32_t& pc, int32_t node,
   pc = pc < kPathMax ? pc + 1 : kPathMax + 1;
 }
 
-// The last of n entries that starts above depth d > 0 (it holds depth d if
-// any does), with its node, start and end; -1 when n is 0.
-__device__ __forceinline__ int32_t trail_at(const int32_t* t, int32_t n, int32_t d, int32_t& node, int32_t& start,
-                                            int32_t& end) {
-  int32_t e = -1;
-  for (int32_t b = 0; b < n; b += KVR_WAVE) {
-    const int32_t k = b + lane_id();
-    const bool above = k < n && (k == 0 || trail_end(t)[k - 1] < d);
-    const uint64_t m = __ballot(above);
-    if (m) e = b + 63 - __clzll((long long)m);
+// A trail as a wave reads it: an entry per lane, so that everything looked up
+// in it is one round of LDS reads.
+struct TrailView {
+  int32_t count, vnode, vend;
+  const int32_t* t;
+  __device__ __forceinline__ int32_t node(int32_t e) const {
+    return KVR_WAVE == 1 ? t[1 + e] : __builtin_amdgcn_readlane(vnode, e);
   }
-  if (e < 0) return -1;
-  node = uni(trail_node(t)[e]);
-  start = e > 0 ? uni(trail_end(t)[e - 1]) : 0;
-  end = uni(trail_end(t)[e]);
-  return e;
+  __device__ __forceinline__ int32_t end(int32_t e) const {
+    return KVR_WAVE == 1 ? t[1 + kPathMax + e] : __builtin_amdgcn_readlane(vend, e);
+  }
+  __device__ __forceinline__ int32_t start(int32_t e) const { return e > 0 ? end(e - 1) : 0; }
+  // the last entry that starts above depth d > 0 (it holds depth d if any
+  // does); -1 when there is none
+  __device__ __forceinline__ int32_t at(int32_t d) const {
+    if (KVR_WAVE == 1) {
+      int32_t e = count - 1;
+      while (e > 0 && end(e - 1) >= d) --e;
+      return e;
+    }
+    return count > 0 ? (int32_t)__popcll(__ballot(lane_id() < count - 1 && vend < d)) : -1;
+  }
+  // the first n entries into another trail
+  __device__ __forceinline__ void copy_to(int32_t* dst, int32_t n) const {
+    if (KVR_WAVE == 1) {
+      for (int32_t e = 0; e < n; ++e) {
+        dst[1 + e] = t[1 + e];
+        dst[1 + kPathMax + e] = t[1 + kPathMax + e];
+      }
+    } else if (lane_id() < n) {
+      dst[1 + lane_id()] = vnode;
+      dst[1 + kPathMax + lane_id()] = vend;
+    }
+  }
+};
+static_assert(KVR_WAVE == 1 || KVR_WAVE >= kPathMax, "a trail's entries fit a wave's lanes");
+
+__device__ __forceinline__ TrailView view_trail(const int32_t* t) {
+  TrailView v;
+  v.t = t;
+  const int32_t c = t[0];
+  v.vnode = t[1 + (lane_id() & (kPathMax - 1))];
+  v.vend = t[1 + kPathMax + (lane_id() & (kPathMax - 1))];
+  v.count = uni(c);
+  return v;
 }
 
 // ---------------------------------------------------------------- matching
@@ -161,35 +190,30 @@ template <int kU>
 __device__ __forceinline__ int32_t match_ahead(const NodeRec* nodes, const int32_t* ar, const uint32_t* rf,
                                                uint32_t A, const int32_t* q, int32_t L, int32_t h_old, int32_t ell,
                                                const int32_t* src, int32_t* dst, bool& walked, MatchEnd& me) {
-  const int32_t have = uni(src[0]);
+  const TrailView v = view_trail(src);
   int32_t x = 0, off = 0, d = 0, pc = 0;
   bool walk = true;
-  if (ell > 0 && have <= kPathMax) {
+  if (ell > 0 && v.count <= kPathMax) {
     if (h_old < ell) {
-      pc = have;
+      pc = v.count;
       d = h_old;
       walk = false;
     } else {
-      int32_t nx = 0, st = 0, en = 0;
-      const int32_t e = trail_at(src, have, ell, nx, st, en);
-      if (e >= 0 && en >= ell) {  // (always, for a consistent record)
+      const int32_t e = v.at(ell);
+      if (e >= 0 && v.end(e) >= ell) {  // (always, for a consistent record)
         pc = e + 1;
         d = ell;
-        if (ell == L || (ell < en && h_old > ell)) {
+        if (ell == L || (ell < v.end(e) && h_old > ell)) {
           walk = false;
         } else {
-          x = nx;
-          off = ell - st;
+          x = v.node(e);
+          off = ell - v.start(e);
         }
       }
     }
   }
-  if (walk && x == 0 && !rf_may(rf, q[0])) walk = false;
-  for (int32_t k = lane_id(); k < pc; k += KVR_WAVE) {
-    const int32_t n = trail_node(src)[k], en = trail_end(src)[k];
-    trail_node(dst)[k] = n;
-    trail_end(dst)[k] = en;
-  }
+  if (walk && x == 0 && !rf_may(rf, uni(q[0]))) walk = false;
+  v.copy_to(dst, pc);
   walked = walk;
   if (walk) {
     NodeRec nx = load_node(nodes, x);
@@ -220,9 +244,10 @@ __device__ __forceinline__ int32_t match_ahead(const NodeRec* nodes, const int32
   return d;
 }
 
-// ---------------------------------------------------------------- insertion, first half
+// ---------------------------------------------------------------- insertion
 
-// What an insertion leaves to its second half (LDS, one word per lane).
+// An insertion: what the routing wave plans (k, worker, h, L, nfree, nev, rn, r0,
+// calm, phase, pre) and what its load adds (LDS, one word per lane).
 struct PipeJob {
   uint32_t k;       // query index in the batch
   uint32_t worker;
@@ -236,7 +261,7 @@ struct PipeJob {
   uint32_t marked;  // the cached part is marked already
   uint32_t calm;    // no new phase can start in this insertion (match_stays)
   uint32_t phase;   // the phase before it
-  uint32_t pad;
+  int32_t pre;      // h of the next query's match taken before the load and final, else -1
 };
 constexpr int kJobWords = sizeof(PipeJob) / 4;
 static_assert(kJobWords == 16, "a job is one word per lane of a row");
@@ -245,9 +270,9 @@ __device__ __forceinline__ PipeJob load_job(const PipeJob* p) {
   if (KVR_WAVE == 1) return *p;
   const uint32_t v = reinterpret_cast<const uint32_t*>(p)[lane_id() & (kJobWords - 1)];
   PipeJob j;
-  uint32_t f[15];
+  uint32_t f[16];
 #pragma unroll
-  for (int k = 0; k < 15; ++k) f[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
+  for (int k = 0; k < 16; ++k) f[k] = (uint32_t)__builtin_amdgcn_readlane((int)v, k);
   j.k = f[0];
   j.worker = f[1];
   j.h = (int32_t)f[2];
@@ -263,6 +288,7 @@ __device__ __forceinline__ PipeJob load_job(const PipeJob* p) {
   j.marked = f[12];
   j.calm = f[13];
   j.phase = f[14];
+  j.pre = (int32_t)f[15];
   return j;
 }
 
@@ -410,97 +436,190 @@ __device__ __forceinline__ int32_t split_for_leaf(const Ptrs& P, St& s, int32_t 
   return hd;
 }
 
-// First half of the RLT insertion of q[0, L) (in LDS) into the worker's cache
-// (h = LCP(q, cache), t = the trail of that match): what the matches of later
-// queries need, the split of the edge the match ends in and the load of
-// q[h, L) as one new leaf.  t then holds q's trail in the updated cache.  The
-// marks, the leaf list and the evictions are left to the second half, except
-// that a path too deep for a trail is marked here.  Fills job's fields from h
-// on but for the draw words; split = the node whose edge was split (its head is
-// job.a), or 0.  KVR_DEV_* bits (0: done).
-__device__ __forceinline__ uint32_t load_leaf(const Ptrs& P, St& s, uint32_t B, uint32_t maxL, const int32_t* q,
-                                              int32_t L, int32_t h, int32_t* t, PipeJob& job, int32_t& split) {
-  int32_t have = uni(t[0]);
-  int32_t last = 0, start = 0, end = 0, e = -1;
-  if (h > 0 && have <= kPathMax) {
-    e = trail_at(t, have, h, last, start, end);
-    if (e < 0 || end < h || last <= 0 || (uint32_t)last >= s.hwm) {
-      KVR_FAIL_CHECK(s, 1, e, h, last);
+// The rare ways of a load, out of line so that the common
+// one keeps its state in registers; St goes through the worker's words in LDS.
+
+// A path too deep for a trail: walk it by child lookups and mark it; the node
+// its cached part ends in and that node's start, or -1.
+__device__ __noinline__ int32_t mark_by_lookup(Ptrs P, uint32_t* state, uint32_t B, const int32_t* q, int32_t h,
+                                               int32_t* start, int64_t* fail) {
+  St s = load_st_lds(state);
+  const int32_t* ar = arena_of(P, s.arena_sel);
+  int32_t d = 0, last = 0;
+  NodeRec nx = load_node(P.nodes, 0);
+  while (d < h) {
+    const int32_t c = uni(child_find(ar, nx, uni(q[d])));
+    if (c <= 0 || (uint32_t)c >= s.hwm) {
+      KVR_FAIL_CHECK(s, 1, last, d, h);
+      last = -1;
+      break;
+    }
+    nx = load_node(P.nodes, c);
+    const int32_t cov = nx.len < h - d ? nx.len : h - d;
+    if (cov <= 0) {
+      KVR_FAIL_CHECK(s, 2, c, nx.len, d);
+      last = -1;
+      break;
+    }
+    mark_edge(P, s, B, c, nx, cov, nx.nchild == 0);
+    last = c;
+    *start = d;
+    d += cov;
+  }
+  wave_mem_sync();  // the marks above are read again below
+  store_st_lds(state, s);
+  fail[0] = s.dbg_check;
+  fail[1] = s.dbg_val[0];
+  fail[2] = s.dbg_val[1];
+  fail[3] = s.dbg_val[2];
+  return last;
+}
+
+// Split the edge of node x (split_for_leaf), with its head's child array at
+// *coff; the head, or -1.
+__device__ __noinline__ int32_t split_out_of_line(Ptrs P, uint32_t* state, int32_t x, int32_t k, uint32_t* coff,
+                                                  uint32_t* err, int64_t* fail) {
+  St s = load_st_lds(state);
+  NodeRec nh;
+  nh.coff = 0;
+  const int32_t fh = s.free_head;
+  uint32_t fh_next = 0;
+  if (fh >= 0) fh_next = uni(P.nodes[fh].off);
+  const int32_t hd = split_for_leaf(P, s, x, load_node(P.nodes, x), k, fh, fh_next, nh);
+  wave_mem_sync();
+  store_st_lds(state, s);
+  *coff = nh.coff;
+  *err = s.err;
+  fail[0] = s.dbg_check;
+  fail[1] = s.dbg_val[0];
+  fail[2] = s.dbg_val[1];
+  fail[3] = s.dbg_val[2];
+  return hd;
+}
+
+// Where an insertion's cached part ends: entry e of the trail (-1: at the root),
+// node `last`, whose edge starts at `start`; and what the load needs from memory
+// in one read (lanes 0-7: that node's record, lane 8: the free list's next
+// entry).
+struct LeafPlace {
+  int32_t count, e, last, start, end, fh;
+  int32_t words;
+};
+
+__device__ __forceinline__ LeafPlace find_place(const Ptrs& P, const uint32_t* state, const int32_t* t, int32_t h) {
+  LeafPlace w;
+  const TrailView v = view_trail(t);
+  w.fh = uni((int32_t)state[4]);
+  w.count = v.count;
+  w.e = -1;
+  w.last = w.start = w.end = 0;
+  if (h > 0 && v.count <= kPathMax) {
+    w.e = v.at(h);
+    if (w.e >= 0) {
+      w.last = v.node(w.e);
+      w.start = v.start(w.e);
+      w.end = v.end(w.e);
+    }
+  }
+  const bool fl = lane_id() >= 8 && w.fh >= 0;
+  const int32_t* p = reinterpret_cast<const int32_t*>(P.nodes + (fl ? w.fh : w.last));
+  w.words = p[fl ? 1 : (lane_id() & 7)];
+  return w;
+}
+
+// The load of the planned insertion of q[0, job.L) (in LDS) into the worker's
+// cache (job.h = LCP(q, cache), t = the trail of that match, s = the worker's
+// state, of which `state` holds a copy): the split of the edge the match ends in
+// and q[h, L) as one new leaf.  t then holds q's trail in the updated cache.
+// The marks, the leaf list and the evictions are left, except that a path too
+// deep for a trail is marked here.  Fills job's l, a, tok, replace and marked;
+// split = the node whose edge was split (its head is job.a), or 0.  KVR_DEV_*
+// bits (0: done).
+__device__ __forceinline__ uint32_t load_leaf(const Ptrs& P, St& s, uint32_t* state, uint32_t B, const int32_t* q,
+                                              int32_t* t, PipeJob& job, int32_t& split) {
+  const int32_t h = job.h, L = job.L;
+  const LeafPlace w = find_place(P, state, t, h);
+  int32_t last = w.last, start = w.start;
+  bool read = true;  // w.words are of the node the leaf hangs from
+  split = 0;
+  if (h > 0 && w.count <= kPathMax && (w.e < 0 || w.end < h || last <= 0 || (uint32_t)last >= s.hwm)) {
+    KVR_FAIL_CHECK(s, 1, w.e, h, last);
+    return s.err;
+  }
+  const uint32_t nload = (uint32_t)(L - h);
+  job.l = job.a = job.tok = 0;
+  job.replace = job.marked = 0;
+  int32_t pc = w.count <= kPathMax ? w.e + 1 : kPathMax + 1;
+  if (h > 0 && (pc > kPathMax || (pc == kPathMax && h < L))) {
+    // no trail, or none after this insertion
+    int64_t fail[4];
+    int32_t at = 0;
+    last = uni(mark_by_lookup(P, state, B, q, h, &at, fail));
+    start = uni(at);
+    s = load_st_lds(state);
+    if (last < 0) {
+      KVR_FAIL_CHECK(s, (int32_t)fail[0], fail[1], fail[2], fail[3]);
       return s.err;
     }
-  }
-  job.h = h;
-  job.L = L;
-  job.l = job.a = job.tok = 0;
-  split = 0;
-  job.replace = job.marked = 0;
-  job.nfree = B - s.size;
-  const uint32_t nload = (uint32_t)(L - h);
-  job.nev = nload > job.nfree ? nload - job.nfree : 0u;
-  if (h > 0 && (have > kPathMax || (e + 1 == kPathMax && h < L))) {
-    // no trail, or none after this insertion: walk and mark by child lookups
-    const int32_t* ar = arena_of(P, s.arena_sel);
-    int32_t d = 0;
-    NodeRec nx = load_node(P.nodes, 0);
-    last = 0;
-    while (d < h) {
-      const int32_t c = child_find(ar, nx, uni(q[d]));
-      if (c <= 0 || (uint32_t)c >= s.hwm) {
-        KVR_FAIL_CHECK(s, 1, last, d, h);
-        return s.err;
-      }
-      nx = load_node(P.nodes, c);
-      const int32_t cov = nx.len < h - d ? nx.len : h - d;
-      if (cov <= 0) {
-        KVR_FAIL_CHECK(s, 2, c, nx.len, d);
-        return s.err;
-      }
-      mark_edge(P, s, B, c, nx, cov, nx.nchild == 0);
-      last = c;
-      start = d;
-      d += cov;
-    }
-    wave_mem_sync();  // the marks above are read again below
-    have = kPathMax + 1;
+    pc = kPathMax + 1;
+    read = false;
     job.marked = 1;
   }
-  const uint32_t join = job.marked ? nload : (uint32_t)L;  // tokens that may join the marking set
-  job.phase = s.phase;
-  job.calm = (uint64_t)s.cnt + join <= B && (uint64_t)s.size >= (uint64_t)s.cnt + (join - nload) + job.nev + maxL;
-  int32_t pc = have <= kPathMax ? e + 1 : kPathMax + 1;
   if (h < L) {
-    const NodeRec lr = load_node(P.nodes, last);
-    // the free list's next entry, read before the stores below
-    const int32_t fh = s.free_head;
-    uint32_t fh_next = 0;
-    if (fh >= 0) fh_next = uni(P.nodes[fh].off);
-    const int32_t cov = h - start;
-    int32_t a = last, fl = fh;
+    int32_t len, known[3];
+    int32_t fh = w.fh;
+    uint32_t fh_next;
+    if (KVR_WAVE == 1 || !read) {
+      const NodeRec lr = load_node(P.nodes, last);
+      len = lr.len;
+      known[0] = lr.nchild;
+      known[1] = lr.ccap;
+      known[2] = (int32_t)lr.coff;
+      fh_next = fh >= 0 ? uni(P.nodes[fh].off) : 0u;
+    } else {
+      len = __builtin_amdgcn_readlane(w.words, 2);
+      known[0] = __builtin_amdgcn_readlane(w.words, 3);
+      known[2] = __builtin_amdgcn_readlane(w.words, 4);
+      known[1] = __builtin_amdgcn_readlane(w.words, 5);
+      fh_next = (uint32_t)__builtin_amdgcn_readlane(w.words, KVR_WAVE == 1 ? 0 : 8);
+    }
+    int32_t a = last;
     uint32_t sel = s.arena_sel;
-    int32_t known[3] = {lr.nchild, lr.ccap, (int32_t)lr.coff};
-    if (last != 0 && cov < lr.len) {
-      NodeRec nh;
-      a = split_for_leaf(P, s, last, lr, cov, fh, fh_next, nh);
-      if (a < 0) return s.err ? s.err : (uint32_t)KVR_DEV_INTERNAL;
-      split = last;
-      fl = -1;
-      sel = s.arena_sel;
-      known[0] = nh.nchild;
-      known[1] = nh.ccap;
-      known[2] = (int32_t)nh.coff;
+    if (last != 0 && h - start < len) {
+      int64_t fail[4];
+      uint32_t coff, err;
+      store_st_lds(state, s);
       wave_mem_sync();
-      if (pc <= kPathMax && lane_id() == 0) trail_node(t)[pc - 1] = a;
+      a = uni(split_out_of_line(P, state, last, h - start, &coff, &err, fail));
+      s = load_st_lds(state);
+      if (a < 0) {
+        s.err = uni(err) ? uni(err) : (uint32_t)KVR_DEV_INTERNAL;
+        s.dbg_check = (int32_t)fail[0];
+        s.dbg_val[0] = fail[1];
+        s.dbg_val[1] = fail[2];
+        s.dbg_val[2] = fail[3];
+        return s.err;
+      }
+      split = last;
+      fh = -1;
+      sel = s.arena_sel;
+      known[0] = 1;
+      known[1] = 2;
+      known[2] = (int32_t)uni(coff);
     }
     // the walked part ends here (its last entry may have ended deeper: a split
     // edge, or one trimmed since)
-    if (pc > 0 && pc <= kPathMax && lane_id() == 0) trail_end(t)[pc - 1] = h;
+    if (pc > 0 && pc <= kPathMax && lane_id() == 0) {
+      trail_node(t)[pc - 1] = a;
+      trail_end(t)[pc - 1] = h;
+    }
     job.replace = a != 0 && known[0] == 0;
     uint32_t eoff;
     if (!place_edge(P, s, nload, (uint32_t)h, eoff)) return s.err;
     // no fence: nothing reads the new edge's words before the fence that
     // ends this half (a collection fences first)
     copy_words(arena_of(P, s.arena_sel), eoff, q, h, (int32_t)nload);
-    const int32_t l = take_node(P, s, fl, fh_next);
+    const int32_t l = take_node(P, s, fh, fh_next);
     if (l < 0) return s.err;
     if (lane_id() == 0) {
       NodeRec nl;
@@ -525,7 +644,7 @@ __device__ __forceinline__ uint32_t load_leaf(const Ptrs& P, St& s, uint32_t B, 
   return 0;
 }
 
-// ---------------------------------------------------------------- insertion, second half
+// ---------------------------------------------------------------- insertion, after the load
 
 // The marking walk over the cached part of the path, along its trail in the
 // updated tree (the records of all its nodes loaded at once, one lane each).
@@ -551,9 +670,8 @@ __device__ __forceinline__ void mark_cached(const Ptrs& P, St& s, uint32_t B, co
   wave_mem_sync();  // the marks above are read again below
 }
 
-// Is a match of query m on the worker of an insertion (of query job.k < m),
-// taken after that insertion's load and before its evictions end, the match
-// that the evictions leave?  They only remove tokens, so it never grows; it is
+// Is a match of query m on the worker of an insertion (of query job.k < m), taken
+// before its evictions end, the match that they leave?  They only remove tokens, so it never grows; it is
 // as long as it was while its last token stays:
 //   * a token of the inserted path stays (that path's leaf is no candidate,
 //     and an eviction takes leaf tokens only): h <= on_path, a lower bound of the
@@ -578,74 +696,85 @@ __device__ __forceinline__ bool match_stays(const NodeRec* nodes, const PipeJob&
   return uni((uint32_t)m) == job.phase && uni((int32_t)(m >> 32)) >= me.pos;
 }
 
-// The match of the next query on the worker of an insertion, after its load,
-// from the match taken before it (h_pre and its trail in tn; tk = the trail of
-// the inserted query, ell = LCP of the two queries).  The load adds the
-// inserted path's prefixes only, so h = max(h_pre, ell) and no node is read:
-// where the next query leaves the inserted path, that path's trail up to
-// there is its trail; else its own stands, with the head of the split edge
-// (which both pass, as then ell is the depth of the split) in front of it.
+// What the routing wave knows of the insertion of a path of L tokens with h
+// cached into a worker with this state (which nothing changes until the load).
+__device__ __forceinline__ void plan_insertion(PipeJob& job, const uint32_t* state, uint32_t B, uint32_t maxL, int32_t h,
+                                               int32_t L) {
+  const uint32_t phase = uni(state[0]), cnt = uni(state[1]), size = uni(state[2]);
+  const uint32_t nload = (uint32_t)(L - h);
+  job.h = h;
+  job.L = L;
+  job.nfree = B - size;
+  job.nev = nload > job.nfree ? nload - job.nfree : 0u;
+  job.phase = phase;
+  job.calm = (uint64_t)cnt + (uint32_t)L <= B && (uint64_t)size >= (uint64_t)cnt + (uint32_t)h + job.nev + maxL;
+}
+
+// The match of the next query on the worker of an insertion that has been
+// planned but not loaded, from the match taken on the tree as it is (h_pre, its
+// trail in tn; ell = LCP of the two queries).  The load adds the inserted path's
+// prefixes only, so h = max(h_pre, ell) and the tree need not be walked again;
 // `stays` as match_stays says.
-__device__ __forceinline__ int32_t match_after_load(const NodeRec* nodes, const PipeJob& job, int32_t split,
-                                                    int32_t h_pre, int32_t ell, const int32_t* tk, int32_t* tn,
-                                                    bool& stays) {
+__device__ __forceinline__ int32_t match_before_load(const NodeRec* nodes, const PipeJob& job, int32_t h_pre,
+                                                     int32_t ell, const int32_t* tn, bool& stays) {
   stays = true;
-  if (h_pre <= ell) {
-    const int32_t have = uni(tk[0]);
-    int32_t pc = have;
-    if (have <= kPathMax) {
-      int32_t x, st, en;
-      pc = ell > 0 ? trail_at(tk, have, ell, x, st, en) + 1 : 0;
-      for (int32_t k = lane_id(); k < pc; k += KVR_WAVE) {
-        const int32_t n = trail_node(tk)[k], e = trail_end(tk)[k];
-        trail_node(tn)[k] = n;
-        trail_end(tn)[k] = e;
-      }
-    }
-    if (lane_id() == 0) tn[0] = pc;
-    return ell;
-  }
-  int32_t have = uni(tn[0]);
+  if (h_pre <= ell) return ell;
+  if (job.nev == 0) return h_pre;
   MatchEnd me{0, 0};
-  if (have > 0 && have <= kPathMax) {
-    if (split > 0) {
-      int32_t at = -1;
-      for (int32_t k = 0; k < have; k += KVR_WAVE) {
-        const uint64_t m = __ballot(k + lane_id() < have && trail_node(tn)[k + lane_id()] == split);
-        if (m) at = k + first_lane(m);
-      }
-      if (at >= 0 && have == kPathMax) {
-        have = kPathMax + 1;
-      } else if (at >= 0) {
-        // entries from `at` on move up by one (from the top, a word per lane)
-        for (int32_t b = have - 1; b >= at; b -= KVR_WAVE) {
-          const int32_t k = b - lane_id();
-          int32_t n = 0, e = 0;
-          if (k >= at) {
-            n = trail_node(tn)[k];
-            e = trail_end(tn)[k];
-          }
-          __builtin_amdgcn_wave_barrier();
-          if (k >= at) {
-            trail_node(tn)[k + 1] = n;
-            trail_end(tn)[k + 1] = e;
-          }
-        }
-        if (lane_id() == 0) {
-          trail_node(tn)[at] = job.a;
-          trail_end(tn)[at] = job.h;
-        }
-        have += 1;
-      }
-      if (lane_id() == 0) tn[0] = have;
-    }
-    if (have <= kPathMax) {
-      me.node = uni(trail_node(tn)[have - 1]);
-      me.pos = h_pre - (have > 1 ? uni(trail_end(tn)[have - 2]) : 0);
-    }
+  const TrailView v = view_trail(tn);
+  if (v.count > 0 && v.count <= kPathMax) {
+    me.node = v.node(v.count - 1);
+    me.pos = h_pre - v.start(v.count - 1);
   }
   stays = match_stays(nodes, job, h_pre, ell, true, me);
   return h_pre;
+}
+
+// That match's trail after the load (tk = the trail of the inserted query):
+// where the next query leaves the inserted path, that path's trail up to there;
+// else its own, with the head of the split edge (which both pass, as then ell is
+// the depth of the split) in front of the split node.
+__device__ __forceinline__ void trail_after_load(const PipeJob& job, int32_t split, int32_t h_pre, int32_t ell,
+                                                 const int32_t* tk, int32_t* tn) {
+  if (h_pre <= ell) {
+    const TrailView k = view_trail(tk);
+    int32_t pc = k.count;
+    if (pc <= kPathMax) {
+      pc = ell > 0 ? k.at(ell) + 1 : 0;
+      k.copy_to(tn, pc);
+    }
+    if (lane_id() == 0) tn[0] = pc;
+    return;
+  }
+  if (split <= 0) return;
+  const TrailView v = view_trail(tn);
+  if (v.count > kPathMax) return;
+  int32_t at = -1;
+  if (KVR_WAVE == 1) {
+    for (int32_t e = 0; e < v.count; ++e)
+      if (v.node(e) == split) at = e;
+  } else {
+    const uint64_t m = __ballot(lane_id() < v.count && v.vnode == split);
+    if (m) at = first_lane(m);
+  }
+  if (at < 0) return;
+  if (v.count < kPathMax) {
+    // entries from `at` on move up by one
+    if (KVR_WAVE == 1) {
+      for (int32_t e = v.count - 1; e >= at; --e) {
+        tn[1 + e + 1] = v.node(e);
+        tn[1 + kPathMax + e + 1] = v.end(e);
+      }
+    } else if (lane_id() >= at && lane_id() < v.count) {
+      tn[1 + lane_id() + 1] = v.vnode;
+      tn[1 + kPathMax + lane_id() + 1] = v.vend;
+    }
+    if (lane_id() == 0) {
+      trail_node(tn)[at] = job.a;
+      trail_end(tn)[at] = job.h;
+    }
+  }
+  if (lane_id() == 0) tn[0] = v.count + 1;  // (kPathMax + 1 is "unknown")
 }
 
 // Rank in the leaf list of the leaf that an insertion added (its entry still

@@ -120,8 +120,8 @@ extern "C" int emul_ahead(const kvr_config* cfg, uint64_t n, const int32_t* toke
     std::vector<uint32_t> rw;
     std::vector<St> after_marks(W);
     auto marks = [&](PipeJob& job) {
-      if (job.pad) return;
-      job.pad = 1;
+      if (job.pre) return;  // (a flag of this replay)
+      job.pre = 1;
       after_marks[job.worker] = load_st_lds(&tree[job.worker * kStWords]);
       if (!job.marked)
         mark_cached(worker_ptrs(ws, L, r, job.worker), after_marks[job.worker], B, job, trail_of(job.k, job.worker));
@@ -209,24 +209,32 @@ extern "C" int emul_ahead(const kvr_config* cfg, uint64_t n, const int32_t* toke
           ++x;
         }
       }
-      // first half
-      St s = load_st_lds(&tree[best * kStWords]);
+      // the insertion as planned before its load, and what it makes of a match of
+      // q_k+1 taken on the tree as it is
       PipeJob job{};
-      int32_t split;
-      err = load_leaf(P, s, B, L.maxL, qbuf(k), len(k), h[cur][best], trail_of(k, best), job, split);
-      store_st_lds(&tree[best * kStWords], s);
-      if (err) return (int)err;
+      uint32_t* state = &tree[best * kStWords];
+      plan_insertion(job, state, B, L.maxL, h[cur][best], len(k));
       job.k = (uint32_t)k;
       job.worker = best;
+      bool stays = false;
+      int32_t h_pre = 0, ha = 0;
+      const bool pre = k + 1 < n && ahead[best];
+      if (pre) {
+        h_pre = h[cur ^ 1][best];
+        ha = match_before_load(P.nodes, job, h_pre, lcp(k), trail_of(k + 1, best), stays);
+      }
+      // the load
+      St s = load_st_lds(state);
+      int32_t split;
+      err = load_leaf(P, s, state, B, qbuf(k), trail_of(k, best), job, split);
+      store_st_lds(state, s);
+      if (err) return (int)err;
       if (h[cur][best] == 0) rf_add(&rootf[best * kRootFilterWords], job.tok);
       h[cur][best] = len(k);
       open.push_back(job);
       ahead2[best] = false;
-      if (k + 1 < n && ahead[best]) {
-        // q_k+1 was matched here before the load
-        bool stays;
-        const int32_t ha = match_after_load(P.nodes, job, split, h[cur ^ 1][best], lcp(k), trail_of(k, best),
-                                            trail_of(k + 1, best), stays);
+      if (pre) {
+        trail_after_load(job, split, h_pre, lcp(k), trail_of(k, best), trail_of(k + 1, best));
         const std::vector<int32_t> ta(trail_of(k + 1, best), trail_of(k + 1, best) + kTrailWords);
         const int32_t hw = match(k + 1, best, len(k), ended, me);
         if (ha != hw) return -9;
