@@ -1,0 +1,73 @@
+"""The pipelined step kernel where its forms change, bit-exact against the
+oracle on an MI355X: 12 or 16 waves (at 24 workers), two, three or four query
+buffers (by the LDS that max_query_tokens leaves), a ring of draw words that
+holds no whole insertion, the learned router's form or the baselines', and
+batches checked by the step kernel itself or by kernels before it."""
+import numpy as np
+import pytest
+
+import paper_2601_18999_amd as K
+from gpu_helpers import assert_parity, gpu_run, note
+from workload import generate, small_spec
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("router", ["lbgr", "cache_aware"])
+@pytest.mark.parametrize("W,max_len", [
+    (1, 4000),              # one worker: every query is routed to it
+    (23, 900), (24, 900),   # 12 and 16 waves
+    (4, 5848), (4, 5860),   # four and three query buffers
+    (4, 7044), (4, 7056),   # three and two
+    (64, 16384),            # two, and no room for draw words or candidates
+])
+def test_forms_of_the_pipelined_kernel(W, max_len, router):
+    s = generate(small_spec(n=260, groups=5, prefix_len=(1, 500), suffix_len=(1, 300), vocab=9, seed=W + max_len))
+    B = max(max_len, 1000)
+    if max_len < 2000:
+        B = max_len + 37  # evictions from the first queries on
+    note(f"W={W} max_len={max_len} router={router}")
+    R = {"lbgr": K.KVR_ROUTE_LBGR, "cache_aware": K.KVR_ROUTE_CACHE_AWARE}[router]
+    res, stats = gpu_run(s, 2, W, B, batch=61, max_len=max_len, router=R)
+    assert_parity(s, res, stats, W, B, range(2), router=router)
+
+
+@pytest.mark.parametrize("batch", [31, 32, 33, 255, 256, 257])
+@pytest.mark.parametrize("max_len", [31, 32, 256])
+def test_batches_either_side_of_the_check_in_the_step_kernel(batch, max_len):
+    """At most 256 queries and 8,192 tokens are checked by the step kernel."""
+    s = generate(small_spec(n=520, groups=6, prefix_len=(1, 20), suffix_len=(1, 11), vocab=5, seed=batch))
+    note(f"batch={batch} max_len={max_len}")
+    res, stats = gpu_run(s, 3, 3, 300, batch=batch, max_len=max_len)
+    assert_parity(s, res, stats, 3, 300, range(3))
+
+
+@pytest.mark.parametrize("n", [5, 256, 257])
+@pytest.mark.parametrize("fault", ["length", "arrival", "token"])
+def test_an_invalid_batch_changes_nothing_on_either_path(n, fault):
+    """The last query of the second batch is wrong: the batch is refused, with
+    the same bits, and the first batch's results stay."""
+    s = generate(small_spec(n=2 * n, groups=4, prefix_len=(2, 12), suffix_len=(2, 9), vocab=5, seed=n))
+    if fault == "length":
+        max_len = int(np.diff(s.offsets)[:-1].max())
+        s.offsets = s.offsets.copy()
+        extra = np.zeros(40, np.int32)
+        s.tokens = np.concatenate([s.tokens, extra])
+        s.offsets[-1] += 40
+    else:
+        max_len = s.max_len
+        if fault == "arrival":
+            s.arrival_us = s.arrival_us.copy()
+            s.arrival_us[-1] = s.arrival_us[-2] - 1
+        else:
+            s.tokens = s.tokens.copy()
+            s.tokens[-1] = -3
+    sim = K.Simulator(2, 3, 200, max_len)
+    try:
+        sim.run(s, batch=n)
+        st, bits = sim.check()
+        stats = sim.stats(check=False)
+    finally:
+        sim.close()
+    assert st != K.KVR_OK and bits == {"length": 1, "token": 2, "arrival": 4}[fault], (st, bits)
+    assert all(sum(stats[r][i]["routed"] for i in range(3)) == n for r in range(2))
