@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Dict, List, Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -186,21 +187,19 @@ def kvr_route_batch(ctx: int, n: int, d_tokens: int, d_offsets: int, d_arrival_u
            "kvr_route_batch")
 
 
+# A worker's record as struct reads it, and the keys of its dict, in order; the
+# four words of theta follow load_est.
+_WORKER_KEYS = STAT_U64 + ["backlog_us", "last_decay_us", "load_est", "theta", "nodes", "gc_runs"] + ROUTER_U64
+_WORKER_RECORD = struct.Struct("<19Q2qd4d2Q4Q")
+assert _WORKER_RECORD.size == ctypes.sizeof(KvrWorkerStats)
+
+
 def _stats_dicts(arr, n: int) -> List[Dict]:
-    out = []
-    for k in range(n):
-        s = arr[k]
-        d = {name: int(getattr(s, name)) for name in STAT_U64}
-        d["backlog_us"] = int(s.backlog_us)
-        d["last_decay_us"] = int(s.last_decay_us)
-        d["load_est"] = float(s.load_est)
-        d["theta"] = [float(x) for x in s.theta]
-        d["nodes"] = int(s.nodes)
-        d["gc_runs"] = int(s.gc_runs)
-        for name in ROUTER_U64:
-            d[name] = int(getattr(s, name))
-        out.append(d)
-    return out
+    # one unpack a record: reading the fields one by one through ctypes takes
+    # most of a kvr_stats call over many workers
+    at = len(STAT_U64) + 3
+    return [dict(zip(_WORKER_KEYS, (*v[:at], [*v[at:at + 4]], *v[at + 4:])))
+            for v in _WORKER_RECORD.iter_unpack(memoryview(arr).cast("B")[:n * _WORKER_RECORD.size])]
 
 
 def _replica_dicts(arr, n: int) -> List[Dict]:
