@@ -77,11 +77,6 @@ __device__ __forceinline__ void count_matched(const Ptrs& P, int32_t h, int32_t*
 constexpr uint32_t kQueryPad = 4;
 __host__ __device__ constexpr uint32_t query_words(uint32_t maxL) { return ((maxL + 3u) & ~3u) + 2u * kQueryPad; }
 
-// The buffer of query k (nbuf = 2, 3 or 4).
-__device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) {
-  return nbuf == 3u ? k % 3u : k & (nbuf - 1u);
-}
-
 // Stage q_next[0, Ln) (threads t0, t0 + stride, ...) and fold each thread's
 // first position where it differs from q_cur into *ell (LDS minimum), so
 // that once all have staged, *ell = LCP(q_cur, q_next).  The stream is read in
@@ -634,22 +629,10 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
 // queries, match, compute draw words, rank new leaves and apply completions and
 // decay, whichever is due first.
 //
-// A worker's matches and insertions are ordered by its state word: the number
-// of queries matched on it, and below it five flags.  A wave takes the match of
-// query m by exchanging (m, no reader) for (m, reader), so each match is taken
-// once and in order.  The routing wave sets the owner flag and waits for a
-// reader before it hands the insertion over; once the leaf is loaded (loaded
-// flag), matches go on beside the evictions: the next query's at once, later ones after the
-// marks (marked flag), which read the trail that the match after the next
-// writes.  One that the evictions could still change is put off (deferred
-// flag) until they end and the owner's flags are cleared.
-// Waves synchronise through these words and the counters below (LDS,
+// The order of a worker's matches and insertions: kvr_trail.h.  Waves
+// synchronise through the workers' state words and the counters below (LDS,
 // workgroup scope, release/acquire); every wait is bounded and sees the stop
 // flag, so an error ends every loop.
-
-constexpr uint32_t kReader = 1u, kOwner = 2u, kLoaded = 4u, kMarked = 8u, kDeferred = 16u;
-constexpr uint32_t kCountShift = 5;
-constexpr uint32_t kCountMask = 0x7ffffffu;  // counts are compared modulo 2^27
 
 struct PipeFlags {
   uint32_t routed;   // queries routed
@@ -675,8 +658,6 @@ static_assert(sizeof(PipeFlags) == 4 * kFlagWords + 32, "counters, then the erro
 #endif
 constexpr int kPipeMatchUnroll = KVR_PIPE_MATCH_UNROLL;
 constexpr uint32_t kSpinLimit = 1u << 24;
-// insertions between routing and the end of their evictions, at most
-constexpr uint32_t kJobs = 8;
 // Waves per workgroup: 12 (three per SIMD, 168 registers a lane; against 8,
 // multi-turn 51.0 ms a simulation instead of 55.3, the paper's groups in
 // round-robin order 67.9 instead of 77.8, the rest within 3%), and 16 for
@@ -793,20 +774,6 @@ struct PipeHook {
   }
   __device__ __forceinline__ void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
 };
-
-// May the match of query m be taken on a worker in this state, owned (if so)
-// by the insertion of query k?  (nbuf: how many queries have a trail.)
-__device__ __forceinline__ bool can_match(uint32_t sv, uint32_t m, uint32_t k, uint32_t nbuf) {
-  const uint32_t c = m << kCountShift;
-  return sv == c || sv == (c | kOwner | kLoaded | kMarked) || (sv == (c | kOwner | kLoaded) && m - k < nbuf);
-}
-
-// Take the match that state sv allows; false when another wave was first.
-__device__ __forceinline__ bool claim_match(uint32_t* st, uint32_t sv) {
-  uint32_t old = 0;
-  if (lane_id() == 0) old = atomicCAS(st, sv, sv | kReader);
-  return uni(old) == sv;
-}
 
 // NW waves, NE of them evicting; kLbgr: the learned router only (the baselines'
 // code would lengthen every step).
@@ -937,41 +904,21 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
     tick_prev = tick;
     st_rel(&f.decayed, 1u);
   }
-  // Take the (claimed) match of query mm on worker mw, whose state was msv.
-  const auto match_one = [&](uint32_t mm, uint32_t mw, uint32_t msv) __attribute__((always_inline)) {
-    const uint32_t mp = query_slot(mm, a.nbuf), mq = query_slot(mm + a.nbuf - 1u, a.nbuf);  // its slot, the last one's
-    const int32_t h_old = uni(h_sh[mq][mw]);
-    const int32_t ell = mm > 0u ? uni(ell_sh[(mm - 1u) & 7u]) : 0;
-    const Ptrs P = worker_ptrs(a.ws, a.L, r, mw);
-    MatchEnd me{};
-    bool walked = false;
-    const int32_t h = match_ahead<kPipeMatchUnroll>(
-        P.nodes, arena_of(P, uni(tree_sh[mw * kStWords + 12])), rootf + mw * kRootFilterWords, P.A,
-        smem + mp * qwords + kQueryPad, uni(len_sh[mm & 7u]), h_old, ell,
-        trail_sh + (mq * W + mw) * kTrailWords, trail_sh + (mp * W + mw) * kTrailWords, walked, me);
-    bool stays = true;
-    if (msv & kOwner) {
-      // beside the evictions of an earlier query's insertion: this match
-      // and the inserted path agree at least up to the LCPs in between
-      const uint32_t jk = uni(owner_sh[mw]);
-      int32_t on_path = jk + 1u == mm ? ell : 0;
-      if (jk + 2u == mm) {
-        const int32_t e0 = uni(ell_sh[jk & 7u]);
-        on_path = e0 < ell ? e0 : ell;
-      }
-      stays = match_stays(P.nodes, load_job(&job_sh[jk % kJobs]), h, on_path, walked, me);
-    }
-    if (stays && lane == 0) {
-      h_sh[mp][mw] = h;
-      atomicAdd(&mtok_sh[mw], (unsigned long long)(uint32_t)h);
-    }
-    if (stays) {  // one more query matched, and no reader
-      add_rel(&st_sh[mw], (1u << kCountShift) - kReader);
-    } else if (lane == 0) {
-      // put off until the owner is done, or to be taken again if it just was
-      if (atomicCAS(&st_sh[mw], msv | kReader, msv | kDeferred) != (msv | kReader)) atomicAnd(&st_sh[mw], ~kReader);
-    }
-  };
+  MatchArea ma;
+  ma.W = W;
+  ma.nbuf = a.nbuf;
+  ma.q = smem + kQueryPad;
+  ma.qstride = qwords;
+  ma.len = len_sh;
+  ma.ell = ell_sh;
+  ma.h = &h_sh[0][0];
+  ma.trail = trail_sh;
+  ma.tree = tree_sh;
+  ma.rootf = rootf;
+  ma.state = st_sh;
+  ma.owner = owner_sh;
+  ma.jobs = job_sh;
+  ma.mtok = mtok_sh;
 
   if (wave == 0) {
     for (;;) {
@@ -1164,7 +1111,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           continue;
         }
       }
-      match_one(mm, mw, msv);
+      take_match<kPipeMatchUnroll>(ma, worker_ptrs(a.ws, a.L, r, mw), mm, mw, msv);
       clock_mark<PT>(&clk, KVR_PHASE_MATCH);
     }
   } else if (wave <= NE) {
@@ -1456,7 +1403,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
         if (!pipe_poll(spins, &f, routed, 9)) continue;  // (the duties of routed queries first)
         continue;
       }
-      match_one(mm, mw, msv);
+      take_match<kPipeMatchUnroll>(ma, worker_ptrs(a.ws, a.L, r, mw), mm, mw, msv);
       clock_mark<PT>(&clk, KVR_PHASE_H_MATCH);
     }
   }

@@ -101,6 +101,11 @@ __device__ __forceinline__ bool rf_may(const uint32_t* rf, int32_t t) {
   return ((rf[rf_bit1(t) >> 5] >> (rf_bit1(t) & 31u)) & 1u) && ((rf[rf_bit2(t) >> 5] >> (rf_bit2(t) & 31u)) & 1u);
 }
 
+// The buffer of query k (nbuf = 2, 3 or 4).
+__device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) {
+  return nbuf == 3u ? k % 3u : k & (nbuf - 1u);
+}
+
 // ---------------------------------------------------------------- trails
 // The trail of a match: the nodes it entered, [0] = their number (kPathMax + 1
 // when there were more or they are unknown), then the nodes, then the depth
@@ -694,6 +699,101 @@ __device__ __forceinline__ bool match_stays(const NodeRec* nodes, const PipeJob&
   const uint64_t m = __hip_atomic_load(reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(nodes + me.node) + offsetof(NodeRec, mphase)), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
   return uni((uint32_t)m) == job.phase && uni((int32_t)(m >> 32)) >= me.pos;
+}
+
+// ---------------------------------------------------------------- the order of matches and insertions
+// A worker's matches and insertions are ordered by its state word: the number
+// of queries matched on it, and below it five flags.  A wave takes the match of
+// query m by exchanging (m, no reader) for (m, reader), so each match is taken
+// once and in order.  The routing wave sets the owner flag and waits for a
+// reader before it hands the insertion over; once the leaf is loaded (loaded
+// flag), matches go on beside the evictions: the next query's at once, later ones after the
+// marks (marked flag), which read the trail that the match after the next
+// writes.  One that the evictions could still change is put off (deferred
+// flag) until they end and the owner's flags are cleared.
+
+constexpr uint32_t kReader = 1u, kOwner = 2u, kLoaded = 4u, kMarked = 8u, kDeferred = 16u;
+constexpr uint32_t kCountShift = 5;
+constexpr uint32_t kCountMask = 0x7ffffffu;  // counts are compared modulo 2^27
+// Insertions between routing and the end of their evictions, at most:
+// insertion k has its record in slot k % kJobs.
+constexpr uint32_t kJobs = 8;
+
+// May the match of query m be taken on a worker in this state, owned (if so)
+// by the insertion of query k?  (nbuf: how many queries have a trail.)  Beside
+// an insertion, not for a query past k + kJobs: the match reads the insertion's
+// record when its walk is over, which may be after the evictions, and the slot
+// is written again when query k + kJobs is routed.  That needs this worker's
+// match of k + kJobs, which is taken after this one or is this one.
+__device__ __forceinline__ bool can_match(uint32_t sv, uint32_t m, uint32_t k, uint32_t nbuf) {
+  const uint32_t c = m << kCountShift;
+  if (sv == c) return true;
+  const uint32_t ahead = m - k;
+  return (sv == (c | kOwner | kLoaded | kMarked) && ahead <= kJobs) || (sv == (c | kOwner | kLoaded) && ahead < nbuf);
+}
+
+// Take the match that state sv allows; false when another wave was first.
+__device__ __forceinline__ bool claim_match(uint32_t* st, uint32_t sv) {
+  uint32_t old = 0;
+  if (lane_id() == 0) old = atomicCAS(st, sv, sv | kReader);
+  return uni(old) == sv;
+}
+
+// What matches read and write besides the trees (LDS).
+struct MatchArea {
+  uint32_t W, nbuf;
+  const int32_t* q;      // the first query buffer
+  uint32_t qstride;
+  const int32_t* len;    // length of q_k in slot k & 7
+  const int32_t* ell;    // LCP(q_k, q_k+1) in slot k & 7
+  int32_t* h;            // h of q_k on worker w at [query_slot(k) * kMaxWorkers + w]
+  int32_t* trail;        // [nbuf][W][kTrailWords]
+  const uint32_t* tree;  // kStWords per worker
+  const uint32_t* rootf;
+  uint32_t* state;       // state words
+  const uint32_t* owner; // the insertion that owns a worker
+  const PipeJob* jobs;
+  unsigned long long* mtok;  // matched tokens per worker
+};
+
+// Take the (claimed) match of query m on worker w (P), whose state was sv.
+template <int kU>
+__device__ __forceinline__ void take_match(const MatchArea& a, const Ptrs& P, uint32_t m, uint32_t w, uint32_t sv) {
+  const uint32_t mp = query_slot(m, a.nbuf), mq = query_slot(m + a.nbuf - 1u, a.nbuf);  // its slot, the last one's
+  int32_t* hp = a.h + mp * kMaxWorkers + w;
+  const int32_t h_old = uni(a.h[mq * kMaxWorkers + w]);
+  const int32_t ell = m > 0u ? uni(a.ell[(m - 1u) & 7u]) : 0;
+  MatchEnd me{};
+  bool walked = false;
+  const int32_t h = match_ahead<kU>(P.nodes, arena_of(P, uni(a.tree[w * kStWords + 12])), a.rootf + w * kRootFilterWords,
+                                    P.A, a.q + mp * a.qstride, uni(a.len[m & 7u]), h_old, ell,
+                                    a.trail + (mq * a.W + w) * kTrailWords, a.trail + (mp * a.W + w) * kTrailWords,
+                                    walked, me);
+  bool stays = true;
+  if (sv & kOwner) {
+    // beside the evictions of an earlier query's insertion: this match
+    // and the inserted path agree at least up to the LCPs in between
+    const uint32_t k = uni(a.owner[w]);
+    int32_t on_path = k + 1u == m ? ell : 0;
+    if (k + 2u == m) {
+      const int32_t e0 = uni(a.ell[k & 7u]);
+      on_path = e0 < ell ? e0 : ell;
+    }
+    stays = match_stays(P.nodes, load_job(&a.jobs[k % kJobs]), h, on_path, walked, me);
+  }
+  if (stays && lane_id() == 0) {
+    *hp = h;
+    atomicAdd(&a.mtok[w], (unsigned long long)(uint32_t)h);
+  }
+  uint32_t* st = &a.state[w];
+  if (stays) {  // one more query matched, and no reader
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane_id() == 0)
+      __hip_atomic_fetch_add(st, (1u << kCountShift) - kReader, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  } else if (lane_id() == 0) {
+    // put off until the owner is done, or to be taken again if it just was
+    if (atomicCAS(st, sv | kReader, sv | kDeferred) != (sv | kReader)) atomicAnd(st, ~kReader);
+  }
 }
 
 // What the routing wave knows of the insertion of a path of L tokens with h

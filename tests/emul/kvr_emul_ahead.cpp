@@ -7,9 +7,6 @@
 // taken at each step comes from a seeded generator.
 #include "emul_wave.h"
 
-inline unsigned atomicOr(unsigned* p, unsigned v) { unsigned o = *p; *p |= v; return o; }
-template <typename T> inline T __hip_atomic_fetch_max(T* p, T v, int, int) { T o = *p; if (v > o) *p = v; return o; }
-
 #include "../../paper_2601_18999_amd/csrc/kvr_trail.h"
 
 #include <cstring>

@@ -8,6 +8,7 @@ import pytest
 
 import paper_2601_18999_amd as K
 from gpu_helpers import assert_parity, gpu_run, note
+from streams import long_beside_short_stream
 from workload import generate, small_spec
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +72,15 @@ def test_an_invalid_batch_changes_nothing_on_either_path(n, fault):
         sim.close()
     assert st != K.KVR_OK and bits == {"length": 1, "token": 2, "arrival": 4}[fault], (st, bits)
     assert all(sum(stats[r][i]["routed"] for i in range(3)) == n for r in range(2))
+
+
+@pytest.mark.parametrize("B", [10600, 20000])
+def test_an_insertion_that_outlasts_the_next_seven(B):
+    """A prompt of 10,500 fresh tokens into a full cache, evicted while short
+    prompts of other workers come and go, and then prefixes of earlier long
+    prompts, matched beside those evictions."""
+    s = long_beside_short_stream(np.random.default_rng(B), 10, 12, 10500, 24)
+    note(f"B={B} max_len={s.max_len}")
+    res, stats = gpu_run(s, 4, 12, B, batch=500, router=K.KVR_ROUTE_ROUND_ROBIN)
+    assert sum(w["evictions"] for w in stats[0]) > 10500
+    assert_parity(s, res, stats, 12, B, range(4), router="round_robin")
