@@ -344,7 +344,8 @@ kvr_status kvr_route_batch(kvr_ctx* ctx, uint32_t n, const int32_t* d_tokens, co
   a.pipe = ctx->pipe;
   a.nbuf = ctx->nbuf;
   a.check = 0;
-  a.pad2 = 0;
+  a.part = 0;
+  a.rows = n;
   a.ucap = ctx->pipe ? ctx->ucap_p : ctx->ucap;
   a.rcap = ctx->pipe ? ctx->rcap_p : ctx->rcap;
   a.j0 = ctx->queries_done;

@@ -259,14 +259,17 @@ __device__ __forceinline__ uint32_t router_admit(const StepArgs& a, uint32_t r, 
 
 // Is the batch to be routed at all?  Called by a whole workgroup before it
 // changes anything, with bad, a word of its LDS, at 0; after the next barrier
-// `batch_ok` says.  The run must not have failed and, with a.check, the batch
+// `batch_ok` says.  The run must not have failed (a later part of a batch: this
+// replica must have routed the parts before it) and, with a.check, the batch
 // must be valid: lengths (with cached responses, a prompt of at least one token
 // before the response) and arrival order, which every wave looks at for
 // itself, and only then the tokens.  Every workgroup reads the same batch and
 // its replica's own last arrival, so all come to the same verdict.
 constexpr uint32_t kRunFailed = 1u << 31;
-__device__ __forceinline__ void check_batch(const StepArgs& a, GlobalHdr* g, int64_t tprev, uint32_t* bad) {
-  if (threadIdx.x == 0 && __atomic_load_n(&g->status, __ATOMIC_RELAXED)) atomicOr(bad, kRunFailed);
+__device__ __forceinline__ void check_batch(const StepArgs& a, GlobalHdr* g, const ReplicaHdr* rh, int64_t tprev,
+                                            uint32_t* bad) {
+  if (threadIdx.x == 0 && (a.part ? rh->failed || rh->queries != a.j0 : __atomic_load_n(&g->status, __ATOMIC_RELAXED)))
+    atomicOr(bad, kRunFailed);
   if (!a.check) return;
   uint32_t bits = 0;
   for (uint32_t j = (uint32_t)lane_id(); j < a.n; j += KVR_WAVE) {
@@ -368,7 +371,7 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
     ell_sh[0] = 0x7fffffff;
   }
   __syncthreads();
-  check_batch(a, g, rh->tprev, &abort_sh);
+  check_batch(a, g, rh, rh->tprev, &abort_sh);
   __syncthreads();
   if (!batch_ok(g, abort_sh)) return;
   // the replica's route digest and query count, kept by the routing wave
@@ -451,7 +454,7 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
         hins_sh = hins;
         next_sh = 0;
         rank_ready_sh = 0;
-        const uint64_t orow = (uint64_t)r * a.n + k;
+        const uint64_t orow = (uint64_t)r * a.rows + k;
         if (a.route) a.route[orow] = (int32_t)best;
         if (a.hits) a.hits[orow] = hb;
         if (!err) {
@@ -468,7 +471,7 @@ __global__ void __launch_bounds__(512) step_kernel(StepArgs a) {
         }
       }
       if (a.all_hits && (uint32_t)lane < W)
-        a.all_hits[((uint64_t)r * a.n + k) * W + (uint32_t)lane] = est[cur][lane];
+        a.all_hits[((uint64_t)r * a.rows + k) * W + (uint32_t)lane] = est[cur][lane];
       if (nh == 0 && has_next) stage_query<8>(a.tokens, n0, Ln, qn, qs, Lp, 0u, KVR_WAVE, &ell_sh[cur]);
     } else if (has_next) {
       stage_query<8>(a.tokens, n0, Ln, qn, qs, Lp, uni(wave - 1u) * KVR_WAVE, blockDim.x - KVR_WAVE, &ell_sh[cur]);
@@ -876,7 +879,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
     const int32_t* ar = arena_of(P, uni(P.hdr->arena_sel));
     for (int32_t c = lane; c < root.nchild; c += KVR_WAVE) rf_add(rootf + i * kRootFilterWords, ar[root.coff + 2 * c]);
   }
-  check_batch(a, g, tprev, &f.bad);
+  check_batch(a, g, rh, tprev, &f.bad);
   __syncthreads();
   if (!batch_ok(g, f.bad)) return;
 
@@ -1028,7 +1031,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           }
           if (err0) {
             if (lane == 0) {
-              const uint64_t orow = (uint64_t)r * n + k;
+              const uint64_t orow = (uint64_t)r * a.rows + k;
               if (a.route) a.route[orow] = (int32_t)best;
               if (a.hits) a.hits[orow] = hb;
             }
@@ -1279,7 +1282,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
           // its outputs, then completions and decay at the next arrival
           const uint32_t best = uni(best_sh[slot]);
           const int32_t hb = uni(hit_sh[slot]);
-          const uint64_t orow = (uint64_t)r * n + k;
+          const uint64_t orow = (uint64_t)r * a.rows + k;
           if (lane == 0) {
             if (a.route) a.route[orow] = (int32_t)best;
             if (a.hits) a.hits[orow] = hb;
@@ -1441,6 +1444,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
     if constexpr (PT)
       for (int p = KVR_PHASE_E_EVICT; p < KVR_PHASES; ++p) rh->phase_ticks[p] += eticks_sh[p];
     if (f.err) {
+      rh->failed = 1;
       if (atomicCAS(&g->err_taken, 0u, 1u) == 0u) {
         g->err_check = f.err_check;
         g->err_replica = r;
@@ -1483,7 +1487,8 @@ __global__ void init_kernel(char* ws, Layout L, double rls_p0) {
     h.queries = 0;
     h.route_digest = 0;
     for (int k = 0; k < KVR_PHASES; ++k) h.phase_ticks[k] = 0;
-    for (int k = 0; k < 12; ++k) h.pad[k] = 0;
+    h.failed = 0;
+    for (uint64_t& x : h.pad) x = 0;
     reinterpret_cast<ReplicaHdr*>(ws + L.off_rhdr)[tid] = h;
   }
   if (tid < RW) {
@@ -1592,6 +1597,33 @@ hipError_t launch_init(char* ws, const Layout& L, double rls_p0, hipStream_t st)
 constexpr uint64_t kCheckTokens = KVR_CHECK_TOKENS;
 constexpr uint32_t kCheckQueries = 256;  // (four rounds of a wave's lanes over their lengths)
 
+// A launch of the pipelined kernel takes at most this many queries: its counters
+// run up to (queries + 4) x helper waves in 32 bits, and a launch more costs
+// about 10 us, 0.1% of the time of this many steps.
+constexpr uint32_t kLaunchQueries = 2048;
+
+void launch_pipe(const StepArgs& a, size_t lds, hipStream_t st) {
+  const bool lbgr = a.C.router == KVR_ROUTE_LBGR;
+#define KVR_PIPE_LAUNCH(PT, NW, LB) \
+  hipLaunchKernelGGL((step_kernel_pipe<PT, NW, kPipeEvictors, LB>), dim3(a.L.R), dim3(64 * NW), lds, st, a)
+  if (a.L.W >= kPipeWideWorkers) {
+    if (a.C.phase_timers)
+      KVR_PIPE_LAUNCH(true, kPipeWavesWide, false);
+    else if (lbgr)
+      KVR_PIPE_LAUNCH(false, kPipeWavesWide, true);
+    else
+      KVR_PIPE_LAUNCH(false, kPipeWavesWide, false);
+  } else {
+    if (a.C.phase_timers)
+      KVR_PIPE_LAUNCH(true, kPipeWaves, false);
+    else if (lbgr)
+      KVR_PIPE_LAUNCH(false, kPipeWaves, true);
+    else
+      KVR_PIPE_LAUNCH(false, kPipeWaves, false);
+  }
+#undef KVR_PIPE_LAUNCH
+}
+
 hipError_t launch_step(const StepArgs& args, hipStream_t st) {
   StepArgs a = args;
   a.check = a.n <= kCheckQueries && (uint64_t)a.n * a.L.maxL <= kCheckTokens ? 1u : 0u;
@@ -1607,25 +1639,18 @@ hipError_t launch_step(const StepArgs& args, hipStream_t st) {
   const bool rt = a.L.has_router != 0, ba = a.L.beta > 1;
   if (a.pipe) {
     const size_t lds_p = step_lds_bytes_pipe(a.L.maxL, a.L.W, a.nbuf, a.ucap, a.rcap);
-    const bool lbgr = a.C.router == KVR_ROUTE_LBGR;
-#define KVR_PIPE_LAUNCH(PT, NW, LB) \
-  hipLaunchKernelGGL((step_kernel_pipe<PT, NW, kPipeEvictors, LB>), dim3(a.L.R), dim3(64 * NW), lds_p, st, a)
-    if (a.L.W >= kPipeWideWorkers) {
-      if (a.C.phase_timers)
-        KVR_PIPE_LAUNCH(true, kPipeWavesWide, false);
-      else if (lbgr)
-        KVR_PIPE_LAUNCH(false, kPipeWavesWide, true);
-      else
-        KVR_PIPE_LAUNCH(false, kPipeWavesWide, false);
-    } else {
-      if (a.C.phase_timers)
-        KVR_PIPE_LAUNCH(true, kPipeWaves, false);
-      else if (lbgr)
-        KVR_PIPE_LAUNCH(false, kPipeWaves, true);
-      else
-        KVR_PIPE_LAUNCH(false, kPipeWaves, false);
+    for (uint32_t k0 = 0; k0 < args.n; k0 += kLaunchQueries) {
+      a.n = args.n - k0 < kLaunchQueries ? args.n - k0 : kLaunchQueries;
+      a.offsets = args.offsets + k0;
+      a.arrival = args.arrival + k0;
+      a.out_len = args.out_len ? args.out_len + k0 : nullptr;
+      a.route = args.route ? args.route + k0 : nullptr;
+      a.hits = args.hits ? args.hits + k0 : nullptr;
+      a.all_hits = args.all_hits ? args.all_hits + (uint64_t)k0 * a.L.W : nullptr;
+      a.j0 = args.j0 + k0;
+      a.part = k0 > 0 ? 1u : 0u;
+      launch_pipe(a, lds_p, st);
     }
-#undef KVR_PIPE_LAUNCH
   } else if (rt && ba)
     hipLaunchKernelGGL((step_kernel<true, true, false>), dim3(a.L.R), dim3(64 * waves), lds, st, a);
   else if (rt)

@@ -101,7 +101,8 @@ struct ReplicaHdr {
   uint64_t queries;       // queries routed
   uint64_t route_digest;  // hash chain over (query index, route, hit), kvr_replica_stats
   uint64_t phase_ticks[KVR_PHASES];
-  uint64_t pad[11];
+  uint64_t failed;        // an error has stopped this replica
+  uint64_t pad[10];
 };
 static_assert(sizeof(ReplicaHdr) == 256, "replica header is 256 bytes");
 
@@ -159,14 +160,15 @@ struct StepArgs {
   int32_t* route;
   int32_t* hits;
   int32_t* all_hits;
-  uint32_t n;
+  uint32_t n;     // queries of this launch
   uint32_t ucap;  // candidate entries staged in LDS (0: U stays in global memory)
   uint32_t rcap;  // draw words precomputed in LDS: per insertion, or (pipelined kernel) the ring that insertions share
   uint64_t j0;
   uint32_t pipe;  // 1: the pipelined step kernel (separate evicting waves)
   uint32_t nbuf;  // its query buffers in LDS (2 to 4)
   uint32_t check; // 1: the step kernel checks the batch before it changes anything
-  uint32_t pad2;
+  uint32_t part;  // 1: not the first launch of its batch
+  uint32_t rows;  // queries per replica in the output arrays (n, or more when a batch is launched in parts)
 };
 
 inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }

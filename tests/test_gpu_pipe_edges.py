@@ -8,6 +8,7 @@ import pytest
 
 import paper_2601_18999_amd as K
 from gpu_helpers import assert_parity, gpu_run, note
+from oracle import oracle as O
 from streams import long_beside_short_stream
 from workload import generate, small_spec
 
@@ -84,3 +85,32 @@ def test_an_insertion_that_outlasts_the_next_seven(B):
     res, stats = gpu_run(s, 4, 12, B, batch=500, router=K.KVR_ROUTE_ROUND_ROBIN)
     assert sum(w["evictions"] for w in stats[0]) > 10500
     assert_parity(s, res, stats, 12, B, range(4), router="round_robin")
+
+
+@pytest.mark.parametrize("batch", [2048, 2049, 5000])
+def test_batches_launched_in_parts(batch):
+    """The pipelined kernel takes at most 2,048 queries a launch: the parts
+    follow one another as one batch, with its rows in the outputs."""
+    s = generate(small_spec(n=5000, groups=9, prefix_len=(1, 20), suffix_len=(1, 9), vocab=5, seed=batch))
+    note(f"batch={batch}")
+    res, stats = gpu_run(s, 3, 3, 300, batch=batch)
+    assert_parity(s, res, stats, 3, 300, range(3))
+
+
+def test_a_replica_that_fails_stops_no_other_in_later_parts():
+    """A completion ring one entry short of what the busiest replica needs: in one
+    batch of several parts the others finish it."""
+    s = generate(small_spec(n=5000, groups=9, prefix_len=(1, 20), suffix_len=(1, 9), vocab=5, seed=3))
+    R, W, B = 8, 4, 300
+    full = [O.run(s, W, B, replica=r, all_hits=True, router="random") for r in range(R)]
+    caps = sorted(max(w["pending_max"] for w in o["workers"]) for o in full)
+    assert caps[0] < caps[-1]
+    res, _ = gpu_run(s, R, W, B, router=K.KVR_ROUTE_RANDOM, pending_capacity=caps[-1] - 1)
+    assert res["status"] == K.KVR_ECAPACITY
+    ok = 0
+    for r in range(R):
+        if max(w["pending_max"] for w in full[r]["workers"]) < caps[-1]:
+            np.testing.assert_array_equal(res["route"][r], full[r]["route"])
+            np.testing.assert_array_equal(res["all_hits"][r], full[r]["all_hits"])
+            ok += 1
+    assert 0 < ok < R
