@@ -263,7 +263,6 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
     left -= rcap_p * 4u;
     ucap_p = left / (ne * 16u);
     if (ucap_p > 8192) ucap_p = 8192;
-    if (ucap_p < 64) ucap_p = 0;
     if (kvr::step_lds_bytes_pipe(L.maxL, L.W, nbuf, (uint32_t)ucap_p, (uint32_t)rcap_p) > 65536) {
       e = kvr::set_step_lds_limit(lds_room);
       if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(max dynamic LDS)");

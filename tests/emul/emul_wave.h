@@ -51,6 +51,7 @@ inline unsigned atomicCAS(unsigned* p, unsigned c, unsigned v) {
 inline unsigned long long atomicAdd(unsigned long long* p, unsigned long long v) { unsigned long long o = *p; *p += v; return o; }
 inline int atomicMin(int* p, int v) { int o = *p; if (v < o) *p = v; return o; }
 inline int atomicSub(int* p, int v) { int o = *p; *p -= v; return o; }
+inline unsigned atomicAdd(unsigned* p, unsigned v) { unsigned o = *p; *p += v; return o; }
 inline int atomicAdd(int* p, int v) { int o = *p; *p += v; return o; }
 inline int __shfl_xor(int v, int, int) { return v; }
 inline int __shfl_up(int v, int, int) { return v; }

@@ -27,6 +27,15 @@ def random_response_stream(rng: np.random.Generator, n: int, vocab: int, max_pro
                   out_len=np.array(olen, dtype=np.uint16), spec={"kind": "random_responses", "n": n})
 
 
+def stream_of(rng: np.random.Generator, paths) -> Stream:
+    """The prompts of `paths`, in order, up to 0.1 s apart."""
+    off = np.zeros(len(paths) + 1, dtype=np.uint64)
+    off[1:] = np.cumsum([len(p) for p in paths])
+    return Stream(tokens=np.concatenate(paths).astype(np.int32), offsets=off,
+                  arrival_us=np.cumsum(rng.integers(1, 100000, size=len(paths))).astype(np.int64),
+                  out_len=np.full(len(paths), 4, dtype=np.uint16), spec={"kind": "paths", "n": len(paths)})
+
+
 def long_beside_short_stream(rng: np.random.Generator, cycles: int, W: int, long_len: int, short_len: int,
                              quiet: int = 8) -> Stream:
     """For W > quiet + 1 workers in round-robin order.  Each cycle brings the
@@ -46,9 +55,4 @@ def long_beside_short_stream(rng: np.random.Generator, cycles: int, W: int, long
             old = last if last is not None and rng.integers(0, 4) else new
             paths.append(old[:int(rng.integers(1, long_len + 1))])
         last = new
-    lens = [len(p) for p in paths]
-    off = np.zeros(len(paths) + 1, dtype=np.uint64)
-    off[1:] = np.cumsum(lens)
-    return Stream(tokens=np.concatenate(paths), offsets=off,
-                  arrival_us=np.cumsum(rng.integers(1, 100000, size=len(paths))).astype(np.int64),
-                  out_len=np.full(len(paths), 4, dtype=np.uint16), spec={"kind": "long_beside_short", "n": len(paths)})
+    return stream_of(rng, paths)

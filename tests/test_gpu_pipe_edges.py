@@ -9,7 +9,7 @@ import pytest
 import paper_2601_18999_amd as K
 from gpu_helpers import assert_parity, gpu_run, note
 from oracle import oracle as O
-from streams import long_beside_short_stream
+from streams import long_beside_short_stream, stream_of
 from workload import generate, small_spec
 
 pytestmark = pytest.mark.gpu
@@ -114,3 +114,25 @@ def test_a_replica_that_fails_stops_no_other_in_later_parts():
             np.testing.assert_array_equal(res["all_hits"][r], full[r]["all_hits"])
             ok += 1
     assert 0 < ok < R
+
+
+@pytest.mark.parametrize("W,max_len,B", [
+    (4, 5848, 9000),     # 512 staged candidates: longer lists have a byte for each
+    (3, 5848, 40000),    # lists of more than 8,192, which have none
+    (64, 16384, 16384),  # some 30 staged candidates, bytes up to 480
+])
+def test_lists_longer_than_the_staging_area(W, max_len, B):
+    """Thousands of short leaves and now and then a long prompt, whose evictions
+    take whole blocks of draws."""
+    rng = np.random.default_rng(W + B)
+    n = {4: 6000, 3: 60000, 64: 4000}[W]
+    paths = [rng.integers(0, 1 << 20, size=int(rng.integers(1, 8))) if j % 41 or j < n // 2 else
+             rng.integers(0, 1 << 20, size=int(rng.integers(300, min(4000, max_len)))) for j in range(n)]
+    if W == 64:
+        paths = [p if j % 8 else rng.integers(0, 1 << 20, size=int(rng.integers(1, 400))) for j, p in enumerate(paths)]
+        paths[::63] = [rng.integers(0, 1 << 20, size=int(rng.integers(4000, 16000))) for _ in paths[::63]]
+    s = stream_of(rng, paths)
+    res, stats = gpu_run(s, 1, W, B, batch=1500, max_len=max_len, router=K.KVR_ROUTE_ROUND_ROBIN)
+    note(f"W={W} B={B} evictions={sum(w['evictions'] for w in stats[0])} nodes={max(w['nodes'] for w in stats[0])}")
+    assert sum(w["evictions"] for w in stats[0]) > 20000
+    assert_parity(s, res, stats, W, B, range(1), router="round_robin")
