@@ -2542,6 +2542,15 @@ fail:
 #define KVR_MATCH_UNROLL 8
 #endif
 
+// Four words at any word address.
+#if KVR_WAVE > 1
+typedef int Words4 __attribute__((ext_vector_type(4), aligned(4)));
+#else
+struct Words4 {
+  int x, y, z, w;
+};
+#endif
+
 // Number of leading words of the edge ar[eo, eo + n) that equal q[d, d + n)
 // (q in LDS).  A new edge is placed so that its 16-byte
 // blocks line up with the query buffer's (`place_edge`), and splits and
@@ -2549,7 +2558,7 @@ fail:
 // per lane in flight, with no branch in the round (lanes past the end read the
 // last block again).  Blocks reach up to three words outside the edge, inside
 // the same aligned 16 bytes; those words are masked.  An edge that a collection
-// had to pack closer is compared word by word.
+// had to pack closer is read by 16-byte loads at any word.
 template <int kU>
 __device__ __forceinline__ int32_t same_words(const int32_t* ar, uint32_t eo, const int32_t* q, int32_t d, int32_t n) {
   const uint32_t ea = (uint32_t)(reinterpret_cast<uintptr_t>(ar + eo) >> 2);
@@ -2581,19 +2590,37 @@ __device__ __forceinline__ int32_t same_words(const int32_t* ar, uint32_t eo, co
     }
     return n;
   }
+  // four words per lane from any place, and the last n & 3 words one by one
   constexpr int kW = 4;
-  for (int32_t b = 0; b < n; b += kW * KVR_WAVE) {
-    int32_t v[kW];
+  const int32_t nb = n >> 2;
+  const Words4* eb = reinterpret_cast<const Words4*>(ar + eo);
+  const Words4* qb = reinterpret_cast<const Words4*>(q + d);
+  for (int32_t b = 0; b < nb; b += kW * KVR_WAVE) {
+    Words4 v[kW];
 #pragma unroll
     for (int u = 0; u < kW; ++u) {
       const int32_t k = b + u * KVR_WAVE + lane_id();
-      v[u] = ar[eo + (uint32_t)(k < n ? k : n - 1)];
+      if (u == 0 || b + u * KVR_WAVE < nb) v[u] = eb[k < nb ? k : nb - 1];
     }
 #pragma unroll
     for (int u = 0; u < kW; ++u) {
-      const int32_t k = b + u * KVR_WAVE + lane_id();
-      const uint64_t m = __ballot(k < n && v[u] != q[d + (k < n ? k : n - 1)]);
-      if (m) return b + u * KVR_WAVE + first_lane(m);
+      const int32_t k0 = b + u * KVR_WAVE + lane_id();
+      const int32_t k = k0 < nb ? k0 : nb - 1;
+      const Words4 w = qb[k];
+      const uint32_t ne = (v[u].x != w.x ? 1u : 0u) | (v[u].y != w.y ? 2u : 0u) | (v[u].z != w.z ? 4u : 0u) |
+                          (v[u].w != w.w ? 8u : 0u);
+      const uint64_t m = __ballot(ne != 0u);
+      if (m) return __builtin_amdgcn_readlane(k * 4 + (__ffsll((unsigned long long)ne) - 1), first_lane(m));
+      if (b + (u + 1) * KVR_WAVE >= nb) break;
+    }
+  }
+  const int32_t at = 4 * nb, rest = n - at;
+  if (rest > 0) {
+    const int32_t k = at + (lane_id() < rest ? lane_id() : rest - 1);
+    for (int32_t c = 0; c < rest; c += KVR_WAVE) {
+      const int32_t x = KVR_WAVE == 1 ? at + c : k;
+      const uint64_t m = __ballot(ar[eo + (uint32_t)x] != q[d + x]);
+      if (m) return KVR_WAVE == 1 ? x : at + first_lane(m);
     }
   }
   return n;
@@ -2889,12 +2916,11 @@ __device__ __forceinline__ uint64_t wave_xor_u64(uint64_t v) {
 constexpr int kTok = 16;
 __device__ __forceinline__ void load_round(const int32_t* ar, uint64_t A, uint64_t at, int32_t rest, int32_t (&t)[kTok]) {
 #if KVR_WAVE > 1
-  typedef int words4 __attribute__((ext_vector_type(4), aligned(4)));
   const bool past = at + kTok > A;
   const int32_t* p = ar + (past ? 0 : at);
 #pragma unroll
   for (int c = 0; c < kTok; c += 4) {
-    const words4 v = *reinterpret_cast<const words4*>(p + c);
+    const Words4 v = *reinterpret_cast<const Words4*>(p + c);
     t[c] = v.x;
     t[c + 1] = v.y;
     t[c + 2] = v.z;

@@ -136,3 +136,15 @@ def test_lists_longer_than_the_staging_area(W, max_len, B):
     note(f"W={W} B={B} evictions={sum(w['evictions'] for w in stats[0])} nodes={max(w['nodes'] for w in stats[0])}")
     assert sum(w["evictions"] for w in stats[0]) > 20000
     assert_parity(s, res, stats, W, B, range(1), router="round_robin")
+
+
+@pytest.mark.parametrize("evict", ["rlt", "lru"])
+def test_edges_that_a_collection_has_packed(evict):
+    """The smallest arena: the collector packs, and matches compare edges at any
+    place within 16 bytes, of lengths around a round of compares (1,024)."""
+    s = generate(small_spec(n=300, groups=8, prefix_len=(900, 1200), suffix_len=(1, 1100), vocab=3, seed=11))
+    W, B = 3, 6000
+    arena = B + 2 * s.max_len + 64
+    res, stats = gpu_run(s, 2, W, B, batch=100, arena_words=arena, evict={"rlt": 0, "lru": 1}[evict])
+    assert min(sum(w["gc_runs"] for w in st) for st in stats) > 10
+    assert_parity(s, res, stats, W, B, range(2), evict=evict)
