@@ -548,34 +548,41 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 // blocks.  While that leaves half of the semispace free, an edge keeps its
 // place within its 16 bytes (new edges are placed in line with the query
 // buffer, so that matches compare 16 bytes per lane); else edges are packed,
-// padded to an even length.  False (and nothing switched) when the live data
-// does not fit a semispace.
+// padded to an even length, and where that leaves less than `need` words, without
+// padding, behind all the child arrays.  False (and nothing switched) when the
+// live data does not fit a semispace.
 // Out of line (it runs rarely) and with scalar arguments only, so the
 // caller's cache state never has to live in memory.  Returns the new arena
 // top, or ~0 when the live data does not fit.
 __device__ __noinline__ uint64_t collect_arena(NodeRec* nodes, const int32_t* src, int32_t* dst, uint32_t hwm,
-                                               uint32_t A, const int32_t* ssrc, int32_t* sdst) {
+                                               uint32_t A, uint32_t need, const int32_t* ssrc, int32_t* sdst) {
   wave_mem_sync();  // the caller's stores (e.g. a new edge) before they are copied
   const uint32_t sbase = (uint32_t)(reinterpret_cast<uintptr_t>(src) >> 2);
   const uint32_t dbase = (uint32_t)(reinterpret_cast<uintptr_t>(dst) >> 2);
-  uint64_t top = 0, top4 = 0;
+  uint64_t top = 0, top4 = 0, edges = 0, arrays = 0;
   // sizes first: the live data must fit
   for (uint32_t b = 0; b < hwm; b += KVR_WAVE) {
     const uint32_t x = b + (uint32_t)lane_id();
-    uint32_t sz = 0, sz4 = 0;
+    uint32_t sz = 0, sz4 = 0, szl = 0, sza = 0;
     if (x < hwm) {
       const NodeRec nd = nodes[x];
       if (nd.parent != -2) {
+        szl = (uint32_t)nd.len;
+        sza = 2u * (uint32_t)nd.ccap;
         sz = (((uint32_t)nd.len + 1u) & ~1u) + 2u * (uint32_t)nd.ccap;
         sz4 = ((((sbase + nd.off) & 3u) + (uint32_t)nd.len + 3u) & ~3u) + ((2u * (uint32_t)nd.ccap + 3u) & ~3u);
       }
     }
     top += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(sz), KVR_WAVE - 1);
     top4 += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(sz4), KVR_WAVE - 1);
+    edges += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(szl), KVR_WAVE - 1);
+    arrays += (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(sza), KVR_WAVE - 1);
   }
-  if (top > A) return ~0ull;
-  const bool in_line = top4 + 4u <= A / 2u;
-  top = in_line ? (0u - dbase) & 3u : 0u;
+  if (edges + arrays > A) return ~0ull;
+  const bool in_line = top4 + 4u <= A / 2u && top4 + 4u + need <= A;
+  const bool dense = !in_line && top + need > A;
+  top = in_line ? (0u - dbase) & 3u : dense ? arrays : 0u;
+  uint32_t atop = 0;  // (dense: the next child array)
   for (uint32_t b = 0; b < hwm; b += KVR_WAVE) {
     const uint32_t x = b + (uint32_t)lane_id();
     NodeRec nd;
@@ -588,12 +595,18 @@ __device__ __noinline__ uint64_t collect_arena(NodeRec* nodes, const int32_t* sr
     if (x < hwm) nd = nodes[x];
     const bool live = x < hwm && nd.parent != -2;
     const uint32_t place = in_line ? (sbase + nd.off) & 3u : 0u;
-    const uint32_t grain = in_line ? 3u : 1u;
+    const uint32_t grain = in_line ? 3u : dense ? 0u : 1u;
     const uint32_t elen = live ? (place + (uint32_t)nd.len + grain) & ~grain : 0u;
-    const uint32_t sz = live ? elen + ((2u * (uint32_t)nd.ccap + grain) & ~grain) : 0u;
+    const uint32_t alen = live ? (2u * (uint32_t)nd.ccap + grain) & ~grain : 0u;
+    const uint32_t sz = elen + (dense ? 0u : alen);
     const uint32_t incl = wave_inclusive_sum(sz);
     const uint32_t noff = (uint32_t)top + incl - sz + place;
-    const uint32_t ncoff = (uint32_t)top + incl - sz + elen;
+    uint32_t ncoff = (uint32_t)top + incl - sz + elen;
+    if (dense) {
+      const uint32_t ainc = wave_inclusive_sum(alen);
+      ncoff = atop + ainc - alen;
+      atop += (uint32_t)__builtin_amdgcn_readlane((int)ainc, KVR_WAVE - 1);
+    }
     uint64_t todo = __ballot(live);
     while (todo) {
       const int j = first_lane(todo);
@@ -618,9 +631,10 @@ __device__ __noinline__ uint64_t collect_arena(NodeRec* nodes, const int32_t* sr
   return top;
 }
 
-__device__ __forceinline__ bool collect(const Ptrs& P, St& s) {
+// A collection for an allocation of `need` words.
+__device__ __forceinline__ bool collect(const Ptrs& P, St& s, uint32_t need) {
   const uint64_t top =
-      collect_arena(P.nodes, arena_of(P, s.arena_sel), arena_of(P, s.arena_sel ^ 1u), s.hwm, P.A,
+      collect_arena(P.nodes, arena_of(P, s.arena_sel), arena_of(P, s.arena_sel ^ 1u), s.hwm, P.A, need,
                     P.stamp0 ? P.stamp0 + (size_t)s.arena_sel * P.A : nullptr,
                     P.stamp0 ? P.stamp0 + (size_t)(s.arena_sel ^ 1u) * P.A : nullptr);
   const uint32_t top_lo = uni((uint32_t)top);  // (an out-of-line call's result is wave-uniform, but not known to be)
@@ -635,7 +649,7 @@ __device__ __forceinline__ bool arena_alloc(const Ptrs& P, St& s, uint32_t words
   uint64_t top = s.arena_top;
   if (even) top = (top + 1u) & ~1ull;
   if (top + words > P.A) {
-    if (!collect(P, s)) {
+    if (!collect(P, s, words + (even ? 1u : 0u))) {
       s.err |= KVR_DEV_ARENA_FULL;
       return false;
     }

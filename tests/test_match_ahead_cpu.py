@@ -8,6 +8,7 @@ import subprocess
 import numpy as np
 import pytest
 
+import emul_kernel as E
 import paper_2601_18999_amd as K
 from oracle import oracle as O
 from workload import generate, small_spec
@@ -79,3 +80,20 @@ def test_shared_prefix_workload(replay):
     s = generate(small_spec(n=300, groups=12, prefix_len=(128, 700), suffix_len=(32, 128), vocab=32000, seed=3))
     total = check(replay, s, 1, 3, 6000, "nlms", 1, 512, 9)
     assert total[1] > 0, total
+
+
+@pytest.mark.parametrize("seed,words", [(14, 1.0), (362, 1.0), (880, 1.0), (13, 1.5), (921, 1.5), (666, 2), (703, 2)])
+def test_arenas_that_the_live_data_just_fits(replay, seed, words):
+    """Short edges in next to the smallest arena: a collection must not need more
+    room than the words that are live, padding or not."""
+    rng = np.random.default_rng(seed)
+    s = generate(small_spec(n=int(rng.integers(50, 300)), groups=int(rng.integers(1, 8)),
+                            prefix_len=(1, int(rng.integers(2, 6))), suffix_len=(1, int(rng.integers(2, 9))),
+                            vocab=int(rng.integers(2, 12)), seed=seed))
+    W = int(rng.integers(1, 4))
+    B = int(max(s.max_len, rng.integers(2, 300)))
+    arena = int((B + 2 * s.max_len + 64) * words)
+    check(replay, s, 1, W, B, "nlms", seed, 8192, seed, arena_words=arena)
+    e = E.run(s, 1, W, B, seed=seed, arena_words=arena)
+    assert e["rc"] == 0 and sum(w["gc_runs"] for w in e["workers"][0]) > 0
+    np.testing.assert_array_equal(e["all_hits"][0], O.run(s, W, B, replica=0, all_hits=True, seed=seed)["all_hits"])
