@@ -732,10 +732,14 @@ __device__ __forceinline__ bool can_match(uint32_t sv, uint32_t m, uint32_t k, u
   return (sv == (c | kOwner | kLoaded | kMarked) && ahead <= kJobs) || (sv == (c | kOwner | kLoaded) && ahead < nbuf);
 }
 
-// Take the match that state sv allows; false when another wave was first.
+// Take the match that state sv allows; false when another wave was first.  (An
+// acquire: the word may have gone through another insertion and come back to sv
+// since it was read.)
 __device__ __forceinline__ bool claim_match(uint32_t* st, uint32_t sv) {
-  uint32_t old = 0;
-  if (lane_id() == 0) old = atomicCAS(st, sv, sv | kReader);
+  uint32_t old = sv;
+  if (lane_id() == 0)
+    __hip_atomic_compare_exchange_strong(st, &old, sv | kReader, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
   return uni(old) == sv;
 }
 
@@ -792,7 +796,10 @@ __device__ __forceinline__ void take_match(const MatchArea& a, const Ptrs& P, ui
       __hip_atomic_fetch_add(st, (1u << kCountShift) - kReader, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   } else if (lane_id() == 0) {
     // put off until the owner is done, or to be taken again if it just was
-    if (atomicCAS(st, sv | kReader, sv | kDeferred) != (sv | kReader)) atomicAnd(st, ~kReader);
+    uint32_t old = sv | kReader;
+    if (!__hip_atomic_compare_exchange_strong(st, &old, sv | kDeferred, __ATOMIC_RELEASE, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP))
+      __hip_atomic_fetch_and(st, ~kReader, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 

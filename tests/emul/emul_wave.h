@@ -40,8 +40,16 @@ template <typename T> inline T __hip_atomic_fetch_add(T* p, T v, int, int) { KVR
 template <typename T> inline T __hip_atomic_fetch_or(T* p, T v, int, int) { KVR_EMUL_STEP(); T o = *p; *p |= v; return o; }
 template <typename T> inline T __hip_atomic_fetch_and(T* p, T v, int, int) { KVR_EMUL_STEP(); T o = *p; *p &= v; return o; }
 template <typename T> inline T __hip_atomic_fetch_max(T* p, T v, int, int) { T o = *p; if (v > o) *p = v; return o; }
+inline bool __hip_atomic_compare_exchange_strong(unsigned* p, unsigned* c, unsigned v, int, int, int) {
+  KVR_EMUL_STEP();
+  if (*p == *c) {
+    *p = v;
+    return true;
+  }
+  *c = *p;
+  return false;
+}
 inline unsigned atomicOr(unsigned* p, unsigned v) { KVR_EMUL_STEP(); unsigned o = *p; *p |= v; return o; }
-inline unsigned atomicAnd(unsigned* p, unsigned v) { KVR_EMUL_STEP(); unsigned o = *p; *p &= v; return o; }
 inline unsigned atomicCAS(unsigned* p, unsigned c, unsigned v) {
   KVR_EMUL_STEP();
   const unsigned o = *p;
