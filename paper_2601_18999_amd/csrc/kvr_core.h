@@ -232,6 +232,9 @@ struct St {
   int64_t dbg_val[3];
 };
 
+// A condition that hardly ever holds: the code under it is placed out of the way.
+#define KVR_RARE(x) __builtin_expect(!!(x), 0)
+
 #define KVR_FAIL_CHECK(s, id, a, b, c) \
   do {                                 \
     (s).err |= KVR_DEV_INTERNAL;       \
@@ -1062,6 +1065,9 @@ __device__ __forceinline__ int32_t await_rank(const InsertArgs& ia) {
 // of them at once (measured faster than starting on the first rounds).
 constexpr uint32_t kAwaitAllRounds = 4;
 
+#ifndef KVR_AWAIT_POLLS
+#define KVR_AWAIT_POLLS (1u << 22)
+#endif
 // Wait (bounded) until draw words [0, need) of rw are written (need <= rn).
 // Returns the count of words known to be there, at least need, or 0 if the
 // wait ran out (the caller then computes every word itself).
@@ -1077,7 +1083,7 @@ __device__ __forceinline__ uint32_t await_words(const InsertArgs& ia, uint32_t n
       const uint64_t have = (uint64_t)want * ia.round;
       return have < ia.rn ? (uint32_t)have : ia.rn;
     }
-    if (++spins > (1u << 22)) return 0u;
+    if (++spins > KVR_AWAIT_POLLS) return 0u;
     __builtin_amdgcn_s_sleep(2);
   }
 }
@@ -1311,14 +1317,14 @@ __device__ __forceinline__ DrawsEnd evict_draws(NodeRec* nodes, const int32_t* U
     const uint32_t d = dctr + (uint32_t)(r * KVR_WAVE + lane);
     bool exact = false;
     if (act[r] && d < rn) exact = draw_index_hi(rw[d], nU, kk[r]);
-    if (act[r] && !exact) kk[r] = (uint32_t)__umul64hi(draw_word_slow(jg, worker, d, seed, replica), (uint64_t)nU);
+    if (KVR_RARE(act[r] && !exact)) kk[r] = (uint32_t)__umul64hi(draw_word_slow(jg, worker, d, seed, replica), (uint64_t)nU);
   }
   bool bad = false;
 #pragma unroll
   for (int r = 0; r < kD; ++r) n[r] = act[r] ? U[kk[r]] : 0;
 #pragma unroll
   for (int r = 0; r < kD; ++r) bad |= act[r] && (n[r] <= 0 || (uint32_t)n[r] >= hwm);
-  if (__ballot(bad)) {
+  if (KVR_RARE(__ballot(bad))) {
     out.bad = 10;
     return out;
   }
@@ -1331,7 +1337,7 @@ __device__ __forceinline__ DrawsEnd evict_draws(NodeRec* nodes, const int32_t* U
     e[r] = nd.len - top;
     bad |= act[r] && (e[r] <= 0 || nd.nchild != 0 || nd.parent < 0);
   }
-  if (__ballot(bad)) {
+  if (KVR_RARE(__ballot(bad))) {
     out.bad = 11;
     return out;
   }
@@ -1427,12 +1433,14 @@ __device__ __forceinline__ bool evict_block_counted(const Ptrs& P, St& s, const 
 }
 
 // What the second half of an insertion does with its new leaf's place in the
-// leaf list and with the worker's state: by default the first half has
-// entered the leaf already, and the state goes back to the header.
+// leaf list, with the worker's state and with draw words that do not come: by
+// default the first half has entered the leaf already, the state goes back to
+// the header, and the words are computed here.
 struct HeaderHook {
   // called before anything edits or reads the leaf list
   __device__ __forceinline__ void before_list(const Ptrs&, St&) {}
   __device__ __forceinline__ void keep(const Ptrs& P, const St& s) { store_st(P.hdr, s); }
+  __device__ __forceinline__ void words_late(St&) {}
 };
 
 // evict_block with U staged in LDS (same draws, same result), kDraws draws
@@ -1476,7 +1484,7 @@ __device__ __forceinline__ bool evict_block_staged(const Ptrs& P, St& s, const I
     for (int r = 0; r < kDraws; ++r) act[r] = (uint32_t)(r * KVR_WAVE + lane) < cnt;
     exact = false;
   }
-  if (__ballot(!exact)) {
+  if (KVR_RARE(__ballot(!exact))) {
     // rare: whole words for this block
 #pragma unroll
     for (int r = 0; r < kDraws; ++r)
@@ -1546,7 +1554,7 @@ __device__ __forceinline__ bool evict_block_staged(const Ptrs& P, St& s, const I
       KVR_FAIL_CHECK(s, 11, (int32_t)cnt, f, 1);
       return false;
     }
-  } else if (over) {
+  } else if (KVR_RARE(over)) {
     // a candidate without an evictable token
     KVR_FAIL_CHECK(s, 11, (int32_t)cnt, first_lane(over), 0);
     return false;
@@ -1961,7 +1969,7 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
     InsertArgs iq = job.ia;
     // draw words [0, have) are known to be written; before a block reads
     // words past that, wait for the drawing waves' rounds to cover them
-    // (bounded: past it the words are computed here instead)
+    // (bounded; past it the words are computed here instead, or the run fails)
     uint32_t have = iq.prog ? 0u : iq.rn;
     while (k < nev) {
       const int32_t p = h + (int32_t)nfree + (int32_t)k;
@@ -1979,7 +1987,7 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
         if (s.err) goto fail;
         rebuild_U(P, s, l);
       }
-      if (s.nU == 0) {
+      if (KVR_RARE(s.nU == 0)) {
         // no unmarked leaf: a new phase starts with the current token
         if (staged) {
           stage_out(P, s, ustage);
@@ -2005,7 +2013,7 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
       // draws for positions p, p+1, ...: never across a pending phase reset
       uint32_t lim = nev;
       if (reset_at >= 0 && !applied && (uint32_t)(reset_at - p) < nev - k) lim = k + (uint32_t)(reset_at - p);
-      if (staged) {
+      if (!KVR_RARE(!staged)) {
         // blocks against the staged list until the limit or until U changes;
         // the loop state is wave-uniform, so keep it in scalar registers
         uint32_t ku = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
@@ -2019,7 +2027,11 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
           if (du + cnt > have && have < iq.rn) {
             const uint32_t need = du + cnt < iq.rn ? du + cnt : iq.rn;
             have = await_words(iq, need);
-            if (have == 0u) iq.rn = 0;
+            if (KVR_RARE(have == 0u)) {
+              hook.words_late(s);
+              if (s.err) goto fail;
+              iq.rn = 0;
+            }
           }
           uint32_t done = 0;
           bool changed = false;
@@ -2040,7 +2052,11 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
         if (dctr + cnt > have && have < iq.rn) {
           const uint32_t need = (uint32_t)dctr + cnt < iq.rn ? (uint32_t)dctr + cnt : iq.rn;
           have = await_words(iq, need);
-          if (have == 0u) iq.rn = 0;
+          if (KVR_RARE(have == 0u)) {
+            hook.words_late(s);
+            if (s.err) goto fail;
+            iq.rn = 0;
+          }
         }
         uint32_t done = 0;
         hook.before_list(P, s);

@@ -36,6 +36,7 @@ struct Hook {
     }
   }
   void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
+  void words_late(St& s) { KVR_FAIL_CHECK(s, 7, job.k, job.worker, job.rn); }
 };
 
 }  // namespace

@@ -177,10 +177,12 @@ struct WaveHook {
     }
   }
   void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
+  void words_late(St& s) { KVR_FAIL_CHECK(s, 7, job.k, job.worker, job.rn); }
 };
 
 }  // namespace
 
+// hold_draws: one insertion in so many has its draws held back (0: none).
 // counts: matches whose insertion (of query k) ended between the claim and the
 // verdict, [0] in all, [1] of query k + 5 and later; [2] matches put off; [3]
 // insertions that were open when the seventh after them was loaded; [4] matches
@@ -188,7 +190,7 @@ struct WaveHook {
 extern "C" int emul_waves(const kvr_config* cfg, uint64_t n64, const int32_t* tokens, const uint64_t* offsets,
                           const int64_t* arrival, const uint16_t* out_len, int32_t* route, int32_t* hits,
                           int32_t* all_hits, kvr_worker_stats* out, uint32_t ucap, uint32_t nbuf, int32_t router,
-                          uint64_t order_seed, uint64_t* counts) {
+                          uint64_t order_seed, uint32_t hold_draws, uint64_t* counts) {
   const Layout L = make_layout(*cfg);
   std::vector<uint64_t> mem((L.total + 255) / 8 + 32);
   char* ws = reinterpret_cast<char*>(((uintptr_t)mem.data() + 255) & ~(uintptr_t)255);
@@ -517,12 +519,16 @@ extern "C" int emul_waves(const kvr_config* cfg, uint64_t n64, const int32_t* to
                 const uint32_t best = best_of[slot];
                 uint32_t* rw = words.data() + slot * L.maxL;
                 uint32_t rounds = 0;
+                // held back in its draws until later insertions have the slot
+                if (hold_draws && s.coin(hold_draws) == 0)
+                  s.hold(1 + s.coin(2 * rn), [&, k] { return f.handed > k + kJobs; });
                 for (uint32_t d = 0; d < rn; d += 2) {
                   for (uint32_t x = d; x < d + 2 && x < rn; ++x)
                     rw[x] = (uint32_t)(philox_word0(k, best, x, 0ull, C.seed, r) >> 32);
                   prog[slot][0] = ++rounds;
                   emul_step();
                 }
+                s.now->after = 0;
               }
             }
             continue;
