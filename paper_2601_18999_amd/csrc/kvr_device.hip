@@ -1384,6 +1384,15 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
                                                : 0u;
         const uint32_t m = routed + (((sv >> kCountShift) - routed) & kCountMask);
         const bool ok = (uint32_t)lane < W && m < lim && can_match(sv, m, owner_sh[lane & (kMaxWorkers - 1u)], a.nbuf);
+        // all that are zero, a worker per lane (in the form for many workers)
+        if constexpr (NW > kPipeWaves) {
+          const bool took = ok && take_zero_match(ma, m, (uint32_t)lane, sv);
+          if (__ballot(took)) {
+            spins = 0;
+            clock_mark<PT>(&clk, KVR_PHASE_H_MATCH);
+            continue;
+          }
+        }
         uint64_t can = __ballot(ok && m == routed);
         if (!can) can = __ballot(ok && m == routed + 1u);
         if (!can) can = __ballot(ok);

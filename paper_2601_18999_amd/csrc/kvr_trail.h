@@ -803,6 +803,37 @@ __device__ __forceinline__ void take_match(const MatchArea& a, const Ptrs& P, ui
   }
 }
 
+// Is the match of query m on worker w zero without a look at the tree?  (As
+// match_ahead finds it: no cached path starts with its first token, or the query
+// before shares a token with it and has none cached here.)
+__device__ __forceinline__ bool zero_match(const MatchArea& a, uint32_t m, uint32_t w) {
+  const int32_t ell = m > 0u ? a.ell[(m - 1u) & 7u] : 0;
+  const int32_t count = a.trail[(query_slot(m + a.nbuf - 1u, a.nbuf) * a.W + w) * kTrailWords];
+  if (ell > 0 && count <= kPathMax) return count == 0;
+  return !rf_may(a.rootf + w * kRootFilterWords, a.q[query_slot(m, a.nbuf) * a.qstride]);
+}
+
+// Take the match of query m on worker w, whose state is sv and allows it, if it is
+// zero.  One lane's work: the lanes of a wave do so for as many workers at once,
+// where a wave takes any other match alone.
+__device__ __forceinline__ bool take_zero_match(const MatchArea& a, uint32_t m, uint32_t w, uint32_t sv) {
+  uint32_t* st = &a.state[w];
+  uint32_t old = sv;
+  if (!zero_match(a, m, w) ||
+      !__hip_atomic_compare_exchange_strong(st, &old, sv | kReader, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WORKGROUP))
+    return false;
+  if (!zero_match(a, m, w)) {  // (the word may have come back to sv since it was read)
+    __hip_atomic_fetch_and(st, ~kReader, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return false;
+  }
+  const uint32_t mp = query_slot(m, a.nbuf);
+  a.h[mp * kMaxWorkers + w] = 0;
+  a.trail[(mp * a.W + w) * kTrailWords] = 0;
+  __hip_atomic_fetch_add(st, (1u << kCountShift) - kReader, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return true;
+}
+
 // What the routing wave knows of the insertion of a path of L tokens with h
 // cached into a worker with this state (which nothing changes until the load).
 __device__ __forceinline__ void plan_insertion(PipeJob& job, const uint32_t* state, uint32_t B, uint32_t maxL, int32_t h,

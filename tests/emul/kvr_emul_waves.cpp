@@ -186,7 +186,8 @@ struct WaveHook {
 // counts: matches whose insertion (of query k) ended between the claim and the
 // verdict, [0] in all, [1] of query k + 5 and later; [2] matches put off; [3]
 // insertions that were open when the seventh after them was loaded; [4] matches
-// beside an insertion that were accepted past the inserted path
+// beside an insertion that were accepted past the inserted path; [5] matches
+// taken as zero
 extern "C" int emul_waves(const kvr_config* cfg, uint64_t n64, const int32_t* tokens, const uint64_t* offsets,
                           const int64_t* arrival, const uint16_t* out_len, int32_t* route, int32_t* hits,
                           int32_t* all_hits, kvr_worker_stats* out, uint32_t ucap, uint32_t nbuf, int32_t router,
@@ -259,6 +260,7 @@ extern "C" int emul_waves(const kvr_config* cfg, uint64_t n64, const int32_t* to
     Sched s;
     s.rs = order_seed * 2 + 1;
     s.rate = 4 + (uint32_t)(order_seed % 5) * 12;
+    const bool zeros = order_seed % 2 == 0;  // (as in the form for many workers)
     const auto match = [&](uint32_t m, uint32_t w, uint32_t sv) {
       const uint32_t k = owner[w];
       const uint64_t before = mtok[w];
@@ -573,7 +575,12 @@ extern "C" int emul_waves(const kvr_config* cfg, uint64_t n64, const int32_t* to
             for (uint32_t x = 0; x < W; ++x) {
               const uint32_t w = (x + hw * W / kHelpers) % W, sv = state[w];
               const uint32_t m = v.routed + (((sv >> kCountShift) - v.routed) & kCountMask);
-              if (m >= lim || !can_match(sv, m, owner[w], nbuf) || (mw < W && m >= mm)) continue;
+              if (m >= lim || !can_match(sv, m, owner[w], nbuf)) continue;
+              if (zeros && take_zero_match(ma, m, w, sv)) {
+                counts[5] += 1;
+                continue;
+              }
+              if (mw < W && m >= mm) continue;
               mw = w;
               mm = m;
               msv = sv;
