@@ -661,13 +661,18 @@ static_assert(sizeof(PipeFlags) == 4 * kFlagWords + 32, "counters, then the erro
 #endif
 constexpr int kPipeMatchUnroll = KVR_PIPE_MATCH_UNROLL;
 constexpr uint32_t kSpinLimit = 1u << 24;
-// Waves per workgroup: 12 (three per SIMD, 168 registers a lane; against 8,
+// Waves per workgroup: 12 (three per SIMD, 150 registers a lane; against 8,
 // multi-turn 51.0 ms a simulation instead of 55.3, the paper's groups in
 // round-robin order 67.9 instead of 77.8, the rest within 3%), and 16 for
-// replicas of many workers, whose matches of one query keep more helpers busy:
-// 128 registers and some scratch, but the long-prompt workload (32 workers)
-// takes 135.7 ms instead of 140.9.  At 16 workers 16 waves are 2% slower
-// (multi-turn, 46.2 against 45.2 ms), so the line is drawn between the two.
+// replicas of many workers, whose matches of one query keep more helpers busy
+// (128 registers and some scratch), and whose lanes take the matches that are zero
+// (take_zero_match; in the 12-wave form it costs 1 to 2%).  16 against 12 waves, in
+// ms a simulation of long prompts, of conversations and of short prompts:
+//   12 workers: 15.83 / 15.60, 15.77 / 15.44, 12.10 / 12.06
+//   16 workers: 14.46 / 14.50, 15.33 / 15.18, 11.72 / 12.13
+//   18 workers: 13.45 / 13.83, 15.10 / 15.09, 11.81 / 12.63
+//   22 workers: 12.26 / 13.49, 14.86 / 15.44, 10.72 / 13.00
+// and the line lies between 16 and 18.
 #ifndef KVR_PIPE_WAVES
 #define KVR_PIPE_WAVES 12
 #endif
@@ -675,7 +680,7 @@ constexpr uint32_t kSpinLimit = 1u << 24;
 #define KVR_PIPE_WAVES_WIDE 16
 #endif
 #ifndef KVR_PIPE_WIDE_WORKERS
-#define KVR_PIPE_WIDE_WORKERS 24
+#define KVR_PIPE_WIDE_WORKERS 17
 #endif
 constexpr uint32_t kPipeWaves = KVR_PIPE_WAVES;
 constexpr uint32_t kPipeWavesWide = KVR_PIPE_WAVES_WIDE;
@@ -1601,13 +1606,17 @@ hipError_t launch_init(char* ws, const Layout& L, double rls_p0, hipStream_t st)
 
 // Batches of at most this many tokens (at the longest) are checked by the step
 // kernel itself, each workgroup for itself, instead of by two kernels before it:
-// 3 us less a call up to 256 replicas (26.7 to 22.4 us for one short query).  At
-// 33,000 tokens the two are equal (217 us), above it the kernels are ahead.
+// 3 us less a call (26.7 to 22.4 us for one short query).  At 33,000 tokens the two
+// are equal (217 us), above it the kernels are ahead.  With one query a call, the
+// time of 96 calls is 5.29 instead of 5.55 ms for 512 replicas, 10.05 instead of
+// 10.23 for 1,024, and 38.1 instead of 37.7 for 4,096, where each compute unit checks
+// the batch 16 times.
 #ifndef KVR_CHECK_TOKENS
 #define KVR_CHECK_TOKENS 8192
 #endif
 constexpr uint64_t kCheckTokens = KVR_CHECK_TOKENS;
 constexpr uint32_t kCheckQueries = 256;  // (four rounds of a wave's lanes over their lengths)
+constexpr uint32_t kCheckReplicas = 1024;
 
 // A launch of the pipelined kernel takes at most this many queries: its counters
 // run up to (queries + 4) x helper waves in 32 bits, and a launch more costs
@@ -1638,7 +1647,7 @@ void launch_pipe(const StepArgs& a, size_t lds, hipStream_t st) {
 
 hipError_t launch_step(const StepArgs& args, hipStream_t st) {
   StepArgs a = args;
-  a.check = a.n <= kCheckQueries && (uint64_t)a.n * a.L.maxL <= kCheckTokens ? 1u : 0u;
+  a.check = a.n <= kCheckQueries && (uint64_t)a.n * a.L.maxL <= kCheckTokens && a.L.R <= kCheckReplicas ? 1u : 0u;
   if (!a.check) {
     const uint32_t blocks_v = (a.n + 255) / 256 < 1024 ? (a.n + 255) / 256 : 1024;
     hipLaunchKernelGGL(validate_kernel, dim3(blocks_v ? blocks_v : 1), dim3(256), 0, st, a.ws, a.L,

@@ -1,5 +1,5 @@
 """The pipelined step kernel where its forms change, bit-exact against the
-oracle on an MI355X: 12 or 16 waves (at 24 workers), two, three or four query
+oracle on an MI355X: 12 or 16 waves (at 17 workers), two, three or four query
 buffers (by the LDS that max_query_tokens leaves), a ring of draw words that
 holds no whole insertion, the learned router's form or the baselines', and
 batches checked by the step kernel itself or by kernels before it."""
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("router", ["lbgr", "cache_aware"])
 @pytest.mark.parametrize("W,max_len", [
     (1, 4000),              # one worker: every query is routed to it
-    (23, 900), (24, 900),   # 12 and 16 waves
+    (16, 900), (17, 900),   # 12 and 16 waves
+    (23, 900), (24, 900),
     (4, 5848), (4, 5860),   # four and three query buffers
     (4, 7044), (4, 7056),   # three and two
     (64, 16384),            # two, and no room for draw words or candidates
@@ -148,3 +149,11 @@ def test_edges_that_a_collection_has_packed(evict):
     res, stats = gpu_run(s, 2, W, B, batch=100, arena_words=arena, evict={"rlt": 0, "lru": 1}[evict])
     assert min(sum(w["gc_runs"] for w in st) for st in stats) > 10
     assert_parity(s, res, stats, W, B, range(2), evict=evict)
+
+
+@pytest.mark.parametrize("R", [1024, 1025])
+def test_batches_checked_for_many_replicas(R):
+    """Up to 1,024 replicas the step kernel checks a small batch itself."""
+    s = generate(small_spec(n=40, groups=3, prefix_len=(1, 9), suffix_len=(1, 6), vocab=5, seed=R))
+    res, stats = gpu_run(s, R, 2, 60, batch=7)
+    assert_parity(s, res, stats, 2, 60, [0, 511, R - 1])
