@@ -49,11 +49,6 @@ struct kvr_ctx {
 
 namespace {
 
-#ifndef KVR_MAX_BUF
-#define KVR_MAX_BUF 4
-#endif
-constexpr uint32_t kMaxBuf = KVR_MAX_BUF;  // query buffers of the pipelined step kernel
-
 thread_local std::string g_err;
 
 kvr_status fail(kvr_status st, const std::string& msg) {
@@ -254,7 +249,7 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
     // words of two whole insertions still fit beside it, then the draw words
     // of one insertion more than are evicted at once, then more candidates
     const size_t ufirst = ne * 512u * 16u;
-    for (uint32_t b = 3; b <= kMaxBuf; ++b)
+    for (uint32_t b = 3; b <= kvr::kMaxBuf; ++b)
       if (kvr::step_lds_bytes_pipe(L.maxL, L.W, b, 512, 2u * L.maxL) <= lds_room) nbuf = b;
     size_t left = lds_room - kvr::step_lds_bytes_pipe(L.maxL, L.W, nbuf, 0, 0);
     rcap_p = (left > ufirst ? left - ufirst : 0u) / 4u;

@@ -819,7 +819,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   int32_t* stage_base = reinterpret_cast<int32_t*>(ring + a.rcap);
 
   __shared__ PipeFlags f;
-  __shared__ int32_t h_sh[4][kMaxWorkers];  // h of q_k in slot query_slot(k)
+  __shared__ int32_t h_sh[kMaxBuf][kMaxWorkers];  // h of q_k in slot query_slot(k)
   __shared__ double eh_sh[kMaxWorkers];
   __shared__ int32_t ell_sh[8];             // LCP(q_k, q_k+1) in slot k & 7
   __shared__ int32_t len_sh[8], olen_sh[8]; // length and output length of q_k
@@ -852,7 +852,7 @@ __global__ void __launch_bounds__(64 * NW) step_kernel_pipe(StepArgs a) {
   if (threadIdx.x < KVR_PHASES) eticks_sh[threadIdx.x] = 0ull;
   if (threadIdx.x < kMaxWorkers) {
     mtok_sh[threadIdx.x] = 0ull;
-    for (uint32_t b = 0; b < 4u; ++b) h_sh[b][threadIdx.x] = 0;
+    for (uint32_t b = 0; b < kMaxBuf; ++b) h_sh[b][threadIdx.x] = 0;
   }
   if (threadIdx.x < 8u) ell_sh[threadIdx.x] = 0x7fffffff;
   if (threadIdx.x < kJobs) {

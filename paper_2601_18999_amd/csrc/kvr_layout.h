@@ -148,6 +148,14 @@ struct Consts {
   int32_t phase_timers;     // 1: accumulate the routing wave's ticks per part of a step
 };
 
+// Query buffers of the pipelined step kernel: two to kMaxBuf (query_slot has forms
+// for two, three and four, and the rings of query data have eight slots).
+#ifndef KVR_MAX_BUF
+#define KVR_MAX_BUF 4
+#endif
+constexpr uint32_t kMaxBuf = KVR_MAX_BUF;
+static_assert(kMaxBuf >= 2 && kMaxBuf <= 4, "query_slot and the rings of query data are made for two to four");
+
 // Arguments of one batch for the step kernel (device pointers).
 struct StepArgs {
   char* ws;
