@@ -144,6 +144,15 @@ std::string describe_bits(uint32_t bits) {
 
 extern "C" {
 
+// What a context's step kernel was laid out as (internal, for the tests): out =
+// {pipelined, query buffers, draw words, staged candidates of an evicting wave}.
+void kvr_internal_form(const kvr_ctx* c, uint32_t out[4]) {
+  out[0] = c->pipe;
+  out[1] = c->pipe ? c->nbuf : 2u;
+  out[2] = c->pipe ? c->rcap_p : c->rcap;
+  out[3] = c->pipe ? c->ucap_p : c->ucap;
+}
+
 void kvr_config_default(kvr_config* c, uint32_t R, uint32_t W, uint32_t B, uint32_t maxL) {
   if (!c) return;
   std::memset(c, 0, sizeof(*c));
@@ -236,18 +245,21 @@ kvr_status kvr_init_replicas(const kvr_config* cfg, void* d_workspace, size_t by
     if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(max dynamic LDS)");
   }
   // the pipelined kernel (RLT, prompts only, no router tree, single-query
-  // processing), where its state fits
+  // processing)
   const size_t lds_room = (size_t)lds_max - static_lds;
-  const bool pipe = cfg->evict == KVR_EVICT_RLT && !cfg->router_tree && cfg->batch_size == 1 && !cfg->cache_responses &&
-                    kvr::step_lds_bytes_pipe(L.maxL, L.W, 2, 0, 0) <= lds_room;
+  const bool pipe = cfg->evict == KVR_EVICT_RLT && !cfg->router_tree && cfg->batch_size == 1 && !cfg->cache_responses;
+  if (pipe && kvr::step_lds_bytes_pipe(L.maxL, L.W, 2, 0, 0) > lds_room)  // (64 workers and 16,384 tokens fit)
+    return fail(KVR_EINVAL, "max_query_tokens does not fit in LDS (" + std::to_string(lds_max) + " bytes)");
   size_t rcap_p = 0, ucap_p = 0;
   uint32_t nbuf = 2;
   if (pipe) {
     const size_t ne = kvr::step_pipe_evictors();
-    // 512 staged candidates per evicting wave first (the candidate lists are
-    // short on these workloads), then a third query buffer where the draw
-    // words of two whole insertions still fit beside it, then the draw words
-    // of one insertion more than are evicted at once, then more candidates
+    // 512 staged candidates per evicting wave first (longer lists are evicted from
+    // in memory, with a byte per candidate in the same area), then a third and a
+    // fourth query buffer where the draw words of two whole insertions still fit
+    // beside them, then the draw words of one insertion more than are evicted at
+    // once, then more candidates.  A third and a fourth buffer gain 10 and 5% on the
+    // two-level workload, 13 and 6% on multi-turn.
     const size_t ufirst = ne * 512u * 16u;
     for (uint32_t b = 3; b <= kvr::kMaxBuf; ++b)
       if (kvr::step_lds_bytes_pipe(L.maxL, L.W, b, 512, 2u * L.maxL) <= lds_room) nbuf = b;

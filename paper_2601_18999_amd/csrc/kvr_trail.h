@@ -1,15 +1,14 @@
 // kvr_trail.h - per-wave tree logic of the pipelined step kernel (included by
 // kvr_device.hip and by the single-lane replay): matches taken a query ahead
-// along recorded trails, the two halves of an insertion (the load of the new
-// leaf on the routing wave; marks, leaf list and evictions on an evicting
-// wave), and completions and decay on state kept in LDS.
+// along recorded trails, the order of a worker's matches and insertions, the two
+// halves of an insertion (the load of the new leaf; marks, leaf list and
+// evictions, both on an evicting wave), and completions and decay on state kept
+// in LDS.
 //
 // Everything a wave decides on is wave-uniform and is read as such: a node
 // record, a worker's state and a job are each read with one load, a word per
-// lane, and taken to scalar registers with readlane.  One instance of the
-// matching code serves every wave (step_kernel_pipe calls it at one place):
-// the kernel's code has to fit the 64 KB instruction cache that two compute
-// units share.
+// lane, and taken to scalar registers with readlane.  The matching code is in the
+// kernel twice, in the routing wave's loop and in the helpers'.
 #ifndef KVR_TRAIL_H
 #define KVR_TRAIL_H
 
@@ -110,8 +109,9 @@ __device__ __forceinline__ uint32_t query_slot(uint32_t k, uint32_t nbuf) {
 // The trail of a match: the nodes it entered, [0] = their number (kPathMax + 1
 // when there were more or they are unknown), then the nodes, then the depth
 // after each node's edge (entry e starts where entry e - 1 ends).  A worker
-// has one for the odd and one for the even queries, so that the next query
-// can be matched while the insertion of this one still needs its trail.
+// has as many as there are query buffers (nbuf, two to four; query k's in slot
+// query_slot(k)), so that the next queries can be matched while the insertion of
+// this one still needs its trail.
 constexpr int32_t kTrailWords = 2 * kPathMax + 1;
 
 __device__ __forceinline__ int32_t* trail_node(int32_t* t) { return t + 1; }

@@ -4,9 +4,12 @@ logic and the CPU oracle, both built with AddressSanitizer and
 UndefinedBehaviorSanitizer (every error aborts), on cases that reach every
 path: random streams under RLT and L-LRU with continuous batching, the
 approximate router tree, cached responses, collector pressure, the staged and
-unstaged candidate list, the pipelined order; the oracle's brute-force and
-invariant pins.  Exits non-zero on the first mismatch."""
+unstaged candidate list; the pipelined step kernel's wave logic (kvr_trail.h) in
+random orders of its waves; the oracle's brute-force and invariant pins.  Exits
+non-zero on the first mismatch."""
 import os
+import subprocess
+import tempfile
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -59,6 +62,27 @@ def main() -> int:
             assert o["rc"] == 0, (case, r, o["rc"])
             assert (e["route"][r] == o["route"]).all(), (case, r)
             assert (e["all_hits"][r] == o["all_hits"]).all(), (case, r)
+        cases += 1
+    # the pipelined step kernel's wave logic, in random orders
+    emul = os.path.join(HERE, "emul", "kvr_emul_ahead.cpp")
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "libahead_asan.so")
+        subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-fPIC", "-shared",
+                               "-Wno-unknown-pragmas", "-fsanitize=address,undefined", "-fno-omit-frame-pointer", "-o",
+                               out, emul], env={k: v for k, v in os.environ.items() if k != "LD_PRELOAD"})
+        ahead = ctypes.CDLL(out)
+    ahead.emul_ahead.restype = ctypes.c_int
+    ahead.emul_ahead.argtypes = ([ctypes.POINTER(K.KvrConfig), ctypes.c_uint64] + [ctypes.c_void_p] * 8 +
+                                 [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p])
+    from test_match_ahead_cpu import check as check_ahead
+    for case in range(24):
+        s = generate(small_spec(n=int(rng.integers(20, 120)), groups=int(rng.integers(1, 8)),
+                                prefix_len=(1, int(rng.integers(2, 40))), suffix_len=(1, int(rng.integers(2, 24))),
+                                vocab=int(rng.integers(2, 12)), seed=900 + case))
+        W = int(rng.integers(1, 6))
+        B = int(max(s.max_len, rng.integers(2, 260)))
+        tight = {"arena_words": 3 * (B + 2 * s.max_len + 64)} if case % 4 == 3 else {}
+        check_ahead(ahead, s, 1, W, B, ["nlms", "rls", "none"][case % 3], case, [8192, 4, 0][case % 3], case, **tight)
         cases += 1
     # the oracle against the brute-force model of tests/spec_model.py
     for seed in range(12):

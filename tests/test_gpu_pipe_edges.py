@@ -157,3 +157,26 @@ def test_batches_checked_for_many_replicas(R):
     s = generate(small_spec(n=40, groups=3, prefix_len=(1, 9), suffix_len=(1, 6), vocab=5, seed=R))
     res, stats = gpu_run(s, R, 2, 60, batch=7)
     assert_parity(s, res, stats, 2, 60, [0, 511, R - 1])
+
+
+@pytest.mark.parametrize("W,max_len,nbuf,words,staged", [
+    (1, 4000, 4, 12000, 900), (24, 900, 4, 2700, 3000),
+    (4, 5848, 4, 11696, 512), (4, 5860, 3, 17580, 512),
+    (4, 7044, 3, 14088, 512), (4, 7056, 2, 21168, 512),
+    (64, 16384, 2, 0, 20),
+])
+def test_the_form_is_the_one_that_the_rows_above_are_for(W, max_len, nbuf, words, staged):
+    """Query buffers, at least so many draw words, and so many candidates."""
+    import ctypes
+    sim = K.Simulator(1, W, max(max_len, 1000), max_len)
+    try:
+        out = (ctypes.c_uint32 * 4)()
+        f = K.load_library().kvr_internal_form
+        f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_void_p], None
+        f(sim.ctx, out)
+    finally:
+        sim.close()
+    note(f"W={W} max_len={max_len}: {list(out)}")
+    assert out[0] == 1 and out[1] == nbuf and out[2] >= words and out[3] >= staged
+    if (W, max_len) == (64, 16384):
+        assert out[2] == 0 and out[3] < 64
