@@ -1440,7 +1440,7 @@ struct HeaderHook {
   // called before anything edits or reads the leaf list
   __device__ __forceinline__ void before_list(const Ptrs&, St&) {}
   __device__ __forceinline__ void keep(const Ptrs& P, const St& s) { store_st(P.hdr, s); }
-  __device__ __forceinline__ void words_late(St&) {}
+  static constexpr bool kWordsMustCome = false;
 };
 
 // evict_block with U staged in LDS (same draws, same result), kDraws draws
@@ -2028,8 +2028,10 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
             const uint32_t need = du + cnt < iq.rn ? du + cnt : iq.rn;
             have = await_words(iq, need);
             if (KVR_RARE(have == 0u)) {
-              hook.words_late(s);
-              if (s.err) goto fail;
+              if constexpr (Hook::kWordsMustCome) {
+                hook.words_late(s);
+                goto fail;
+              }
               iq.rn = 0;
             }
           }
@@ -2053,8 +2055,10 @@ __device__ __forceinline__ uint32_t rlt_evict(const Ptrs& P, const EvictJob& job
           const uint32_t need = (uint32_t)dctr + cnt < iq.rn ? (uint32_t)dctr + cnt : iq.rn;
           have = await_words(iq, need);
           if (KVR_RARE(have == 0u)) {
-            hook.words_late(s);
-            if (s.err) goto fail;
+            if constexpr (Hook::kWordsMustCome) {
+              hook.words_late(s);
+              goto fail;
+            }
             iq.rn = 0;
           }
         }

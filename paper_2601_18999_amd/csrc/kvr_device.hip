@@ -783,6 +783,7 @@ struct PipeHook {
   __device__ __forceinline__ void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
   // the ring and the rounds' counts go to later insertions once this one ends: a
   // wave that still draws would write into theirs
+  static constexpr bool kWordsMustCome = true;
   __device__ __forceinline__ void words_late(St& s) { KVR_FAIL_CHECK(s, 7, job.k, job.worker, job.rn); }
 };
 

@@ -177,6 +177,7 @@ struct WaveHook {
     }
   }
   void keep(const Ptrs&, const St& s) { store_st_lds(state, s); }
+  static constexpr bool kWordsMustCome = true;
   void words_late(St& s) { KVR_FAIL_CHECK(s, 7, job.k, job.worker, job.rn); }
 };
 
